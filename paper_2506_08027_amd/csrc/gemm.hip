@@ -28,19 +28,11 @@
 // dwords per row). With 4-bit elements the instruction takes dwords 0..3 only, lane (r, g) holds K =
 // 32g..32g+31 of row r and its own scale byte applies to them (pinned on the hardware by a test that runs
 // single instructions on registers taken from memory).
-#include "mxfp8_device.h"
+#include "gemm_device.h"
+#include "gemm_staged.h"
 
 namespace mxfp8 {
 
-constexpr int BK = 128;  // K bytes per step = 4 scale blocks = one MFMA
-constexpr int kStageBytes = 4608;  // per-wavefront LDS area of the persistent kernel's epilogue (16 rows x (256 + 32) bytes)
-
-// Operand formats. kFmtFp8: MXFP8 operands with their scale bytes (the method itself), 128 elements and 4 scale
-// blocks per 128-byte K step. kFmtBf16: plain BF16 operands, 64 per K step, no scales (the product of the
-// simulated path of Section 3.1). kFmtFp4: MXFP4 operands (Table 1), two E2M1 codes per byte: 256 elements and
-// 8 scale blocks (two scale dwords per row) per K step. Everything about tiles, buffers, data requests and the
-// schedule is counted in BYTES of a K-contiguous operand row and is the same for all three.
-constexpr int kFmtFp8 = 0, kFmtBf16 = 1, kFmtFp4 = 2;
 // A_E5M2 / B_E5M2 (kFmtFp8 only): the elements of that operand are E5M2 instead of E4M3 (Section 3.2.2 compares the
 // two per tensor type); nothing but the format fields of the matrix instruction changes.
 template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, int FMT_ = kFmtFp8, bool A_E5M2_ = false, bool B_E5M2_ = false> struct GemmCfg {
@@ -72,65 +64,6 @@ template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, int FMT_ = kFmtFp8, bool
     static_assert(NA + NB < 64, "wait-count immediate");
 };
 
-// Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2. Renumber them so
-// that consecutive logical ids run on the same XCD, then walk the tile grid in column panels of
-// `PANEL` tiles so that the workgroups resident on one XCD share A rows and B rows in its L2.
-__device__ __forceinline__ int xcd_logical_id(int bid, int nblocks)
-{
-    constexpr int XCDS = 8;
-    const int full = (nblocks / XCDS) * XCDS;
-    return bid < full ? (bid % XCDS) * (nblocks / XCDS) + bid / XCDS : bid;
-}
-__device__ __forceinline__ void panel_tile(int lid, int tiles_m, int tiles_n, int &tm, int &tn)
-{
-    constexpr int PANEL = 8;
-    const int per_panel = PANEL * tiles_m;
-    const int panel = lid / per_panel;
-    const int in_panel = lid - panel * per_panel;
-    const int width = min(PANEL, tiles_n - panel * PANEL);
-    tm = in_panel / width;
-    tn = panel * PANEL + in_panel % width;
-}
-__device__ __forceinline__ void tile_of_block(int bid, int nblocks, int tiles_m, int tiles_n, int &tm,
-                                              int &tn)
-{
-    panel_tile(xcd_logical_id(bid, nblocks), tiles_m, tiles_n, tm, tn);
-}
-
-// Nothing may be scheduled across this point: the instruction order below is the schedule.
-#define MXFP8_PIN() __builtin_amdgcn_sched_barrier(0)
-// s_waitcnt vmcnt(n), other counters untouched (gfx9 encoding: vmcnt is split over bits 3:0 and 15:14)
-#define MXFP8_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
-
-// One K step of one 16x16 output tile. MXFP8: one scaled matrix instruction over 128 k (4 blocks per
-// operand row, scale byte 0 of each lane's scale register). BF16: the lane's two 16-byte pieces are k
-// 8g..8g+7 and 32+8g..32+8g+7 of the row's 64 values: two 16x16x32 instructions. MXFP4: the lane's two
-// 16-byte pieces are scale blocks g and 4+g of the row's 8 (with 4-bit elements a lane holds one whole block
-// and its own scale byte applies to it): two scaled instructions over 128 k each; the scale registers carry
-// the byte of block g in bits 7:0 and that of block 4+g in bits 15:8.
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-template <class Cfg>
-__device__ __forceinline__ v4f mma_step(const v8i &first, const v8i &second, v4f acc, int s_first, int s_second)
-{
-    constexpr int FMT = Cfg::FMT;
-    if constexpr (FMT == kFmtFp8) {
-        // format fields: 0 = E4M3, 1 = E5M2; the kernels feed B fragments as the first operand, A as the second
-        return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(first, second, acc, Cfg::B_E5M2 ? 1 : 0, Cfg::A_E5M2 ? 1 : 0, 0,
-                                                                s_first, 0, s_second);
-    } else if constexpr (FMT == kFmtFp4) {
-        const v8i f0 = {first[0], first[1], first[2], first[3], 0, 0, 0, 0}, f1 = {first[4], first[5], first[6], first[7], 0, 0, 0, 0};
-        const v8i s0 = {second[0], second[1], second[2], second[3], 0, 0, 0, 0}, s1 = {second[4], second[5], second[6], second[7], 0, 0, 0, 0};
-        acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(f0, s0, acc, 4, 4, 0, s_first & 0xFF, 0, s_second & 0xFF);
-        return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(f1, s1, acc, 4, 4, 0, (int)((uint32_t)s_first >> 8), 0,
-                                                                (int)((uint32_t)s_second >> 8));
-    } else {
-        const v4i f0 = {first[0], first[1], first[2], first[3]}, f1 = {first[4], first[5], first[6], first[7]};
-        const v4i s0 = {second[0], second[1], second[2], second[3]}, s1 = {second[4], second[5], second[6], second[7]};
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, f0), __builtin_bit_cast(v8bf, s0), acc, 0, 0, 0);
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, f1), __builtin_bit_cast(v8bf, s1), acc, 0, 0, 0);
-    }
-}
-
 // Expert groups of the grouped products (Appendix A.4), see gemm_persistent_kernel (rows of A grouped) and
 // gemm_kernel (the reduction axis grouped).
 struct GemmGroups {
@@ -138,18 +71,6 @@ struct GemmGroups {
     int count;
     int64_t b_group_bytes, bs_group_bytes;
 };
-
-// Scale register of one fragment from a scale buffer in LDS ([dword][row][4], `rows` tile rows): MXFP8 takes the
-// byte of the lane's K block, MXFP4 the bytes of blocks g and 4+g (same position in the two dwords of the row).
-template <class Cfg> __device__ __forceinline__ int read_scale(const uint8_t *sbuf, int off, int rows)
-{
-    if constexpr (Cfg::FMT == kFmtFp4)
-        return (int)sbuf[off] | ((int)sbuf[rows * 4 + off] << 8);
-    else if constexpr (Cfg::FMT == kFmtFp8)
-        return sbuf[off];
-    else
-        return 0;
-}
 
 // The kernel. LDS holds two A buffers, two B buffers and their scale dwords; the software pipeline
 // is described at the step lambda below.
@@ -424,16 +345,6 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_kernel(
         }
     }
 }
-
-// Workgroup barrier without the LDS fence of __syncthreads(): LDS reads issued before it may still be in
-// flight afterwards. The persistent kernel uses it where a barrier only publishes DMA-written buffers
-// (their arrival is tracked by vmcnt) and nothing that is still being read is handed back for overwriting.
-// Where a buffer IS handed back (end of a K step) the reads that can still be in flight are awaited first
-// (MXFP8_WAIT_VMCNT_AND_LDS): fragment reads that an already issued MFMA consumed have returned by
-// construction, the in-place refills of the A fragments are the only ones left.
-#define MXFP8_BARRIER() __builtin_amdgcn_s_barrier()
-// s_waitcnt vmcnt(n) lgkmcnt(0): additionally every LDS read of this wavefront has returned
-#define MXFP8_WAIT_VMCNT_AND_LDS(n) __builtin_amdgcn_s_waitcnt(0x0070 | ((n) & 15) | (((n) >> 4) << 14))
 
 // ---- persistent variant --------------------------------------------------------------------------
 // One workgroup per compute unit walks over several output tiles and keeps the K pipeline running
@@ -1040,26 +951,110 @@ static hipError_t launch_any(const uint8_t *a_q, const uint8_t *a_s, const uint8
                              int N, int K, void *c, bool c_bf16, bool tiled, int64_t ldc, int max_workgroups,
                              hipStream_t stream)
 {
-    if (tiled)
-        return c_bf16 ? launch_cfg<Cfg, true, true>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream)
-                      : launch_cfg<Cfg, false, true>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream);
+    if constexpr (Cfg::SCALED)
+        if (tiled)
+            return c_bf16 ? launch_cfg<Cfg, true, true>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream)
+                          : launch_cfg<Cfg, false, true>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream);
     return c_bf16 ? launch_cfg<Cfg, true, false>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream)
                   : launch_cfg<Cfg, false, false>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream);
+}
+
+// ---- staged kernel (gemm_staged.h): everything that 256x256 tiles cannot spread over the chip -------------------
+template <class Cfg, bool OUT_BF16, bool TILED>
+static hipError_t launch_staged_t(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s, int M, int N, int K,
+                                  void *c, int64_t ldc, int max_workgroups, hipStream_t stream)
+{
+    const int tiles_m = (M + Cfg::BM - 1) / Cfg::BM, tiles_n = (N + Cfg::BN - 1) / Cfg::BN;
+    const int64_t ldc_bytes = ldc * (OUT_BF16 ? 2 : 4);
+    const bool vec_store = (reinterpret_cast<uintptr_t>(c) % 16 == 0) && (ldc_bytes % 16 == 0);
+    const int ntiles = tiles_m * tiles_n;
+    const int grid = max_workgroups > 0 && max_workgroups < ntiles ? max_workgroups : ntiles;
+    auto kern = gemm_staged_kernel<Cfg, OUT_BF16, TILED>;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::lds_bytes(TILED));
+    if (e != hipSuccess)
+        return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Cfg::THREADS), Cfg::lds_bytes(TILED), stream, a_q, a_s, b_q, b_s, M, N, K,
+                       static_cast<uint8_t *>(c), ldc_bytes, tiles_m, tiles_n, vec_store);
+    return hipGetLastError();
+}
+
+template <class Cfg>
+static hipError_t launch_staged_cfg(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s, int M, int N, int K,
+                                    void *c, bool c_bf16, bool tiled, int64_t ldc, int max_workgroups, hipStream_t stream)
+{
+    if constexpr (Cfg::SCALED)
+        if (tiled)
+            return c_bf16 ? launch_staged_t<Cfg, true, true>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream)
+                          : launch_staged_t<Cfg, false, true>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream);
+    return c_bf16 ? launch_staged_t<Cfg, true, false>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream)
+                  : launch_staged_t<Cfg, false, false>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream);
+}
+
+// Which tile: an estimate of the time, what a launch costs around its K loop plus (rounds of tiles over the compute units)
+// x (K steps) x (time of a step), from measurements on an MI355X (MXFP8, row-major scales, us):
+//                           128x128   128x64   64x64   32x64   32x32
+//   [1000 x 2880 x 5760]      24.5     34.2     31.7    47.4    62.4
+//   [2048 x 3072 x 4096]      34.9     38.2     42.0    63.6    87.1
+//   [512 x 4096 x 4096]       17.3     14.1     16.4    24.0    31.5
+//   [48 x 6144 x 4096]        14.9     11.4      9.3     8.8     9.8
+//   [384 x 896 x 512]          5.7      4.5      3.7     3.3     3.4
+//   [304 x 704 x 640]          5.8      4.6      3.7     3.3     3.1
+//   [16 x 1024 x 2048]         9.0      7.1      5.5     5.2     4.5
+// A 128x128 step takes longer where every unit has several tiles (all units fetch all the time). The 256x256 tiles of the
+// kernels above take 1.5 us per step, but share each fetched byte among twice as many matrix instructions.
+enum class Tile { k256, k128, k128x64, k64x128, k64, k32x64, k32 };
+static Tile choose_tile(int64_t M, int64_t N, int64_t KT)
+{
+    struct Option { Tile tile; int bm, bn; double around_us, step_us, step_us_full; };
+    static const Option options[] = {{Tile::k256, 256, 256, 5.0, 1.45, 1.45}, {Tile::k128, 128, 128, 4.0, 0.43, 0.55},
+                                     {Tile::k128x64, 128, 64, 3.5, 0.32, 0.36}, {Tile::k64x128, 64, 128, 3.5, 0.32, 0.36},
+                                     {Tile::k64, 64, 64, 2.6, 0.215, 0.215}, {Tile::k32x64, 32, 64, 2.4, 0.19, 0.19},
+                                     {Tile::k32, 32, 32, 2.2, 0.165, 0.165}};
+    constexpr int64_t UNITS = 256;
+    Tile best = Tile::k256;
+    double least = 1e30;
+    for (const Option &o : options) {
+        const int64_t tiles = ((M + o.bm - 1) / o.bm) * ((N + o.bn - 1) / o.bn);
+        const double us = o.around_us + (double)((tiles + UNITS - 1) / UNITS * KT) * (tiles > UNITS ? o.step_us_full : o.step_us);
+        if (us < least) {
+            least = us;
+            best = o.tile;
+        }
+    }
+    return best;
+}
+
+// K in bytes of an operand row. The staged kernel fills a ring of four K steps before it starts.
+template <int FMT, bool A5, bool B5>
+static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s, int M, int N, int K,
+                                 void *c, bool c_bf16, bool tiled, int64_t ldc, int max_workgroups, hipStream_t stream)
+{
+    const bool many = (int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 128;
+    const Tile tile = K >= 4 * BK ? choose_tile(M, N, K / BK) : Tile::k256;
+#define MXFP8_STAGED(BM, BN) \
+    return launch_staged_cfg<StagedCfg<BM, BN, 2, 2, 4, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream)
+    switch (tile) {
+    case Tile::k128: MXFP8_STAGED(128, 128);
+    case Tile::k128x64: MXFP8_STAGED(128, 64);
+    case Tile::k64x128: MXFP8_STAGED(64, 128);
+    case Tile::k64: MXFP8_STAGED(64, 64);
+    case Tile::k32x64: MXFP8_STAGED(32, 64);
+    case Tile::k32: MXFP8_STAGED(32, 32);
+    case Tile::k256: break;
+    }
+#undef MXFP8_STAGED
+    // fewer than four K steps, or enough 256x256 tiles
+    if (many)
+        return launch_any<GemmCfg<256, 256, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream);
+    return launch_any<GemmCfg<128, 128, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream);
 }
 
 hipError_t launch_gemm(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s, int64_t M,
                        int64_t N, int64_t K, void *c, bool c_bf16, bool tiled_scales, int64_t ldc, int max_workgroups,
                        hipStream_t stream)
 {
-    using Big = GemmCfg<256, 256, 2, 2>;
-    using Small = GemmCfg<128, 128, 2, 2>;
-    // Small problems cannot fill 256 compute units with 256x256 tiles.
-    const bool big = ((M + 255) / 256) * ((N + 255) / 256) >= 128;
-    if (big)
-        return launch_any<Big>(a_q, a_s, b_q, b_s, (int)M, (int)N, (int)K, c, c_bf16, tiled_scales, ldc, max_workgroups,
-                               stream);
-    return launch_any<Small>(a_q, a_s, b_q, b_s, (int)M, (int)N, (int)K, c, c_bf16, tiled_scales, ldc, max_workgroups,
-                             stream);
+    return launch_product<kFmtFp8, false, false>(a_q, a_s, b_q, b_s, (int)M, (int)N, (int)K, c, c_bf16, tiled_scales, ldc,
+                                                 max_workgroups, stream);
 }
 
 // Grouped product over expert-sorted rows of A (see GemmGroups). Always the persistent kernel: N a multiple of
@@ -1150,28 +1145,16 @@ hipError_t launch_gemm_grouped(const uint8_t *a_q, const uint8_t *a_s, const uin
 }
 
 // MXFP8 product with the element format of each operand chosen by the caller (E4M3 or E5M2: Section 3.2.2).
-template <bool A5, bool B5>
-static hipError_t launch_gemm_elements_t(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s, int64_t M,
-                                         int64_t N, int64_t K, void *c, bool c_bf16, bool tiled_scales, int64_t ldc,
-                                         int max_workgroups, hipStream_t stream)
-{
-    using Big = GemmCfg<256, 256, 2, 2, kFmtFp8, A5, B5>;
-    using Small = GemmCfg<128, 128, 2, 2, kFmtFp8, A5, B5>;
-    const bool big = ((M + 255) / 256) * ((N + 255) / 256) >= 128;
-    if (big)
-        return launch_any<Big>(a_q, a_s, b_q, b_s, (int)M, (int)N, (int)K, c, c_bf16, tiled_scales, ldc, max_workgroups, stream);
-    return launch_any<Small>(a_q, a_s, b_q, b_s, (int)M, (int)N, (int)K, c, c_bf16, tiled_scales, ldc, max_workgroups, stream);
-}
-
 hipError_t launch_gemm_elements(const uint8_t *a_q, const uint8_t *a_s, bool a_e5m2, const uint8_t *b_q, const uint8_t *b_s,
                                 bool b_e5m2, int64_t M, int64_t N, int64_t K, void *c, bool c_bf16, bool tiled_scales, int64_t ldc,
                                 int max_workgroups, hipStream_t stream)
 {
+    const int m = (int)M, n = (int)N, k = (int)K;
     if (a_e5m2)
-        return b_e5m2 ? launch_gemm_elements_t<true, true>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled_scales, ldc, max_workgroups, stream)
-                      : launch_gemm_elements_t<true, false>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled_scales, ldc, max_workgroups, stream);
+        return b_e5m2 ? launch_product<kFmtFp8, true, true>(a_q, a_s, b_q, b_s, m, n, k, c, c_bf16, tiled_scales, ldc, max_workgroups, stream)
+                      : launch_product<kFmtFp8, true, false>(a_q, a_s, b_q, b_s, m, n, k, c, c_bf16, tiled_scales, ldc, max_workgroups, stream);
     if (b_e5m2)
-        return launch_gemm_elements_t<false, true>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled_scales, ldc, max_workgroups, stream);
+        return launch_product<kFmtFp8, false, true>(a_q, a_s, b_q, b_s, m, n, k, c, c_bf16, tiled_scales, ldc, max_workgroups, stream);
     return launch_gemm(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled_scales, ldc, max_workgroups, stream);
 }
 
@@ -1182,14 +1165,8 @@ hipError_t launch_gemm_fp4(const uint8_t *a_q, const uint8_t *a_s, const uint8_t
                            int64_t N, int64_t K, void *c, bool c_bf16, bool tiled_scales, int64_t ldc, int max_workgroups,
                            hipStream_t stream)
 {
-    using Big = GemmCfg<256, 256, 2, 2, kFmtFp4>;
-    using Small = GemmCfg<128, 128, 2, 2, kFmtFp4>;
-    const bool big = ((M + 255) / 256) * ((N + 255) / 256) >= 128;
-    if (big)
-        return launch_any<Big>(a_q, a_s, b_q, b_s, (int)M, (int)N, (int)(K / 2), c, c_bf16, tiled_scales, ldc, max_workgroups,
-                               stream);
-    return launch_any<Small>(a_q, a_s, b_q, b_s, (int)M, (int)N, (int)(K / 2), c, c_bf16, tiled_scales, ldc, max_workgroups,
-                             stream);
+    return launch_product<kFmtFp4, false, false>(a_q, a_s, b_q, b_s, (int)M, (int)N, (int)(K / 2), c, c_bf16, tiled_scales, ldc,
+                                                 max_workgroups, stream);
 }
 
 // Product of two BF16 operands, [M x K] and [N x K], both K-contiguous, FP32 accumulation: the GEMM of the
@@ -1198,16 +1175,8 @@ hipError_t launch_gemm_fp4(const uint8_t *a_q, const uint8_t *a_s, const uint8_t
 hipError_t launch_gemm_bf16(const uint8_t *a, const uint8_t *b, int64_t M, int64_t N, int64_t K, void *c, bool c_bf16,
                             int64_t ldc, int max_workgroups, hipStream_t stream)
 {
-    using Big = GemmCfg<256, 256, 2, 2, kFmtBf16>;
-    using Small = GemmCfg<128, 128, 2, 2, kFmtBf16>;
-    const bool big = ((M + 255) / 256) * ((N + 255) / 256) >= 128;
     const uint8_t *none = nullptr;
-    const int m = (int)M, n = (int)N, kbytes = (int)(2 * K);
-    if (big)
-        return c_bf16 ? launch_cfg<Big, true, false>(a, none, b, none, m, n, kbytes, c, ldc, max_workgroups, stream)
-                      : launch_cfg<Big, false, false>(a, none, b, none, m, n, kbytes, c, ldc, max_workgroups, stream);
-    return c_bf16 ? launch_cfg<Small, true, false>(a, none, b, none, m, n, kbytes, c, ldc, max_workgroups, stream)
-                  : launch_cfg<Small, false, false>(a, none, b, none, m, n, kbytes, c, ldc, max_workgroups, stream);
+    return launch_product<kFmtBf16, false, false>(a, none, b, none, (int)M, (int)N, (int)(2 * K), c, c_bf16, false, ldc, max_workgroups, stream);
 }
 
 // GEMM with BF16 output and MXFP8 copies of that output (axis bit 0: row-wise, bit 1: column-wise) from
