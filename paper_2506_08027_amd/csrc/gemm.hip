@@ -30,6 +30,7 @@
 // single instructions on registers taken from memory).
 #include "gemm_device.h"
 #include "gemm_staged.h"
+#include "quantize_tile.h"
 
 namespace mxfp8 {
 
@@ -357,17 +358,13 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_kernel(
 // Wait counts: the epilogue's stores also count in vmcnt. Loads complete in order among themselves,
 // so "at most n operations outstanding" still implies that all but the last n loads have landed,
 // whatever the stores do; the immediates of the K step stay valid (they can only wait longer).
-// FUSE_Q (BF16 output only; bit 0 = row-wise copy, bit 1 = column-wise copy): the epilogue also emits
-// MXFP8 copies of the BF16-rounded output tile (Section 2: the output is re-quantized when the next layer
-// needs it in MX format; Section 3.2: along rows and along columns; conversion of Section 3.3 /
-// Appendix A.1, A.2 applied to the BF16 values), scales in the same layout as the inputs.
-//   row-wise:    cq [M x N], cs = scales of C as an [M x N] operand. A 32-column block lies in two adjacent
-//                MFMA tiles of one row, 8 values in each of the 4 lanes that share the row.
-//   column-wise: cqT [N x M], csT = scales of C^T as an [N x M] operand. A 32-row block lies in two
-//                vertically adjacent MFMA tiles, 2 values in each of the 16 lanes of a DPP row. The bytes
-//                are transposed through the two LDS buffers that are idle between tiles (the B buffer the
-//                finished step read and the A buffer whose fragments already sit in registers) and leave
-//                as full lines of cqT.
+// FUSE_Q (BF16 output only; bit 0 = row-wise copy, bit 1 = column-wise copy): the epilogue also emits MXFP8 copies of the
+// BF16 output tile (Section 2: the output is re-quantized when the next layer needs it in MX format), scales in the same
+// layout as the inputs: cq [M x N], cs = scales of C as an [M x N] operand; cqT [N x M], csT = scales of C^T. As soon as
+// the tile is stored, the workgroup reads it back (from the L2 it was just written to) in 128x128 pieces and converts
+// those like the quantizer does. A conversion straight from the accumulators needs the amax and the transposed bytes of
+// values that lie spread over 16 lanes: it spilled 316 bytes per work-item and took 42 us per 256x256 tile
+// ([4096 x 14336 x 4096], both copies: 337 us, 259 us this way).
 #ifndef MXFP8_GEMM_SCHED
 #define MXFP8_GEMM_SCHED 242  // B requests behind every 2nd MFMA, a gap of 2, A requests behind every 4th
 #endif
@@ -387,9 +384,8 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
     uint8_t *__restrict__ csT, GemmGroups groups)
 {
     static_assert(!GROUPED || (FUSE_Q == 0 && Cfg::ALL_E4M3), "grouped products: MXFP8-E4M3 operands, plain epilogue");
-    static_assert(!FUSE_Q || (OUT_BF16 && (Cfg::TN == 8 || Cfg::TN == 4) && Cfg::TM == Cfg::TN), "fused output quantization");
-    constexpr bool Q_ROW = (FUSE_Q & 1) != 0, Q_COL = (FUSE_Q & 2) != 0;
-    static_assert(!Q_COL || Cfg::BM * Cfg::BN <= 2 * Cfg::B_BYTES, "transposed tile fits the two idle buffers");
+    static_assert(!FUSE_Q || (OUT_BF16 && Cfg::BM % kTile == 0 && Cfg::BN % kTile == 0 && Cfg::THREADS == kQuantThreads), "fused output quantization");
+    static_assert(!FUSE_Q || Cfg::WAVES * kStageBytes >= kTile * kTile + 2 * kTile * 4, "the converted tile fits the staging areas");
     static_assert(!Cfg::SCALED || (Cfg::SA_LOADS == Cfg::SDW && Cfg::SB_LOADS == Cfg::SDW), "one scale request per wavefront, operand and scale dword");
     static_assert(Cfg::ALL_E4M3 || FUSE_Q == 0, "output quantization belongs to the MXFP8-E4M3 product");
     MXFP8_DYNAMIC_LDS(lds);
@@ -653,8 +649,6 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
         // the wavefront's staging area, so that the converted values of only one row group are live at a
         // time next to the A fragments of the next tile.
         constexpr int ESZ = OUT_BF16 ? 2 : 4;
-        if constexpr (Q_COL)
-            __syncthreads();  // every wavefront's fragment refills have left the A buffer that is reused below
         uint8_t *ctile = c + (int64_t)cur_tile.m0 * ldc_bytes + (int64_t)cur_tile.n0 * ESZ;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
@@ -664,206 +658,55 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
 #pragma unroll
             for (int j = 0; j < TN; ++j)
                 MXFP8_KEEP_IN_ACC(acc[i][j]);
-            if constexpr (Q_ROW) {
-                // BF16 rows and their MXFP8 copy both leave through the wavefront's staging area (see the plain
-                // epilogue below for why): first the 16 BF16 rows, then, in the same area, the 16 byte rows.
-                const int64_t m = cur_tile.m0 + wm * Cfg::WM + i * 16 + r16;        // this lane's row of C
-                const int n_wave = cur_tile.n0 + wn * Cfg::WN;                       // first column of the wavefront
-                constexpr int ROWB = Cfg::WN * 2, PITCH = ROWB + 32;                 // BF16 row and its staged pitch
-                constexpr int QPITCH = Cfg::WN + 16;                                 // staged pitch of a byte row
-                static_assert(16 * PITCH <= kStageBytes && (16 * ROWB) % 1024 == 0 && (16 * Cfg::WN) % 1024 == 0, "staging area");
-                uint8_t *stage = lds + Cfg::LDS_BYTES + wave * kStageBytes;
-                uint32_t scales = 0;                                                 // scale bytes of the row's blocks
-                uint32_t q[TN];
+            // Row group i of this wavefront (16 rows x WN columns) goes through a wavefront-private LDS area
+            // so that it leaves as whole rows: a lane holds 4 consecutive columns of one row per MFMA tile,
+            // and storing those directly costs one partial cache line per row and instruction (the address
+            // unit of the compute unit then needs ~7 us per 256 x 256 tile, during which the matrix pipes
+            // wait behind their own stores). Staged, every store instruction writes 1 KB of contiguous rows.
+            constexpr int ROWB = Cfg::WN * ESZ;                            // bytes of one row of the wavefront's part
+            constexpr int PITCH = ROWB + 32;                               // staged row pitch: spreads the rows over the banks
+            constexpr int RPP = ROWB * 16 <= 4096 ? 16 : 4096 / ROWB;      // rows per pass (at most 4 KB staged)
+            static_assert(RPP * PITCH <= kStageBytes && (RPP * ROWB) % 1024 == 0, "staging area");
+            uint8_t *stage = lds + Cfg::LDS_BYTES + wave * kStageBytes;
 #pragma unroll
-                for (int blk = 0; blk < TN / 2; ++blk) {
-                    uint32_t h[4];  // BF16 pairs: columns 4g..4g+3 of tile 2*blk, then of tile 2*blk+1
+            for (int pass = 0; pass < 16 / RPP; ++pass) {
+                if (RPP == 16 || r16 / RPP == pass) {
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        const v4f v = acc[i][2 * blk + t];
-                        v2bf p0 = {(__bf16)v[0], (__bf16)v[1]}, p1 = {(__bf16)v[2], (__bf16)v[3]};
-                        h[2 * t] = __builtin_bit_cast(uint32_t, p0);
-                        h[2 * t + 1] = __builtin_bit_cast(uint32_t, p1);
-                        *reinterpret_cast<uint2 *>(stage + r16 * PITCH + ((2 * blk + t) * 16 + 4 * g) * 2) = make_uint2(h[2 * t], h[2 * t + 1]);
-                    }
-                    // block amax on the magnitude bits: 8 values here, then the 3 other lanes of the row
-                    uint32_t am = pk_max_u16(pk_max_u16(h[0] & 0x7FFF7FFFu, h[1] & 0x7FFF7FFFu),
-                                             pk_max_u16(h[2] & 0x7FFF7FFFu, h[3] & 0x7FFF7FFFu));
-                    am = umax(am & 0xFFFFu, am >> 16);
-                    am = umax(am, (uint32_t)__shfl_xor((int)am, 16, 64));
-                    am = umax(am, (uint32_t)__shfl_xor((int)am, 32, 64));
-                    const uint32_t sb = scale_byte_from_bf16_bits(am);
-                    const float sc = scale_operand(sb);
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        uint32_t qt = cvt2_bf16(cvt2_bf16(0, h[2 * t], sc, false), h[2 * t + 1], sc, true);
-                        if (sb >= 254) {  // NaN or Inf in the block: rare
-                            if (sb == 0xFF) {
-                                qt = 0x7F7F7F7Fu;
-                            } else {
-                                uint32_t f = 0;
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) {
-                                    const uint32_t bits = (e & 1) ? h[2 * t + e / 2] >> 16 : h[2 * t + e / 2] & 0xFFFFu;
-                                    f |= inf_byte_bf16(bits, (qt >> (8 * e)) & 0xFFu) << (8 * e);
-                                }
-                                qt = f;
-                            }
+                    for (int j = 0; j < TN; ++j) {
+                        const v4f v = acc[i][j];
+                        uint8_t *dst = stage + (r16 % RPP) * PITCH + (j * 16 + 4 * g) * ESZ;
+                        if constexpr (OUT_BF16) {
+                            v2bf p0 = {(__bf16)v[0], (__bf16)v[1]}, p1 = {(__bf16)v[2], (__bf16)v[3]};
+                            *reinterpret_cast<uint2 *>(dst) =
+                                make_uint2(__builtin_bit_cast(uint32_t, p0), __builtin_bit_cast(uint32_t, p1));
+                        } else {
+                            *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
                         }
-                        q[2 * blk + t] = qt;
                     }
-                    scales |= sb << (8 * blk);
                 }
                 __builtin_amdgcn_wave_barrier();  // the reads below see the other lanes' writes (LDS serves a wavefront in order)
 #pragma unroll
-                for (int t = 0; t < 16 * ROWB / 1024; ++t) {
+                for (int t = 0; t < RPP * ROWB / 1024; ++t) {
                     const int lin = t * 1024 + lane * 16, row = lin / ROWB, colb = lin % ROWB;
                     const uint4 v = *reinterpret_cast<const uint4 *>(stage + row * PITCH + colb);
-                    *reinterpret_cast<uint4 *>(crow + (int64_t)(wm * Cfg::WM + row) * ldc_bytes + wn * ROWB + colb) = v;
+                    if (!GROUPED || wm * Cfg::WM + i * 16 + pass * RPP + row < cur_tile.rows)
+                        *reinterpret_cast<uint4 *>(crow + (int64_t)(wm * Cfg::WM + pass * RPP + row) * ldc_bytes +
+                                                   wn * ROWB + colb) = v;
                 }
-                __builtin_amdgcn_wave_barrier();  // the byte rows overwrite the area after these reads
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    *reinterpret_cast<uint32_t *>(stage + r16 * QPITCH + j * 16 + 4 * g) = q[j];
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int t = 0; t < 16 * Cfg::WN / 1024; ++t) {
-                    const int lin = t * 1024 + lane * 16, row = lin / Cfg::WN, colb = lin % Cfg::WN;
-                    const uint4 v = *reinterpret_cast<const uint4 *>(stage + row * QPITCH + colb);
-                    *reinterpret_cast<uint4 *>(cq + (cur_tile.m0 + wm * Cfg::WM + i * 16 + row) * (int64_t)N + n_wave + colb) = v;
-                }
-                __builtin_amdgcn_wave_barrier();  // (the next row group overwrites the area after these reads)
-                if (g == 0) {  // the TN/2 scale bytes of this row and wavefront: one dword or halfword
-                    const int64_t nb = N / kBlock, b0 = n_wave / kBlock;
-                    uint8_t *sp = TILED ? cs + (((m >> 6) * ((nb + 3) / 4) + (b0 >> 2)) * 64 + (m & 63)) * 4 + (b0 & 3)
-                                        : cs + m * nb + b0;
-                    if constexpr (TN / 2 == 4)
-                        *reinterpret_cast<uint32_t *>(sp) = scales;
-                    else
-                        *reinterpret_cast<uint16_t *>(sp) = (uint16_t)scales;
-                }
-            } else {
-                // Row group i of this wavefront (16 rows x WN columns) goes through a wavefront-private LDS area
-                // so that it leaves as whole rows: a lane holds 4 consecutive columns of one row per MFMA tile,
-                // and storing those directly costs one partial cache line per row and instruction (the address
-                // unit of the compute unit then needs ~7 us per 256 x 256 tile, during which the matrix pipes
-                // wait behind their own stores). Staged, every store instruction writes 1 KB of contiguous rows.
-                constexpr int ROWB = Cfg::WN * ESZ;                            // bytes of one row of the wavefront's part
-                constexpr int PITCH = ROWB + 32;                               // staged row pitch: spreads the rows over the banks
-                constexpr int RPP = ROWB * 16 <= 4096 ? 16 : 4096 / ROWB;      // rows per pass (at most 4 KB staged)
-                static_assert(RPP * PITCH <= kStageBytes && (RPP * ROWB) % 1024 == 0, "staging area");
-                uint8_t *stage = lds + Cfg::LDS_BYTES + wave * kStageBytes;
-#pragma unroll
-                for (int pass = 0; pass < 16 / RPP; ++pass) {
-                    if (RPP == 16 || r16 / RPP == pass) {
-#pragma unroll
-                        for (int j = 0; j < TN; ++j) {
-                            const v4f v = acc[i][j];
-                            uint8_t *dst = stage + (r16 % RPP) * PITCH + (j * 16 + 4 * g) * ESZ;
-                            if constexpr (OUT_BF16) {
-                                v2bf p0 = {(__bf16)v[0], (__bf16)v[1]}, p1 = {(__bf16)v[2], (__bf16)v[3]};
-                                *reinterpret_cast<uint2 *>(dst) =
-                                    make_uint2(__builtin_bit_cast(uint32_t, p0), __builtin_bit_cast(uint32_t, p1));
-                            } else {
-                                *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
-                            }
-                        }
-                    }
-                    __builtin_amdgcn_wave_barrier();  // the reads below see the other lanes' writes (LDS serves a wavefront in order)
-#pragma unroll
-                    for (int t = 0; t < RPP * ROWB / 1024; ++t) {
-                        const int lin = t * 1024 + lane * 16, row = lin / ROWB, colb = lin % ROWB;
-                        const uint4 v = *reinterpret_cast<const uint4 *>(stage + row * PITCH + colb);
-                        if (!GROUPED || wm * Cfg::WM + i * 16 + pass * RPP + row < cur_tile.rows)
-                            *reinterpret_cast<uint4 *>(crow + (int64_t)(wm * Cfg::WM + pass * RPP + row) * ldc_bytes +
-                                                       wn * ROWB + colb) = v;
-                    }
-                    __builtin_amdgcn_wave_barrier();  // (the next pass overwrites the area after these reads)
-                }
+                __builtin_amdgcn_wave_barrier();  // (the next pass overwrites the area after these reads)
             }
             MXFP8_PIN();
         }
-        if constexpr (Q_COL) {
-            // Idle LDS between tiles: B buffer par^1 (read by the step that just ended) and A buffer par (its
-            // fragments are in registers). Transposed tile [column][BM row bytes]; the first half of the
-            // columns in the B buffer, the second half in the A buffer when one buffer is too small. The
-            // 16-byte chunk of a column line is XORed with (column / 4) so that the four lanes of a row,
-            // whose columns are 4 apart, write different banks.
-            constexpr bool SPLIT = Cfg::BM * Cfg::BN > Cfg::B_BYTES;
-            constexpr int COLS_PER_REGION = SPLIT ? Cfg::BN / 2 : Cfg::BN;
-            constexpr int CHUNKS = Cfg::BM / 16;  // 16-byte chunks per column line
-            uint8_t *region0 = lds + Cfg::B_OFF + (par ^ 1) * Cfg::B_BYTES;
-            uint8_t *region1 = lds + Cfg::A_OFF + par * Cfg::A_BYTES;
-            auto line_of = [&](int n_tile) __attribute__((always_inline)) {
-                return (SPLIT && n_tile >= COLS_PER_REGION ? region1 : region0) + (n_tile % COLS_PER_REGION) * Cfg::BM;
-            };
-            const int64_t nbT = M / kBlock;                                   // scale blocks per row of C^T
-            const int64_t bT0 = (cur_tile.m0 + wm * Cfg::WM) / kBlock;        // first row block of this wavefront
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-                    MXFP8_KEEP_IN_ACC(acc[i][j]);  // (see the row loop above)
-#pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    const int n_tile = wn * Cfg::WN + j * 16 + 4 * g + 2 * half;  // columns n_tile and n_tile + 1
-                    uint8_t *line0 = line_of(n_tile), *line1 = line_of(n_tile + 1);
-                    const int sw0 = (n_tile >> 2) & (CHUNKS - 1);                 // same for n_tile + 1
-                    uint32_t scales0 = 0, scales1 = 0;
-#pragma unroll
-                    for (int rb = 0; rb < TM / 2; ++rb) {
-                        // rows r16 and 16 + r16 of the 32-row block, as BF16 pairs (column n_tile low, n_tile + 1 high)
-                        const v4f va = acc[2 * rb][j], vb = acc[2 * rb + 1][j];
-                        v2bf pa = {(__bf16)va[2 * half], (__bf16)va[2 * half + 1]}, pb = {(__bf16)vb[2 * half], (__bf16)vb[2 * half + 1]};
-                        const uint32_t xa = __builtin_bit_cast(uint32_t, pa), xb = __builtin_bit_cast(uint32_t, pb);
-                        uint32_t am = pk_max_u16(xa & 0x7FFF7FFFu, xb & 0x7FFF7FFFu);
-                        am = pk_max_u16(am, dpp_xor1(am));
-                        am = pk_max_u16(am, dpp_xor2(am));
-                        am = pk_max_u16(am, dpp_half_mirror(am));
-                        am = pk_max_u16(am, dpp_mirror(am));
-                        const uint32_t sb0 = scale_byte_from_bf16_bits(am & 0xFFFFu), sb1 = scale_byte_from_bf16_bits(am >> 16);
-                        // (row r16, row 16 + r16) of one column as a BF16 pair
-                        const uint32_t c0 = __builtin_amdgcn_perm(xb, xa, 0x05040100u), c1 = __builtin_amdgcn_perm(xb, xa, 0x07060302u);
-                        uint32_t q0 = cvt2_bf16(0, c0, scale_operand(sb0), false) & 0xFFFFu;
-                        uint32_t q1 = cvt2_bf16(0, c1, scale_operand(sb1), false) & 0xFFFFu;
-                        if (sb0 >= 254)
-                            q0 = sb0 == 0xFF ? 0x7F7Fu
-                                             : inf_byte_bf16(c0 & 0xFFFFu, q0 & 0xFFu) | (inf_byte_bf16(c0 >> 16, q0 >> 8) << 8);
-                        if (sb1 >= 254)
-                            q1 = sb1 == 0xFF ? 0x7F7Fu
-                                             : inf_byte_bf16(c1 & 0xFFFFu, q1 & 0xFFu) | (inf_byte_bf16(c1 >> 16, q1 >> 8) << 8);
-                        const int m_lo = wm * Cfg::WM + rb * 32 + r16, m_hi = m_lo + 16;  // rows inside the tile
-                        line0[(((m_lo >> 4) ^ sw0) << 4) + (m_lo & 15)] = (uint8_t)q0;
-                        line0[(((m_hi >> 4) ^ sw0) << 4) + (m_hi & 15)] = (uint8_t)(q0 >> 8);
-                        line1[(((m_lo >> 4) ^ sw0) << 4) + (m_lo & 15)] = (uint8_t)q1;
-                        line1[(((m_hi >> 4) ^ sw0) << 4) + (m_hi & 15)] = (uint8_t)(q1 >> 8);
-                        scales0 |= sb0 << (8 * rb);
-                        scales1 |= sb1 << (8 * rb);
-                    }
-                    if (r16 == 0) {  // the TM/2 scale bytes of two columns of C^T: a dword or halfword each
-#pragma unroll
-                        for (int t = 0; t < 2; ++t) {
-                            const int64_t n = cur_tile.n0 + n_tile + t;
-                            uint8_t *sp = TILED ? csT + (((n >> 6) * ((nbT + 3) / 4) + (bT0 >> 2)) * 64 + (n & 63)) * 4 + (bT0 & 3)
-                                                : csT + n * nbT + bT0;
-                            if constexpr (TM / 2 == 4)
-                                *reinterpret_cast<uint32_t *>(sp) = t ? scales1 : scales0;
-                            else
-                                *reinterpret_cast<uint16_t *>(sp) = (uint16_t)(t ? scales1 : scales0);
-                        }
-                    }
-                }
-                MXFP8_PIN();
+        if constexpr (FUSE_Q) {
+            uint8_t *stage = lds + Cfg::LDS_BYTES;
+            const QuantLds qlds{stage, stage + kTile * kTile, stage + kTile * kTile + kTile * 4, nullptr, nullptr};
+            for (int part = 0; part < (Cfg::BM / kTile) * (Cfg::BN / kTile); ++part) {
+                __syncthreads();  // the tile of C is stored; the staging areas are free
+                quantize_tile<true, (FUSE_Q & 1) != 0, (FUSE_Q & 2) != 0, TILED, 0>(
+                    c, M, N, ldc_bytes, cq, cs, cqT, csT, nullptr, (uint32_t)(cur_tile.m0 / kTile + part / (Cfg::BN / kTile)),
+                    (uint32_t)(cur_tile.n0 / kTile + part % (Cfg::BN / kTile)), tid, qlds);
             }
-            __syncthreads();  // the transposed tile is complete
-#pragma unroll
-            for (int pass = 0; pass < Cfg::BN * CHUNKS / Cfg::THREADS; ++pass) {
-                const int chunk = pass * Cfg::THREADS + tid;
-                const int n_tile = chunk / CHUNKS, part = chunk % CHUNKS;
-                const uint4 v = *reinterpret_cast<const uint4 *>(line_of(n_tile) + ((part ^ ((n_tile >> 2) & (CHUNKS - 1))) << 4));
-                *reinterpret_cast<uint4 *>(cqT + (int64_t)(cur_tile.n0 + n_tile) * M + cur_tile.m0 + part * 16) = v;
-            }
-            __syncthreads();  // nobody requests the next tiles into these buffers while they are still read
+            __syncthreads();  // the next tile's rows are staged where the last piece was
         }
 #pragma unroll
         for (int i = 0; i < TM; ++i)

@@ -121,11 +121,11 @@ QUANT_MUTANTS = [
      "(abs_bits + 0x1FFFFFu) >> 23) - 8", "(abs_bits + 0x0FFFFFu) >> 23) - 8"),
     ("quantizer: BF16 scale rule carries at 1.875 instead of 1.75", "mxfp8_device.h",
      "(abs_bits16 + 0x1Fu) >> 7) - 8", "(abs_bits16 + 0x0Fu) >> 7) - 8"),
-    ("quantizer: staging swizzle of the transposed copy differs from the write-out's", "quantize.hip",
+    ("quantizer: staging swizzle of the transposed copy differs from the write-out's", "quantize_tile.h",
      "const int slot16 = (lrow0 >> 4) ^ (cc & 7);", "const int slot16 = (lrow0 >> 4) ^ ((cc + 1) & 7);"),
-    ("quantizer: barrier between staging and write-out removed", "quantize.hip",
-     "        __syncthreads();\n\n        // ---- write-out of the staged pieces", "\n        // ---- write-out of the staged pieces"),
-    ("quantizer: infinities keep the converter's NaN code in the row copy", "quantize.hip",
+    ("quantizer: barrier between staging and write-out removed", "quantize_tile.h",
+     "    __syncthreads();\n\n    // ---- write-out of the staged pieces", "\n    // ---- write-out of the staged pieces"),
+    ("quantizer: infinities keep the converter's NaN code in the row copy", "quantize_tile.h",
      "f0 |= inf_byte<BF16, MODE>(elem_at<BF16>(x[i], j), (q0 >> (8 * j)) & 0xFFu) << (8 * j);",
      "f0 |= ((q0 >> (8 * j)) & 0xFFu) << (8 * j);"),
     ("quantizer: MXFP4 scale rule carries at 1.75 instead of 1.5", "mxfp4.hip",
