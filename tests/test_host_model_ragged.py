@@ -1,0 +1,48 @@
+"""The resident product kernel on ragged problems (the last tiles are moved back to end with the operand) and with
+256x192 tiles, on the CPU execution model of the kernels: both scale layouts (with tiled scales a moved tile begins
+inside a 64-row group), several tiles per workgroup, all operand formats."""
+import numpy as np
+import pytest
+
+import test_host_model as fp8
+import test_host_model_fp4 as fp4
+import test_host_model_simulated as sim
+from test_host_model import MODES, hostmodel, run_case  # noqa: F401  (hostmodel is a fixture)
+
+# M, N, K steps, BF16 output, tiled scales, workgroup bound, simulated workgroups, mode
+CASES = [(2100, 4088, 3, True, True, 0, 3, 1), (2049, 4104, 2, True, False, 48, 2, 2), (2248, 3700, 3, False, True, 100, 2, 3)]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda s: "x".join(str(int(v)) for v in s))
+def test_ragged_resident_gemm(hostmodel, tmp_path, case):
+    M, N, steps, bf16, tiled, wg, blocks, mode = case
+    ops = fp8._operands(M, N, steps * 128, seed=M + N)
+    line, out = fp8._gemm_case(tmp_path, M, N, steps * 128, ops, bf16, tiled=tiled, wg=wg)
+    _, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_BLOCKS=blocks, **MODES[mode])
+    assert calls[0][0] == 0 and len(calls[0][1]) == blocks
+    fp8._check_gemm(out, M, N, N, ops, bf16, expect_full=False)
+
+
+def test_256x192_tiles(hostmodel, tmp_path):
+    """[2048 x 6144]: 256 tiles of 256x192 where 256x256 tiles would leave a quarter of the units idle; and ragged."""
+    for i, (M, N, steps, bf16, tiled) in enumerate(((2048, 6144, 5, True, True), (2040, 6136, 4, False, False))):
+        ops = fp8._operands(M, N, steps * 128, seed=7 + i)
+        line, out = fp8._gemm_case(tmp_path, M, N, steps * 128, ops, bf16, tiled=tiled, wg=128, tag=str(i))
+        _, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_BLOCKS=2, **MODES[3 * i])
+        assert calls[0] == (0, [0, 127])
+        n = fp8._check_gemm(out, M, N, N, ops, bf16, expect_full=False)
+        assert 3 * 256 * 192 < n <= 4 * 256 * 192
+
+
+def test_256x192_tiles_other_operand_formats(hostmodel, tmp_path):
+    M, N = 2048, 6144
+    ops = fp4._fp4_operands(M, N, 1024, seed=3)
+    line, out = fp4._fp4_gemm_case(tmp_path, M, N, 1024, ops, True, N, tiled=True)
+    _, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_BLOCKS=2)
+    assert calls[0][1] == [0, 255]
+    fp4._check_fp4_gemm(out, M, N, N, ops, True, expect_full=False)
+    ops = sim._operands(M, N, 320, seed=9)
+    line, out = sim._case(tmp_path, M, N, 320, ops, True)
+    _, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_BLOCKS=2, **MODES[3])
+    assert calls[0][1] == [0, 255]
+    sim._check(out, M, N, N, ops, True, expect_full=False)
