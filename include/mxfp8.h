@@ -164,10 +164,10 @@ mxfp8_status mxfp8_gemm(mxfp8_pass pass, const uint8_t *a_q, const uint8_t *a_s,
 /* mxfp8_gemm with a_s and b_s both stored in `scale_layout` (Section 2, Appendix A.3: same sum), on at
  * most `max_workgroups` compute units. Problems made of full output tiles (M and N multiples of 256, or of
  * 128 when ceil(M/256)*ceil(N/256) < 128; K >= 256; c 16-byte aligned with ldc*sizeof(element) a multiple
- * of 16) run as one resident workgroup per compute unit that walks over its share of the tiles;
+ * of 16) can be held to a number of workgroups that walk over their share of the tiles;
  * max_workgroups > 0 caps the number of those workgroups, e.g. to leave compute units to a kernel that
  * runs beside the product, max_workgroups == 0 takes every compute unit of the current device, a negative
- * value returns MXFP8_ERR_MODE. Other shapes take one workgroup per tile and ignore the bound. The result
+ * value returns MXFP8_ERR_MODE. Other shapes ignore the bound. The result
  * does not depend on it. */
 mxfp8_status mxfp8_gemm_ex(mxfp8_pass pass, const uint8_t *a_q, const uint8_t *a_s,
                            const uint8_t *b_q, const uint8_t *b_s, int64_t M, int64_t N, int64_t K,

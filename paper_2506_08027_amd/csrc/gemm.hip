@@ -883,22 +883,21 @@ static hipError_t launch_staged_cfg(const uint8_t *a_q, const uint8_t *a_s, cons
 //   [384 x 896 x 512]          5.7      4.5      3.7     3.3     3.4
 //   [304 x 704 x 640]          5.8      4.6      3.7     3.3     3.1
 //   [16 x 1024 x 2048]         9.0      7.1      5.5     5.2     4.5
-// A 128x128 step takes longer where every unit has several tiles (all units fetch all the time). The 256x256 tiles of the
+// A 128x128 step takes longer where all 256 units have several tiles (all of them fetch all the time). The 256x256 tiles of the
 // kernels above take 1.5 us per step, but share each fetched byte among twice as many matrix instructions.
 enum class Tile { k256, k256x192, k128, k128x64, k64x128, k64, k32x64, k32 };
-static Tile choose_tile(int64_t M, int64_t N, int64_t KT)
+static Tile choose_tile(int64_t M, int64_t N, int64_t KT, int64_t units)
 {
     struct Option { Tile tile; int bm, bn; double around_us, step_us, step_us_full; };
     static const Option options[] = {{Tile::k256, 256, 256, 5.0, 1.45, 1.45}, {Tile::k256x192, 256, 192, 5.0, 1.2, 1.2}, {Tile::k128, 128, 128, 4.0, 0.43, 0.55},
                                      {Tile::k128x64, 128, 64, 3.5, 0.32, 0.36}, {Tile::k64x128, 64, 128, 3.5, 0.32, 0.36},
                                      {Tile::k64, 64, 64, 2.6, 0.215, 0.215}, {Tile::k32x64, 32, 64, 2.4, 0.19, 0.19},
                                      {Tile::k32, 32, 32, 2.2, 0.165, 0.165}};
-    constexpr int64_t UNITS = 256;
     Tile best = Tile::k256;
     double least = 1e30;
     for (const Option &o : options) {
         const int64_t tiles = ((M + o.bm - 1) / o.bm) * ((N + o.bn - 1) / o.bn);
-        const double us = o.around_us + (double)((tiles + UNITS - 1) / UNITS * KT) * (tiles > UNITS ? o.step_us_full : o.step_us);
+        const double us = o.around_us + (double)((tiles + units - 1) / units * KT) * (tiles > units && units == 256 ? o.step_us_full : o.step_us);
         if (us < least) {
             least = us;
             best = o.tile;
@@ -907,13 +906,23 @@ static Tile choose_tile(int64_t M, int64_t N, int64_t KT)
     return best;
 }
 
-// K in bytes of an operand row. The staged kernel fills a ring of four K steps before it starts.
+// K in bytes of an operand row. The bound on workgroups applies to problems made of full 256x256 tiles (128x128 ones where there
+// are fewer than 128 of the large) whose rows of C are aligned, and the tile is chosen for the units it leaves; everything
+// else ignores it. [2048 x 2048 x 4096] on 64 workgroups (row-major scales): resident 128x128 tiles 102.5 us, staged 128x128
+// tiles 60.5 us, resident 256x256 tiles 45.7 us; [512 x 6144 x 4096] on 32: 150.5, 87, 256x192 tiles 72 us. The staged kernel fills a ring of four K steps before it starts.
 template <int FMT, bool A5, bool B5>
 static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s, int M, int N, int K,
                                  void *c, bool c_bf16, bool tiled, int64_t ldc, int max_workgroups, hipStream_t stream)
 {
     const bool many = (int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 128;
-    const Tile tile = K >= 4 * BK ? choose_tile(M, N, K / BK) : Tile::k256;
+    const int full = many ? 256 : 128;
+    const int64_t ldc_bytes = ldc * (c_bf16 ? 2 : 4);
+    const bool whole = M % full == 0 && N % full == 0 && K >= 2 * BK && reinterpret_cast<uintptr_t>(c) % 16 == 0 &&
+                       ldc_bytes % 16 == 0 && ldc_bytes * full < (int64_t(1) << 31);
+    if (!whole)
+        max_workgroups = 0;
+    const int units = max_workgroups > 0 && max_workgroups < 256 ? max_workgroups : 256;
+    const Tile tile = K >= 4 * BK ? choose_tile(M, N, K / BK, units) : Tile::k256;
 #define MXFP8_STAGED(BM, BN) \
     return launch_staged_cfg<StagedCfg<BM, BN, 2, 2, 4, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream)
     switch (tile) {
@@ -930,8 +939,8 @@ static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const u
     case Tile::k256: break;
     }
 #undef MXFP8_STAGED
-    // fewer than four K steps, or enough 256x256 tiles
-    if (many)
+    // enough 256x256 tiles (on few workgroups: chosen above), or fewer than four K steps
+    if (many || (units < 256 && K >= 4 * BK && M >= 256 && N >= 256))
         return launch_any<GemmCfg<256, 256, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream);
     return launch_any<GemmCfg<128, 128, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream);
 }

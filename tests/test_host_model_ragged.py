@@ -9,26 +9,36 @@ import test_host_model_fp4 as fp4
 import test_host_model_simulated as sim
 from test_host_model import MODES, hostmodel, run_case  # noqa: F401  (hostmodel is a fixture)
 
-# M, N, K steps, BF16 output, tiled scales, workgroup bound, simulated workgroups, mode
+# M, N, K steps, BF16 output, tiled scales, compute units (ragged problems ignore the bound on workgroups), simulated workgroups, mode
 CASES = [(2100, 4088, 3, True, True, 0, 3, 1), (2049, 4104, 2, True, False, 48, 2, 2), (2248, 3700, 3, False, True, 100, 2, 3)]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda s: "x".join(str(int(v)) for v in s))
 def test_ragged_resident_gemm(hostmodel, tmp_path, case):
-    M, N, steps, bf16, tiled, wg, blocks, mode = case
+    M, N, steps, bf16, tiled, units, blocks, mode = case
     ops = fp8._operands(M, N, steps * 128, seed=M + N)
-    line, out = fp8._gemm_case(tmp_path, M, N, steps * 128, ops, bf16, tiled=tiled, wg=wg)
-    _, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_BLOCKS=blocks, **MODES[mode])
+    line, out = fp8._gemm_case(tmp_path, M, N, steps * 128, ops, bf16, tiled=tiled, wg=2)
+    _, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_BLOCKS=blocks, WAVESIM_CUS=units or 256, **MODES[mode])
     assert calls[0][0] == 0 and len(calls[0][1]) == blocks
     fp8._check_gemm(out, M, N, N, ops, bf16, expect_full=False)
 
 
+def test_bounded_product_takes_256_tiles(hostmodel, tmp_path):
+    """Whole 128x128 tiles on few workgroups: 256x256 tiles although there are few of them, the last ones moved back."""
+    M, N, steps = 896, 512, 4
+    ops = fp8._operands(M, N, steps * 128, seed=M + N)
+    line, out = fp8._gemm_case(tmp_path, M, N, steps * 128, ops, True, tiled=True, wg=1)
+    _, calls = run_case(hostmodel, tmp_path, [line], **MODES[2])
+    assert calls[0] == (0, [0])
+    fp8._check_gemm(out, M, N, N, ops, True)
+
+
 def test_256x192_tiles(hostmodel, tmp_path):
     """[2048 x 6144]: 256 tiles of 256x192 where 256x256 tiles would leave a quarter of the units idle; and ragged."""
-    for i, (M, N, steps, bf16, tiled) in enumerate(((2048, 6144, 5, True, True), (2040, 6136, 4, False, False))):
+    for i, (M, N, steps, bf16, tiled) in enumerate(((2048, 6144, 9, True, True), (2040, 6136, 4, False, False))):
         ops = fp8._operands(M, N, steps * 128, seed=7 + i)
         line, out = fp8._gemm_case(tmp_path, M, N, steps * 128, ops, bf16, tiled=tiled, wg=128, tag=str(i))
-        _, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_BLOCKS=2, **MODES[3 * i])
+        _, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_BLOCKS=2, WAVESIM_CUS=128 if i else 256, **MODES[3 * i])
         assert calls[0] == (0, [0, 127])
         n = fp8._check_gemm(out, M, N, N, ops, bf16, expect_full=False)
         assert 3 * 256 * 192 < n <= 4 * 256 * 192

@@ -11,8 +11,9 @@ import test_host_model_simulated as sim
 from test_host_model import MODES, hostmodel, run_case  # noqa: F401  (hostmodel is a fixture)
 
 # M, N, K steps, BF16 output, leading dimension - N, tiled scales, workgroup bound
-SHAPES = [(1, 16, 4, False, 0, False, 0), (65, 129, 5, True, 7, True, 0), (200, 136, 8, True, 0, False, 2),
-          (130, 72, 9, False, 4, False, 0), (192, 80, 12, True, 8, True, 3), (33, 255, 7, False, 1, True, 0)]
+SHAPES = [(1, 16, 4, False, 0, False, 0), (65, 129, 5, True, 7, True, 0), (200, 136, 8, True, 0, False, 0),
+          (130, 72, 9, False, 4, False, 0), (192, 80, 12, True, 8, True, 0), (33, 255, 7, False, 1, True, 0),
+          (384, 256, 8, True, 0, False, 2), (384, 384, 5, False, 4, True, 4)]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(str(int(v)) for v in s))
