@@ -361,11 +361,13 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_kernel(
 // whatever the stores do; the immediates of the K step stay valid (they can only wait longer).
 // FUSE_Q (BF16 output only; bit 0 = row-wise copy, bit 1 = column-wise copy): the epilogue also emits MXFP8 copies of the
 // BF16 output tile (Section 2: the output is re-quantized when the next layer needs it in MX format), scales in the same
-// layout as the inputs: cq [M x N], cs = scales of C as an [M x N] operand; cqT [N x M], csT = scales of C^T. As soon as
-// the tile is stored, the workgroup reads it back (from the L2 it was just written to) in 128x128 pieces and converts
-// those like the quantizer does. A conversion straight from the accumulators needs the amax and the transposed bytes of
-// values that lie spread over 16 lanes: it spilled 316 bytes per work-item and took 42 us per 256x256 tile
-// ([4096 x 14336 x 4096], both copies: 337 us, 259 us this way).
+// layout as the inputs: cq [M x N], cs = scales of C as an [M x N] operand; cqT [N x M], csT = scales of C^T.
+//   row-wise alone: straight from the accumulators; a 32-column block lies in two adjacent MFMA tiles of one row, 8 values
+//     in each of the 4 lanes that share the row. ([8192 x 14336 x 4096]: 389 us, 417 us by way of the tile read back.)
+//   with a column-wise copy: as soon as the tile is stored, the workgroup reads it back (from the L2 it was just written
+//     to) in 128x128 pieces and converts those like the quantizer does. Straight from the accumulators this needs the amax
+//     and the transposed bytes of values that lie spread over 16 lanes: it spilled 316 bytes per work-item and took 42 us
+//     per 256x256 tile ([4096 x 14336 x 4096], both copies: 337 us, 259 us this way).
 #ifndef MXFP8_GEMM_SCHED
 #define MXFP8_GEMM_SCHED 242  // B requests behind every 2nd MFMA, a gap of 2, A requests behind every 4th
 #endif
@@ -387,6 +389,8 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
 {
     static_assert(!GROUPED || (FUSE_Q == 0 && Cfg::ALL_E4M3), "grouped products: MXFP8-E4M3 operands, plain epilogue");
     static_assert(!FUSE_Q || (OUT_BF16 && Cfg::BM % kTile == 0 && Cfg::BN % kTile == 0 && Cfg::THREADS == kQuantThreads), "fused output quantization");
+    constexpr bool Q_ROW_ONLY = FUSE_Q == 1;
+    static_assert(!Q_ROW_ONLY || Cfg::TN == 8 || Cfg::TN == 4, "the scale bytes of a row are a dword or a halfword");
     static_assert(!FUSE_Q || Cfg::WAVES * kStageBytes >= kTile * kTile + 2 * kTile * 4, "the converted tile fits the staging areas");
     static_assert(!Cfg::SCALED || (Cfg::SA_LOADS == Cfg::SDW && Cfg::SB_LOADS == Cfg::SDW), "one scale request per wavefront, operand and scale dword");
     static_assert(Cfg::ALL_E4M3 || FUSE_Q == 0, "output quantization belongs to the MXFP8-E4M3 product");
@@ -689,47 +693,127 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
 #pragma unroll
             for (int j = 0; j < TN; ++j)
                 MXFP8_KEEP_IN_ACC(acc[i][j]);
-            // Row group i of this wavefront (16 rows x WN columns) goes through a wavefront-private LDS area
-            // so that it leaves as whole rows: a lane holds 4 consecutive columns of one row per MFMA tile,
-            // and storing those directly costs one partial cache line per row and instruction (the address
-            // unit of the compute unit then needs ~7 us per 256 x 256 tile, during which the matrix pipes
-            // wait behind their own stores). Staged, every store instruction writes 1 KB of contiguous rows.
-            constexpr int ROWB = Cfg::WN * ESZ;                            // bytes of one row of the wavefront's part
-            constexpr int PITCH = ROWB + 32;                               // staged row pitch: spreads the rows over the banks
-            constexpr int RPP = ROWB * 16 <= 4096 ? 16 : ROWB * 8 <= 4096 ? 8 : 4;  // rows per pass (at most 4 KB staged)
-            static_assert(RPP * PITCH <= kStageBytes && (RPP * ROWB) % 1024 == 0, "staging area");
-            uint8_t *stage = lds + Cfg::LDS_BYTES + wave * kStageBytes;
+            if constexpr (Q_ROW_ONLY) {
+                // BF16 rows and their MXFP8 copy both leave through the wavefront's staging area (see the plain
+                // epilogue below for why): first the 16 BF16 rows, then, in the same area, the 16 byte rows.
+                const int64_t m = cur_tile.m0 + wm * Cfg::WM + i * 16 + r16;        // this lane's row of C
+                const int n_wave = cur_tile.n0 + wn * Cfg::WN;                       // first column of the wavefront
+                constexpr int ROWB = Cfg::WN * 2, PITCH = ROWB + 32;                 // BF16 row and its staged pitch
+                constexpr int QPITCH = Cfg::WN + 16;                                 // staged pitch of a byte row
+                static_assert(16 * PITCH <= kStageBytes && (16 * ROWB) % 1024 == 0 && (16 * Cfg::WN) % 1024 == 0, "staging area");
+                uint8_t *stage = lds + Cfg::LDS_BYTES + wave * kStageBytes;
+                uint32_t scales = 0;                                                 // scale bytes of the row's blocks
+                uint32_t q[TN];
 #pragma unroll
-            for (int pass = 0; pass < 16 / RPP; ++pass) {
-                if (RPP == 16 || r16 / RPP == pass) {
+                for (int blk = 0; blk < TN / 2; ++blk) {
+                    uint32_t h[4];  // BF16 pairs: columns 4g..4g+3 of tile 2*blk, then of tile 2*blk+1
 #pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        const v4f v = acc[i][j];
-                        uint8_t *dst = stage + (r16 % RPP) * PITCH + (j * 16 + 4 * g) * ESZ;
-                        if constexpr (OUT_BF16) {
-                            v2bf p0 = {(__bf16)v[0], (__bf16)v[1]}, p1 = {(__bf16)v[2], (__bf16)v[3]};
-                            *reinterpret_cast<uint2 *>(dst) =
-                                make_uint2(__builtin_bit_cast(uint32_t, p0), __builtin_bit_cast(uint32_t, p1));
-                        } else {
-                            *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
-                        }
+                    for (int t = 0; t < 2; ++t) {
+                        const v4f v = acc[i][2 * blk + t];
+                        v2bf p0 = {(__bf16)v[0], (__bf16)v[1]}, p1 = {(__bf16)v[2], (__bf16)v[3]};
+                        h[2 * t] = __builtin_bit_cast(uint32_t, p0);
+                        h[2 * t + 1] = __builtin_bit_cast(uint32_t, p1);
+                        *reinterpret_cast<uint2 *>(stage + r16 * PITCH + ((2 * blk + t) * 16 + 4 * g) * 2) = make_uint2(h[2 * t], h[2 * t + 1]);
                     }
+                    // block amax on the magnitude bits: 8 values here, then the 3 other lanes of the row
+                    uint32_t am = pk_max_u16(pk_max_u16(h[0] & 0x7FFF7FFFu, h[1] & 0x7FFF7FFFu),
+                                             pk_max_u16(h[2] & 0x7FFF7FFFu, h[3] & 0x7FFF7FFFu));
+                    am = umax(am & 0xFFFFu, am >> 16);
+                    am = umax(am, (uint32_t)__shfl_xor((int)am, 16, 64));
+                    am = umax(am, (uint32_t)__shfl_xor((int)am, 32, 64));
+                    const uint32_t sb = scale_byte_from_bf16_bits(am);
+                    const float sc = scale_operand(sb);
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        uint32_t qt = cvt2_bf16(cvt2_bf16(0, h[2 * t], sc, false), h[2 * t + 1], sc, true);
+                        if (sb >= 254) {  // NaN or Inf in the block: rare
+                            if (sb == 0xFF) {
+                                qt = 0x7F7F7F7Fu;
+                            } else {
+                                uint32_t f = 0;
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) {
+                                    const uint32_t bits = (e & 1) ? h[2 * t + e / 2] >> 16 : h[2 * t + e / 2] & 0xFFFFu;
+                                    f |= inf_byte_bf16(bits, (qt >> (8 * e)) & 0xFFu) << (8 * e);
+                                }
+                                qt = f;
+                            }
+                        }
+                        q[2 * blk + t] = qt;
+                    }
+                    scales |= sb << (8 * blk);
                 }
                 __builtin_amdgcn_wave_barrier();  // the reads below see the other lanes' writes (LDS serves a wavefront in order)
 #pragma unroll
-                for (int t = 0; t < RPP * ROWB / 1024; ++t) {
+                for (int t = 0; t < 16 * ROWB / 1024; ++t) {
                     const int lin = t * 1024 + lane * 16, row = lin / ROWB, colb = lin % ROWB;
                     const uint4 v = *reinterpret_cast<const uint4 *>(stage + row * PITCH + colb);
-                    const int m = wm * Cfg::WM + i * 16 + pass * RPP + row;  // inside the tile
-                    if (GROUPED ? m < cur_tile.rows : !RAGGED || (m >= cur_tile.row_lo && wn * ROWB + colb >= cur_tile.col_lo * ESZ))
-                        *reinterpret_cast<uint4 *>(crow + (int64_t)(wm * Cfg::WM + pass * RPP + row) * ldc_bytes +
-                                                   wn * ROWB + colb) = v;
+                    *reinterpret_cast<uint4 *>(crow + (int64_t)(wm * Cfg::WM + row) * ldc_bytes + wn * ROWB + colb) = v;
                 }
-                __builtin_amdgcn_wave_barrier();  // (the next pass overwrites the area after these reads)
+                __builtin_amdgcn_wave_barrier();  // the byte rows overwrite the area after these reads
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    *reinterpret_cast<uint32_t *>(stage + r16 * QPITCH + j * 16 + 4 * g) = q[j];
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int t = 0; t < 16 * Cfg::WN / 1024; ++t) {
+                    const int lin = t * 1024 + lane * 16, row = lin / Cfg::WN, colb = lin % Cfg::WN;
+                    const uint4 v = *reinterpret_cast<const uint4 *>(stage + row * QPITCH + colb);
+                    *reinterpret_cast<uint4 *>(cq + (cur_tile.m0 + wm * Cfg::WM + i * 16 + row) * (int64_t)N + n_wave + colb) = v;
+                }
+                __builtin_amdgcn_wave_barrier();  // (the next row group overwrites the area after these reads)
+                if (g == 0) {  // the TN/2 scale bytes of this row and wavefront: one dword or halfword
+                    const int64_t nb = N / kBlock, b0 = n_wave / kBlock;
+                    uint8_t *sp = TILED ? cs + (((m >> 6) * ((nb + 3) / 4) + (b0 >> 2)) * 64 + (m & 63)) * 4 + (b0 & 3)
+                                        : cs + m * nb + b0;
+                    if constexpr (TN / 2 == 4)
+                        *reinterpret_cast<uint32_t *>(sp) = scales;
+                    else
+                        *reinterpret_cast<uint16_t *>(sp) = (uint16_t)scales;
+                }
+            } else {
+                // Row group i of this wavefront (16 rows x WN columns) goes through a wavefront-private LDS area
+                // so that it leaves as whole rows: a lane holds 4 consecutive columns of one row per MFMA tile,
+                // and storing those directly costs one partial cache line per row and instruction (the address
+                // unit of the compute unit then needs ~7 us per 256 x 256 tile, during which the matrix pipes
+                // wait behind their own stores). Staged, every store instruction writes 1 KB of contiguous rows.
+                constexpr int ROWB = Cfg::WN * ESZ;                            // bytes of one row of the wavefront's part
+                constexpr int PITCH = ROWB + 32;                               // staged row pitch: spreads the rows over the banks
+                constexpr int RPP = ROWB * 16 <= 4096 ? 16 : ROWB * 8 <= 4096 ? 8 : 4;  // rows per pass (at most 4 KB staged)
+                static_assert(RPP * PITCH <= kStageBytes && (RPP * ROWB) % 1024 == 0, "staging area");
+                uint8_t *stage = lds + Cfg::LDS_BYTES + wave * kStageBytes;
+#pragma unroll
+                for (int pass = 0; pass < 16 / RPP; ++pass) {
+                    if (RPP == 16 || r16 / RPP == pass) {
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) {
+                            const v4f v = acc[i][j];
+                            uint8_t *dst = stage + (r16 % RPP) * PITCH + (j * 16 + 4 * g) * ESZ;
+                            if constexpr (OUT_BF16) {
+                                v2bf p0 = {(__bf16)v[0], (__bf16)v[1]}, p1 = {(__bf16)v[2], (__bf16)v[3]};
+                                *reinterpret_cast<uint2 *>(dst) =
+                                    make_uint2(__builtin_bit_cast(uint32_t, p0), __builtin_bit_cast(uint32_t, p1));
+                            } else {
+                                *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+                            }
+                        }
+                    }
+                    __builtin_amdgcn_wave_barrier();  // the reads below see the other lanes' writes (LDS serves a wavefront in order)
+#pragma unroll
+                    for (int t = 0; t < RPP * ROWB / 1024; ++t) {
+                        const int lin = t * 1024 + lane * 16, row = lin / ROWB, colb = lin % ROWB;
+                        const uint4 v = *reinterpret_cast<const uint4 *>(stage + row * PITCH + colb);
+                        const int m = wm * Cfg::WM + i * 16 + pass * RPP + row;  // inside the tile
+                        if (GROUPED ? m < cur_tile.rows : !RAGGED || (m >= cur_tile.row_lo && wn * ROWB + colb >= cur_tile.col_lo * ESZ))
+                            *reinterpret_cast<uint4 *>(crow + (int64_t)(wm * Cfg::WM + pass * RPP + row) * ldc_bytes +
+                                                       wn * ROWB + colb) = v;
+                    }
+                    __builtin_amdgcn_wave_barrier();  // (the next pass overwrites the area after these reads)
+                }
             }
             MXFP8_PIN();
         }
-        if constexpr (FUSE_Q) {
+        if constexpr (FUSE_Q && !Q_ROW_ONLY) {
             uint8_t *stage = lds + Cfg::LDS_BYTES;
             const QuantLds qlds{stage, stage + kTile * kTile, stage + kTile * kTile + kTile * 4, nullptr, nullptr};
             for (int part = 0; part < (Cfg::BM / kTile) * (Cfg::BN / kTile); ++part) {
