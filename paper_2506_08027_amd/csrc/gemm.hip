@@ -869,6 +869,17 @@ template <class Cfg> constexpr int sched_for()
     return 2 * Cfg::NB + 2 + 2 * (Cfg::NA - 1) < (Cfg::TN - 1) * Cfg::TM ? 222 : 0;
 }
 
+// Whether a problem runs on the persistent kernel with bm x bn tiles (K in bytes of an operand row): problems made of full
+// tiles, and those of at least one 256-row tile whose rows of C end on 16 bytes. Everything else takes one workgroup per
+// tile. (Ragged, BF16 out, tiled scales: [16000 x 6144 x 512] 108 us with one workgroup per tile, 67 us resident.)
+static bool goes_resident(int bm, int bn, int M, int N, int K, const void *c, int64_t ldc_bytes, int esize)
+{
+    const bool full = M % bm == 0 && N % bn == 0;
+    const bool ragged = bm == 256 && M >= bm && N >= bn && (int64_t)N * esize % 16 == 0;
+    return (full || ragged) && K >= 2 * BK && reinterpret_cast<uintptr_t>(c) % 16 == 0 && ldc_bytes % 16 == 0 &&
+           ldc_bytes * bm < (int64_t(1) << 31);
+}
+
 template <class Cfg, bool OUT_BF16, bool TILED>
 static hipError_t launch_cfg(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s,
                              int M, int N, int K, void *c, int64_t ldc, int max_workgroups, hipStream_t stream)
@@ -877,12 +888,8 @@ static hipError_t launch_cfg(const uint8_t *a_q, const uint8_t *a_s, const uint8
     const int64_t ldc_bytes = ldc * (OUT_BF16 ? 2 : 4);
     // 128-bit (FP32) / 64-bit (BF16) stores need every row start aligned; otherwise element stores
     const bool vec_store = (reinterpret_cast<uintptr_t>(c) % 16 == 0) && (ldc_bytes % 16 == 0);
-    // Problems made of full tiles, and those of at least one 256-row tile whose rows of C end on 16 bytes, run on the persistent
-    // kernel; everything else takes one workgroup per tile. (Ragged, BF16 out, tiled scales: [16000 x 6144 x 512] 108 us with
-    // one workgroup per tile, 67 us here.)
-    const bool full = M % Cfg::BM == 0 && N % Cfg::BN == 0;
-    const bool ragged = Cfg::BM == 256 && M >= Cfg::BM && N >= Cfg::BN && (int64_t)N * (OUT_BF16 ? 2 : 4) % 16 == 0;
-    if ((full || ragged) && K >= 2 * BK && vec_store && ldc_bytes * Cfg::BM < (int64_t(1) << 31)) {
+    if (goes_resident(Cfg::BM, Cfg::BN, M, N, K, c, ldc_bytes, OUT_BF16 ? 2 : 4)) {
+        const bool full = M % Cfg::BM == 0 && N % Cfg::BN == 0;
         int grid = 0;
         hipError_t e = persistent_grid(tiles_m * tiles_n, max_workgroups, grid);
         if (e != hipSuccess)
@@ -970,7 +977,7 @@ static hipError_t launch_staged_cfg(const uint8_t *a_q, const uint8_t *a_s, cons
 // A 128x128 step takes longer where all 256 units have several tiles (all of them fetch all the time). The 256x256 tiles of the
 // kernels above take 1.5 us per step, but share each fetched byte among twice as many matrix instructions.
 enum class Tile { k256, k256x192, k128, k128x64, k64x128, k64, k32x64, k32 };
-static Tile choose_tile(int64_t M, int64_t N, int64_t KT, int64_t units)
+template <class F> static Tile choose_tile(int64_t M, int64_t N, int64_t KT, int64_t units, F possible)
 {
     struct Option { Tile tile; int bm, bn; double around_us, step_us, step_us_full; };
     static const Option options[] = {{Tile::k256, 256, 256, 5.0, 1.45, 1.45}, {Tile::k256x192, 256, 192, 5.0, 1.2, 1.2}, {Tile::k128, 128, 128, 4.0, 0.43, 0.55},
@@ -980,6 +987,8 @@ static Tile choose_tile(int64_t M, int64_t N, int64_t KT, int64_t units)
     Tile best = Tile::k256;
     double least = 1e30;
     for (const Option &o : options) {
+        if (!possible(o.bm, o.bn))
+            continue;
         const int64_t tiles = ((M + o.bm - 1) / o.bm) * ((N + o.bn - 1) / o.bn);
         const double us = o.around_us + (double)((tiles + units - 1) / units * KT) * (tiles > units && units == 256 ? o.step_us_full : o.step_us);
         if (us < least) {
@@ -1000,13 +1009,15 @@ static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const u
 {
     const bool many = (int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 128;
     const int full = many ? 256 : 128;
-    const int64_t ldc_bytes = ldc * (c_bf16 ? 2 : 4);
-    const bool whole = M % full == 0 && N % full == 0 && K >= 2 * BK && reinterpret_cast<uintptr_t>(c) % 16 == 0 &&
-                       ldc_bytes % 16 == 0 && ldc_bytes * full < (int64_t(1) << 31);
+    const int esize = c_bf16 ? 2 : 4;
+    const int64_t ldc_bytes = ldc * esize;
+    const bool whole = M % full == 0 && N % full == 0 && goes_resident(full, full, M, N, K, c, ldc_bytes, esize);
     if (!whole)
         max_workgroups = 0;
     const int units = max_workgroups > 0 && max_workgroups < 256 ? max_workgroups : 256;
-    const Tile tile = K >= 4 * BK ? choose_tile(M, N, K / BK, units) : Tile::k256;
+    // 256-row tiles keep a bound only on the resident kernel (rows of C 8 MiB and more apart do not fit its offsets)
+    auto possible = [&](int bm, int bn) { return max_workgroups == 0 || bm != 256 || goes_resident(bm, bn, M, N, K, c, ldc_bytes, esize); };
+    const Tile tile = K >= 4 * BK ? choose_tile(M, N, K / BK, units, possible) : Tile::k256;
 #define MXFP8_STAGED(BM, BN) \
     return launch_staged_cfg<StagedCfg<BM, BN, 2, 2, 4, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream)
     switch (tile) {

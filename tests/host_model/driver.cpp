@@ -6,6 +6,8 @@
 //   quantize   <f32|bf16> <rows> <cols> <ld> <axis 1|2|3> <src.bin> <out-prefix> [tiled]
 //   gemm       <pass 0|1|2> <M> <N> <K> <f32|bf16> <ldc> <a_q> <a_s> <b_q> <b_s> <c.bin> [tiled]
 //   dequantize <rows> <cols> <f32|bf16> <ld> <q.bin> <s.bin> <out.bin> [tiled]
+//   route      <fp8|fp4|bf16> <M> <N> <K> <f32|bf16> <ldc> <bytes that c is off 16> [tiled]
+//              (the launch alone, for WAVESIM_BLOCKS=0: no operand is read; prints "route <status> <workgroups> <LDS bytes>")
 //   gemmbf16   <M> <N> <K> <f32|bf16> <ldc> <a.bin> <b.bin> <c.bin>      (BF16 operands, no scales)
 //   gemmgrp    <M> <N> <K> <f32|bf16> <ldc> <groups> <a_q> <a_s> <b_q> <b_s> <ends.bin (int32)> <c.bin> [tiled]
 //              (b_q = groups x N x K bytes, b_s = groups scale operands; rows outside every group keep 0xA5)
@@ -392,6 +394,22 @@ int main(int argc, char **argv)
             unchanged(sb, "s");
             report(st);
             save(out, o);
+        } else if (op == "route") {
+            std::string fmt, dt;
+            int64_t M, N, K, ldc;
+            size_t off;
+            ls >> fmt >> M >> N >> K >> dt >> ldc >> off;
+            const mxfp8_scale_layout lay = layout_of(ls);
+            if (const char *e = getenv("WAVESIM_BLOCKS"); !e || strcmp(e, "0") != 0) {
+                fprintf(stderr, "route needs WAVESIM_BLOCKS=0\n");
+                return 2;
+            }
+            static uint8_t operand[64] __attribute__((aligned(64)));  // addresses only
+            uint8_t *a = operand, *c = operand + off;
+            const int st = fmt == "bf16" ? mxfp8_gemm_bf16(a, a, M, N, K, c, dtype_of(dt), ldc, g_max_workgroups, nullptr)
+                           : fmt == "fp4" ? mxfp8_fp4_gemm_ex(MXFP8_FPROP, a, a, a, a, M, N, K, c, dtype_of(dt), ldc, lay, g_max_workgroups, nullptr)
+                                          : mxfp8_gemm_ex(MXFP8_FPROP, a, a, a, a, M, N, K, c, dtype_of(dt), ldc, lay, g_max_workgroups, nullptr);
+            printf("route %d %u %zu\n", st, wavesim::g.grid.x, wavesim::g.launch_lds);
         } else if (op == "expandfp6") {
             long rows, cols;
             int element;

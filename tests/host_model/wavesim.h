@@ -111,6 +111,7 @@ struct Machine {
     const std::function<void()> *body = nullptr;
     std::vector<Buffer> buffers;
     std::vector<unsigned> simulated;  // block ids of the last launch that were run
+    size_t launch_lds = 0;            // dynamic LDS bytes of the last launch
     uint64_t launches = 0;
 #ifdef WAVESIM_ASAN
     const void *main_bottom = nullptr;
@@ -768,6 +769,7 @@ inline void launch(dim3 grid, dim3 block, size_t shmem, const std::function<void
     g.grid = grid;
     g.block = block;
     g.body = &body;
+    g.launch_lds = shmem;
     g.simulated.clear();
     ++g.launches;
     // all workgroups, or max_blocks of them spread evenly over the grid (first and last included)
