@@ -834,17 +834,24 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
     MXFP8_WAIT_VMCNT(0);  // the redundant prefetches of the last steps must land before LDS is released
 }
 
-// Number of workgroups of a persistent launch: one per compute unit of the current device, at most
-// `max_workgroups` when the caller gives a positive bound, never more than there are tiles.
-static hipError_t persistent_grid(int ntiles, int max_workgroups, int &grid)
+// Compute units of the current device.
+static hipError_t compute_units(int &units)
 {
     int dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess)
         e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    units = cus > 0 ? cus : 1;
+    return e;
+}
+
+// Number of workgroups of a persistent launch: one per compute unit of the current device, at most
+// `max_workgroups` when the caller gives a positive bound, never more than there are tiles.
+static hipError_t persistent_grid(int ntiles, int max_workgroups, int &grid)
+{
+    const hipError_t e = compute_units(grid);
     if (e != hipSuccess)
         return e;
-    grid = cus > 0 ? cus : 1;
     if (max_workgroups > 0 && max_workgroups < grid)
         grid = max_workgroups;
     if (ntiles < grid)
@@ -974,10 +981,12 @@ static hipError_t launch_staged_cfg(const uint8_t *a_q, const uint8_t *a_s, cons
 //   [384 x 896 x 512]          5.7      4.5      3.7     3.3     3.4
 //   [304 x 704 x 640]          5.8      4.6      3.7     3.3     3.1
 //   [16 x 1024 x 2048]         9.0      7.1      5.5     5.2     4.5
-// A 128x128 step takes longer where all 256 units have several tiles (all of them fetch all the time). The 256x256 tiles of the
-// kernels above take 1.5 us per step, but share each fetched byte among twice as many matrix instructions.
+// A 128x128 step takes longer where all units of the device have several tiles (all of them fetch all the time); under a
+// bound, also one of 200 or 250 of 256 units, the shorter time was the better estimate. The 256x256 tiles of the kernels
+// above take 1.5 us per step, but share each fetched byte among twice as many matrix instructions.
+// units: compute units that the launch may use; all_units: it may use all of them.
 enum class Tile { k256, k256x192, k128, k128x64, k64x128, k64, k32x64, k32 };
-template <class F> static Tile choose_tile(int64_t M, int64_t N, int64_t KT, int64_t units, F possible)
+template <class F> static Tile choose_tile(int64_t M, int64_t N, int64_t KT, int64_t units, bool all_units, F possible)
 {
     struct Option { Tile tile; int bm, bn; double around_us, step_us, step_us_full; };
     static const Option options[] = {{Tile::k256, 256, 256, 5.0, 1.45, 1.45}, {Tile::k256x192, 256, 192, 5.0, 1.2, 1.2}, {Tile::k128, 128, 128, 4.0, 0.43, 0.55},
@@ -990,7 +999,7 @@ template <class F> static Tile choose_tile(int64_t M, int64_t N, int64_t KT, int
         if (!possible(o.bm, o.bn))
             continue;
         const int64_t tiles = ((M + o.bm - 1) / o.bm) * ((N + o.bn - 1) / o.bn);
-        const double us = o.around_us + (double)((tiles + units - 1) / units * KT) * (tiles > units && units == 256 ? o.step_us_full : o.step_us);
+        const double us = o.around_us + (double)((tiles + units - 1) / units * KT) * (tiles > units && all_units ? o.step_us_full : o.step_us);
         if (us < least) {
             least = us;
             best = o.tile;
@@ -1014,10 +1023,15 @@ static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const u
     const bool whole = M % full == 0 && N % full == 0 && goes_resident(full, full, M, N, K, c, ldc_bytes, esize);
     if (!whole)
         max_workgroups = 0;
-    const int units = max_workgroups > 0 && max_workgroups < 256 ? max_workgroups : 256;
+    int device_units = 0;
+    const hipError_t e = compute_units(device_units);
+    if (e != hipSuccess)
+        return e;
+    const bool all_units = max_workgroups == 0 || max_workgroups >= device_units;
+    const int units = all_units ? device_units : max_workgroups;
     // 256-row tiles keep a bound only on the resident kernel (rows of C 8 MiB and more apart do not fit its offsets)
     auto possible = [&](int bm, int bn) { return max_workgroups == 0 || bm != 256 || goes_resident(bm, bn, M, N, K, c, ldc_bytes, esize); };
-    const Tile tile = K >= 4 * BK ? choose_tile(M, N, K / BK, units, possible) : Tile::k256;
+    const Tile tile = K >= 4 * BK ? choose_tile(M, N, K / BK, units, all_units, possible) : Tile::k256;
 #define MXFP8_STAGED(BM, BN) \
     return launch_staged_cfg<StagedCfg<BM, BN, 2, 2, 4, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream)
     switch (tile) {
@@ -1034,8 +1048,8 @@ static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const u
     case Tile::k256: break;
     }
 #undef MXFP8_STAGED
-    // enough 256x256 tiles (on few workgroups: chosen above), or fewer than four K steps
-    if (many || (units < 256 && K >= 4 * BK && M >= 256 && N >= 256))
+    // enough 256x256 tiles (or on few units: chosen above), or fewer than four K steps
+    if (many || (K >= 4 * BK && M >= 256 && N >= 256))
         return launch_any<GemmCfg<256, 256, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream);
     return launch_any<GemmCfg<128, 128, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream);
 }

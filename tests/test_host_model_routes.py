@@ -34,3 +34,17 @@ def test_bound_holds_where_rows_of_c_are_far_apart(hostmodel, tmp_path, bf16):
              for ldc in (512, 8 * mib - 8, 8 * mib, 10 * mib, 16 * mib - 8)]
     for call, (workgroups, _) in zip(calls, routes(hostmodel, tmp_path, calls)):
         assert workgroups == call[-1], call
+
+
+def test_tile_is_chosen_for_the_units_of_the_device(hostmodel, tmp_path):
+    """A device of n units runs a product on the kernel and tile of a 256-unit device that is held to n workgroups (shapes at
+    which the contention of a fully used chip, counted in the first case only, does not change the choice)."""
+    shapes = [("fp8", 2048, 2048, 32, True), ("fp8", 1024, 4096, 32, True), ("fp8", 512, 6144, 32, True), ("bf16", 1024, 1024, 16, False),
+              ("fp4", 512, 1024, 12, True), ("fp8", 256, 1024, 8, False)]
+    for units in (32, 64):
+        own = routes(hostmodel, tmp_path, [s + (0, 0, True, 0) for s in shapes], WAVESIM_CUS=units)
+        held = routes(hostmodel, tmp_path, [s + (0, 0, True, units) for s in shapes])
+        full = routes(hostmodel, tmp_path, [s + (0, 0, True, 0) for s in shapes])
+        lds = lambda r: [v[1] for v in r]  # noqa: E731
+        assert lds(own) == lds(held)
+        assert lds(own) != lds(full)
