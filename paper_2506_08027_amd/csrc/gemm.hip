@@ -983,26 +983,42 @@ static hipError_t launch_staged_cfg(const uint8_t *a_q, const uint8_t *a_s, cons
 //   [16 x 1024 x 2048]         9.0      7.1      5.5     5.2     4.5
 // A 128x128 step takes longer where all units of the device have several tiles (all of them fetch all the time); under a
 // bound, also one of 200 or 250 of 256 units, the shorter time was the better estimate. The 256x256 tiles of the kernels
-// above take 1.5 us per step, but share each fetched byte among twice as many matrix instructions.
-// units: compute units that the launch may use; all_units: it may use all of them.
+// above take 1.5 us per step, but share each fetched byte among twice as many matrix instructions. Where they cannot go
+// resident, their prologue and epilogue are paid in every round and a step is slower ([137 x 74069 x 4864], BF16 out, tiled:
+// 153.8 us as one-tile 256x256 workgroups, 138.4 as staged 64x128 tiles; [6144 x 6922 x 3456]: 211.6 us, 235.0 as staged
+// 128x128 tiles).
+// units: compute units that the launch may use; all_units: it may use all of them; route(bm, bn): how 256-row tiles would run.
 enum class Tile { k256, k256x192, k128, k128x64, k64x128, k64, k32x64, k32 };
-template <class F> static Tile choose_tile(int64_t M, int64_t N, int64_t KT, int64_t units, bool all_units, F possible)
+enum class Route { resident, one_tile, none };
+struct TileOption {
+    Tile tile;
+    int bm, bn;
+    double around_us, round_us, step_us, step_us_full;
+    int64_t tiles(int64_t M, int64_t N) const { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
+    int64_t rounds(int64_t M, int64_t N, int64_t units) const { return (tiles(M, N) + units - 1) / units; }
+};
+template <class F> static TileOption choose_tile(int64_t M, int64_t N, int64_t KT, int64_t units, bool all_units, F route)
 {
-    struct Option { Tile tile; int bm, bn; double around_us, step_us, step_us_full; };
-    static const Option options[] = {{Tile::k256, 256, 256, 5.0, 1.45, 1.45}, {Tile::k256x192, 256, 192, 5.0, 1.2, 1.2}, {Tile::k128, 128, 128, 4.0, 0.43, 0.55},
-                                     {Tile::k128x64, 128, 64, 3.5, 0.32, 0.36}, {Tile::k64x128, 64, 128, 3.5, 0.32, 0.36},
-                                     {Tile::k64, 64, 64, 2.6, 0.215, 0.215}, {Tile::k32x64, 32, 64, 2.4, 0.19, 0.19},
-                                     {Tile::k32, 32, 32, 2.2, 0.165, 0.165}};
-    Tile best = Tile::k256;
+    static const TileOption options[] = {{Tile::k256, 256, 256, 5.0, 0, 1.45, 1.45}, {Tile::k256x192, 256, 192, 5.0, 0, 1.2, 1.2},
+                                         {Tile::k128, 128, 128, 4.0, 0, 0.43, 0.55}, {Tile::k128x64, 128, 64, 3.5, 0, 0.32, 0.36},
+                                         {Tile::k64x128, 64, 128, 3.5, 0, 0.32, 0.36}, {Tile::k64, 64, 64, 2.6, 0, 0.215, 0.215},
+                                         {Tile::k32x64, 32, 64, 2.4, 0, 0.19, 0.19}, {Tile::k32, 32, 32, 2.2, 0, 0.165, 0.165}};
+    static const TileOption one_tile[] = {{Tile::k256, 256, 256, 3.0, 1.5, 1.5, 1.5}, {Tile::k256x192, 256, 192, 2.0, 2.5, 1.22, 1.22}};
+    TileOption best = options[0];
     double least = 1e30;
-    for (const Option &o : options) {
-        if (!possible(o.bm, o.bn))
-            continue;
-        const int64_t tiles = ((M + o.bm - 1) / o.bm) * ((N + o.bn - 1) / o.bn);
-        const double us = o.around_us + (double)((tiles + units - 1) / units * KT) * (tiles > units && all_units ? o.step_us_full : o.step_us);
+    for (TileOption o : options) {
+        if (o.bm == 256) {
+            const Route r = route(o.bm, o.bn);
+            if (r == Route::none)
+                continue;
+            if (r == Route::one_tile)
+                o = one_tile[o.tile == Tile::k256 ? 0 : 1];
+        }
+        const double step = o.tiles(M, N) > units && all_units ? o.step_us_full : o.step_us;
+        const double us = o.around_us + (double)o.rounds(M, N, units) * (o.round_us + (double)KT * step);
         if (us < least) {
             least = us;
-            best = o.tile;
+            best = o;
         }
     }
     return best;
@@ -1030,8 +1046,37 @@ static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const u
     const bool all_units = max_workgroups == 0 || max_workgroups >= device_units;
     const int units = all_units ? device_units : max_workgroups;
     // 256-row tiles keep a bound only on the resident kernel (rows of C 8 MiB and more apart do not fit its offsets)
-    auto possible = [&](int bm, int bn) { return max_workgroups == 0 || bm != 256 || goes_resident(bm, bn, M, N, K, c, ldc_bytes, esize); };
-    const Tile tile = K >= 4 * BK ? choose_tile(M, N, K / BK, units, all_units, possible) : Tile::k256;
+    auto route = [&](int bm, int bn) {
+        return goes_resident(bm, bn, M, N, K, c, ldc_bytes, esize) ? Route::resident : max_workgroups == 0 ? Route::one_tile : Route::none;
+    };
+    const int KT = K / BK;
+    Tile tile = Tile::k256;
+    bool two_buffers = K < 4 * BK && !many;  // 128x128 tiles on the resident or the one-tile kernel instead of the staged one
+    if (K >= 4 * BK) {
+        const TileOption o = choose_tile(M, N, KT, units, all_units, route);
+        tile = o.tile;
+        const int64_t tiles128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
+        const bool staged = tile != Tile::k256 && tile != Tile::k256x192;
+        if (staged && goes_resident(128, 128, M, N, K, c, ldc_bytes, esize)) {
+            // Few K steps and several tiles per workgroup: the resident kernel fetches the next tile under the epilogue of
+            // the last, the staged one starts anew. [896 x 2688 x 512] on 40 workgroups (row-major scales): staged 18.0 us,
+            // resident 15.7; from 11 steps on the staged kernel wins ([2304 x 2176 x 1408] on 40: 49.8 against 57.8), with
+            // row-major MXFP4 scales always ([1024 x 4352 x 1280]: 11.0, 13.4), and where half the units would get no tile
+            // ([384 x 1408 x 1024] MXFP4 on 100: 5.8, 6.6).
+            two_buffers = KT <= (tile == Tile::k128 ? 10 : 6) && o.rounds(M, N, units) >= 2 && (FMT != kFmtFp4 || tiled) &&
+                          2 * tiles128 >= units;
+        } else if (staged && max_workgroups == 0 && tile != Tile::k32x64 && tile != Tile::k32) {
+            // Two of the one-tile kernel's 128x128 workgroups fit a unit, so what takes the staged kernel two rounds runs side
+            // by side. Not with row-major scales (a cache line per row and request), FP32 output (its direct stores) or few
+            // rows, and not before the second place of a quarter of the units is filled. BF16 out, tiled: [2064 x 3528 x 5376]
+            // MXFP4 33.5 us staged, 28.8 here; [2254 x 2584 x 1280] MXFP8 17.1, 15.4; but [651 x 5566 x 16640] MXFP4 (264
+            // tiles) 67.3 and 71.3, and [564 x 6688 x 1024] MXFP4, FP32 out, 9.1 and 12.8.
+            two_buffers = (FMT == kFmtBf16 || tiled) && c_bf16 && M > 64 && N > 64 && 4 * tiles128 > 5 * units && tiles128 <= 2 * units &&
+                           (tile == Tile::k128 || KT >= 8);
+        }
+    }
+    if (two_buffers)
+        return launch_any<GemmCfg<128, 128, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream);
 #define MXFP8_STAGED(BM, BN) \
     return launch_staged_cfg<StagedCfg<BM, BN, 2, 2, 4, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream)
     switch (tile) {
@@ -1042,16 +1087,11 @@ static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const u
     case Tile::k32x64: MXFP8_STAGED(32, 64);
     case Tile::k32: MXFP8_STAGED(32, 32);
     case Tile::k256x192:
-        if (M >= 256 && N >= 192)
-            return launch_any<GemmCfg<256, 192, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream);
-        break;
+        return launch_any<GemmCfg<256, 192, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream);
     case Tile::k256: break;
     }
 #undef MXFP8_STAGED
-    // enough 256x256 tiles (or on few units: chosen above), or fewer than four K steps
-    if (many || (K >= 4 * BK && M >= 256 && N >= 256))
-        return launch_any<GemmCfg<256, 256, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream);
-    return launch_any<GemmCfg<128, 128, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream);
+    return launch_any<GemmCfg<256, 256, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream);
 }
 
 hipError_t launch_gemm(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s, int64_t M,
