@@ -1078,7 +1078,7 @@ static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const u
     if (two_buffers)
         return launch_any<GemmCfg<128, 128, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream);
 #define MXFP8_STAGED(BM, BN) \
-    return launch_staged_cfg<StagedCfg<BM, BN, 2, 2, 4, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream)
+    return launch_staged_cfg<StagedCfg<BM, BN, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream)
     switch (tile) {
     case Tile::k128: MXFP8_STAGED(128, 128);
     case Tile::k128x64: MXFP8_STAGED(128, 64);

@@ -6,11 +6,11 @@
 
 namespace mxfp8 {
 
-// Tile BM x BN per workgroup of WAVES_M x WAVES_N wavefronts, a ring of STAGES K steps in LDS. One stage holds the
-// A rows, the B rows (128 bytes each) and, with tiled scales, one scale dword (two for MXFP4) per row.
-template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, int STAGES_, int FMT_ = kFmtFp8, bool A_E5M2_ = false, bool B_E5M2_ = false>
+// Tile BM x BN per workgroup of 2 x 2 wavefronts, a ring of four K steps in LDS. One stage holds the A rows, the B rows
+// (128 bytes each) and, with tiled scales, one scale dword (two for MXFP4) per row.
+template <int BM_, int BN_, int FMT_ = kFmtFp8, bool A_E5M2_ = false, bool B_E5M2_ = false>
 struct StagedCfg {
-    static constexpr int BM = BM_, BN = BN_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, STAGES = STAGES_, FMT = FMT_;
+    static constexpr int BM = BM_, BN = BN_, WAVES_M = 2, WAVES_N = 2, STAGES = 4, FMT = FMT_;
     static constexpr bool A_E5M2 = A_E5M2_, B_E5M2 = B_E5M2_;
     static constexpr bool SCALED = FMT_ != kFmtBf16;
     static constexpr int SDW = FMT_ == kFmtFp4 ? 2 : 1;     // scale dwords per operand row and K step
@@ -25,7 +25,7 @@ struct StagedCfg {
     static constexpr int SREQ = (SGROUPS + WAVES - 1) / WAVES;  // scale requests per wavefront and stage (some are made twice)
     static constexpr int STAGE_SCALE_BYTES = SGROUPS * 256;
     // row-major scales: 16 bytes per row = the dwords of SPG steps, QUADS buffers of them
-    static constexpr int SPG = 4 / SDW, QUADS = STAGES > 4 ? 8 : 4, QUAD_BYTES = SCALED ? (AG + BG) * 1024 : 0;
+    static constexpr int SPG = 4 / SDW, QUADS = 4, QUAD_BYTES = SCALED ? (AG + BG) * 1024 : 0;
     static constexpr int L = LOADS + SREQ;  // requests per wavefront and stage
     static constexpr int EPI_BYTES = WAVES * kStageBytes;
     static constexpr int lds_bytes(bool tiled)
@@ -36,7 +36,7 @@ struct StagedCfg {
     static_assert(BM % 16 == 0 && BN % 16 == 0 && WM % 16 == 0 && WN % 16 == 0, "whole matrix instructions");
     static_assert((BM + BN) % (8 * WAVES) == 0 && BM % 8 == 0, "8-row requests spread evenly over the wavefronts");
     static_assert((BM % 64 == 0 || 64 % BM == 0) && (BN % 64 == 0 || 64 % BN == 0), "a tile's scale rows start inside one 64-row group");
-    static_assert(STAGES >= 3 && STAGES <= 8 && (STAGES - 1) * L < 64, "wait counts");
+    static_assert((STAGES - 1) * L < 64, "wait counts");
     static_assert(SPG * QUADS > STAGES + 2 * SPG - 3, "a quad buffer is refilled only after its last step was read");
 };
 
