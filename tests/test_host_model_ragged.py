@@ -23,6 +23,44 @@ def test_ragged_resident_gemm(hostmodel, tmp_path, case):
     fp8._check_gemm(out, M, N, N, ops, bf16, expect_full=False)
 
 
+def _tiles_of(workgroup, units, tiles_m, tiles_n):
+    """(row, column) of the tiles that a resident workgroup walks over: XCD-contiguous ids, panels of 8 tile columns."""
+    n, out = tiles_m * tiles_n, []
+    for bid in range(workgroup, n, units):
+        lid = (bid % 8) * (n // 8) + bid // 8 if bid < n // 8 * 8 else bid
+        panel, rest = divmod(lid, 8 * tiles_m)
+        width = min(8, tiles_n - panel * 8)
+        out.append((rest // width, panel * 8 + rest % width))
+    return out
+
+
+# operand format, M, N, K steps, BF16 output: three by three 256x256 tiles, the last row and column of them moved back to a place
+# inside a 64-row group of the tiled scales
+HAND_OVERS = [("fp8", 760, 744, 5, True), ("fp8", 712, 744, 4, False), ("fp4", 760, 744, 4, True)]
+
+
+@pytest.mark.parametrize("case", HAND_OVERS, ids=lambda s: "x".join(str(v) for v in s))
+def test_ragged_resident_hand_over_between_tiles(hostmodel, tmp_path, case):
+    """Two workgroups go from tiles in place to tiles moved back in M, in N and in both, and back: with tiled scales a lane's
+    scale offset then differs from one tile to the next, for A and B separately, while both tiles' steps are in flight."""
+    fmt, M, N, steps, bf16 = case
+    moved = lambda t: (t[0] == 2, t[1] == 2)  # noqa: E731
+    pairs = [(moved(a), moved(b)) for w in (0, 1) for a, b in zip(_tiles_of(w, 2, 3, 3)[:-1], _tiles_of(w, 2, 3, 3)[1:])]
+    for axis in (0, 1):
+        assert {(a[axis], b[axis]) for a, b in pairs} >= {(False, True), (False, False)}
+    assert ((False, True), (False, False)) in pairs and (M - 256) % 64 and (N - 256) % 64
+    mode = MODES[HAND_OVERS.index(case)]
+    if fmt == "fp8":
+        ops = fp8._operands(M, N, steps * 128, seed=M + N)
+        line, out = fp8._gemm_case(tmp_path, M, N, steps * 128, ops, bf16, tiled=True)
+    else:
+        ops = fp4._fp4_operands(M, N, steps * 256, seed=M + N)
+        line, out = fp4._fp4_gemm_case(tmp_path, M, N, steps * 256, ops, bf16, N, tiled=True)
+    _, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_CUS=2, **mode)
+    assert calls[0] == (0, [0, 1])   # two resident workgroups: everything is computed, the moved tiles among it
+    (fp8._check_gemm if fmt == "fp8" else fp4._check_fp4_gemm)(out, M, N, N, ops, bf16)
+
+
 def test_bounded_product_takes_256_tiles(hostmodel, tmp_path):
     """Whole 128x128 tiles on few workgroups: 256x256 tiles although there are few of them, the last ones moved back."""
     M, N, steps = 896, 512, 4
