@@ -170,12 +170,13 @@ def _one_tile_per_workgroup(args, dtype, lay):
     return pad[:, :N].contiguous()
 
 
-@pytest.mark.parametrize("shape,workgroups", [((256, 384, 384), 2), ((384, 256, 256), 0), ((2048, 4096, 512), 64),
-                                              ((2048, 4096, 512), 0), ((4352, 4096, 256), 0)])
+@pytest.mark.parametrize("shape,workgroups", [((256, 384, 384), 2), ((384, 256, 256), 0), ((2048, 4096, 384), 64),
+                                              ((2048, 4096, 384), 0), ((4352, 4096, 256), 0)])
 @pytest.mark.parametrize("tiled", [False, True])
 def test_persistent_gemm_matches_oracle_and_one_tile_kernel(shape, workgroups, tiled):
-    """Full-tile shapes run on the persistent kernel; 2 and 64 workgroups walk over 3 and 2 tiles each, the
-    last shape has 272 tiles of 256 x 256 for 256 compute units (16 workgroups take a second tile)."""
+    """Full-tile shapes of fewer than four K steps run on the persistent kernel, with unaligned rows of C on the
+    one-tile kernel (from four steps on, both may go to the staged one); 2 and 64 workgroups walk over 3 and 2
+    tiles each, the last shape has 272 tiles of 256 x 256 for 256 compute units (16 workgroups take a second tile)."""
     M, N, K = shape
     ops = _operands(M, N, K, seed=100 + M + K)
     a_q, a_s, b_q, b_s = ops

@@ -72,8 +72,8 @@ def test_bf16_product_one_hot_rows_select_columns():
                                          ((130, 129, 64), torch.bfloat16), ((384, 256, 4096), torch.float32),
                                          ((2048, 4096, 512), torch.bfloat16), ((2048 + 72, 4096 - 100, 192), torch.float32)])
 def test_bf16_product_matches_oracle(shape, dtype):
-    """Round-tripped activations x weights: one-tile kernels (ragged), persistent kernels (full tiles), both
-    tile configurations, long K."""
+    """Round-tripped activations x weights: one-tile kernel (ragged), persistent kernel (full tiles, large ragged ones),
+    both tile configurations, the staged kernel from four 64-value steps on, long K."""
     M, N, K = shape
     a, b = oracle.roundtrip_bf16(si.activations(M, K, seed=2)), oracle.roundtrip_bf16(si.weights(N, K, seed=4))
     rows = np.arange(M) if M * N * K <= 2 ** 27 else np.unique(np.concatenate([[0, M - 1], np.random.default_rng(1).integers(0, M, 14)]))

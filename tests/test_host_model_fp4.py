@@ -195,14 +195,14 @@ def test_fp4_gemm_persistent_large_tiles_sampled_workgroups(hostmodel, tmp_path,
 
 
 def test_fp4_gemm_large_tiles_ragged_sampled_workgroups(hostmodel, tmp_path):
-    """256 x 256 configuration, one workgroup per tile, ragged last tiles in both directions."""
-    M, N, K = 2040, 4100, 512
+    """256 x 256 configuration, one workgroup per tile (the rows of C end off 16 bytes), ragged last tiles in both directions."""
+    M, N, K = 2040, 4098, 512
     ops = _fp4_operands(M, N, K, seed=41)
     for tiled in (False, True):
-        line, out = _fp4_gemm_case(tmp_path, M, N, K, ops, tiled=tiled, tag=str(int(tiled)))
+        line, out = _fp4_gemm_case(tmp_path, M, N, K, ops, ldc=N + 2, tiled=tiled, tag=str(int(tiled)))
         _, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_BLOCKS=2)
-        assert calls[0][0] == 0
-        assert _check_fp4_gemm(out, M, N, N, ops, False, expect_full=False) > 256 * 256
+        assert calls[0] == (0, [0, 8 * 17 - 1])
+        assert _check_fp4_gemm(out, M, N, N + 2, ops, False, expect_full=False) > 256 * 256
 
 
 def test_fp4_gemm_k_zero_and_validation(hostmodel, tmp_path):
