@@ -951,10 +951,13 @@ static hipError_t launch_staged_t(const uint8_t *a_q, const uint8_t *a_s, const 
     const int ntiles = tiles_m * tiles_n;
     const int grid = max_workgroups > 0 && max_workgroups < ntiles ? max_workgroups : ntiles;
     auto kern = gemm_staged_kernel<Cfg, OUT_BF16, TILED>;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::lds_bytes(TILED));
-    if (e != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Cfg::THREADS), Cfg::lds_bytes(TILED), stream, a_q, a_s, b_q, b_s, M, N, K,
+    constexpr int lds = Cfg::lds_bytes(TILED);
+    if (lds > 64 * 1024) {  // what a launch may ask for by itself
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess)
+            return e;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Cfg::THREADS), lds, stream, a_q, a_s, b_q, b_s, M, N, K,
                        static_cast<uint8_t *>(c), ldc_bytes, tiles_m, tiles_n, vec_store);
     return hipGetLastError();
 }
