@@ -8,19 +8,23 @@ import test_host_model as fp8
 import test_host_model_fp4 as fp4
 import test_host_model_gemm_modes as modes
 import test_host_model_simulated as sim
+from route_cases import launch
 from test_host_model import MODES, hostmodel, run_case  # noqa: F401  (hostmodel is a fixture)
+from test_host_model_routes import routes
 
 # M, N, K steps, BF16 output, leading dimension - N, tiled scales, workgroup bound
 SHAPES = [(1, 16, 4, False, 0, False, 0), (65, 129, 5, True, 7, True, 0), (200, 136, 8, True, 0, False, 0),
           (130, 72, 9, False, 4, False, 0), (192, 80, 12, True, 8, True, 0), (33, 255, 7, False, 1, True, 0),
-          (384, 256, 8, True, 0, False, 2), (384, 384, 5, False, 4, True, 4)]
+          (384, 256, 12, True, 0, False, 2), (384, 384, 11, False, 4, True, 3)]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(str(int(v)) for v in s))
 def test_staged_gemm_edges(hostmodel, tmp_path, shape):
     M, N, steps, bf16, pad, tiled, wg = shape
     ops = fp8._operands(M, N, steps * 128, seed=M + N)
-    lines, outs = [], []
+    if wg:   # several 128x128 tiles per workgroup (with fewer K steps they would go to the resident kernel)
+        call = ("fp8", M, N, steps, bf16, pad, tiled, wg)
+        assert routes(hostmodel, tmp_path, [call[:5] + (N + pad, 0, tiled, wg)])[0] == launch(call, "staged", 128, 128)
     line, out = fp8._gemm_case(tmp_path, M, N, steps * 128, ops, bf16, N + pad, tiled=tiled, wg=wg)
     for mode in (MODES[0], MODES[3]):
         _, calls = run_case(hostmodel, tmp_path, [line], **mode)
