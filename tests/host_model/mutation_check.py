@@ -1,10 +1,11 @@
 """Sensitivity check of the CPU execution model (test infrastructure; `python tests/host_model/mutation_check.py`,
 or tests/test_mutation_checks.py with --runslow). Plants one mistake at a time into a scratch
-copy of the GEMM kernel source -- a removed barrier, a wait count that is one too loose, a missing wait,
-a swizzle mismatch, a prefetch into the wrong buffer or of the wrong K step, a missing ragged-tile clamp,
-a wrong output row -- builds the host model from it and runs a few products against the oracle in all
-four scheduling modes (lazy / eager DMA completion, either wavefront running ahead). Every mutant must
-be caught, by a wrong or NaN result or by the model's range check. A second group plants mistakes into the
+copy of the product kernels' sources -- a removed barrier, a wait count that is one too loose, a missing wait,
+a swizzle mismatch, a prefetch into the wrong buffer or of the wrong K step, a missing ragged-tile clamp, a scale
+of another row or step, a wrong output row -- builds the host model from it and runs a few products on that kernel
+(one-tile, resident, resident on ragged problems, staged) against the oracle in all four scheduling modes (lazy /
+eager DMA completion, either wavefront running ahead). Every mutant must be caught, by a wrong, NaN or missing
+result or by the model's range check. A second group plants mistakes into the
 converters (scale-rule constants, the staging swizzle of the transposed copy, a removed barrier, the infinity patch,
 the narrow formats' scale rules) and compares the quantized bytes with the oracle's. Arguments, if any, select the
 mutants whose description contains one of them."""
@@ -13,13 +14,16 @@ import shutil
 import subprocess
 import sys
 import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 import numpy as np
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(os.path.dirname(HERE))
 sys.path.insert(0, ROOT)
+sys.path.insert(0, os.path.dirname(HERE))
 import oracle  # noqa: E402
+import scale_layout as sl  # noqa: E402
 
 MID = ("                MXFP8_WAIT_VMCNT(Cfg::NA + Cfg::NB);  // all but this step's requests: A(kt+1) is in LDS\n"
        "                __syncthreads();")
@@ -64,6 +68,33 @@ PERSISTENT_MUTANTS = [
     ("persistent: buffer parity not carried across tiles", "            step(par, b_src, bs_src, a_src, as_src, a_lim);\n            par ^= 1;",
      "            step(kt & 1, b_src, bs_src, a_src, as_src, a_lim);\n            par ^= 1;"),
 ]
+# ragged problems on the resident kernel (three by three tiles on two workgroups, the last row and column moved back)
+RAGGED_MUTANTS = [
+    ("ragged: A scales of the next tile read at the current tile's offset", "as_off = kt + 2 < KT ? cur_tile.as_off : next_tile.as_off;",
+     "as_off = cur_tile.as_off;"),
+    ("ragged: B scales of the next tile read at the current tile's offset", "bs_off = kt + 1 < KT ? cur_tile.bs_off : next_tile.bs_off;",
+     "bs_off = cur_tile.bs_off;"),
+    ("ragged: last row of tiles not moved back", "t.m0 = RAGGED ? min(tm * Cfg::BM, M - Cfg::BM) : tm * Cfg::BM;", "t.m0 = tm * Cfg::BM;"),
+    ("ragged: tiled scales of a moved tile as if it began a 64-row group", "            if constexpr (RAGGED) {\n                const int row = first + lane;",
+     "            if constexpr (false) {\n                const int row = first + lane;"),
+    ("ragged: first own row of a moved tile not stored", "(m >= cur_tile.row_lo &&", "(m > cur_tile.row_lo - (cur_tile.row_lo == 0) &&"),
+]
+STEP_BARRIER = ("                MXFP8_BARRIER();\n                MXFP8_FENCE();\n            }\n            MXFP8_PIN();")
+STAGED_MUTANTS = [  # gemm_staged.h
+    ("staged: prologue wait one request too loose", "MXFP8_WAIT_VMCNT_AND_LDS((S - 1) * L);", "MXFP8_WAIT_VMCNT_AND_LDS((S - 1) * L + 1);"),
+    ("staged: wait of a step one request too loose", "MXFP8_WAIT_VMCNT_AND_LDS((S - 2) * L);", "MXFP8_WAIT_VMCNT_AND_LDS((S - 2) * L + 1);"),
+    ("staged: waits of the last steps one step too loose", "wait_tail<S - 2, L>(left - 1);", "wait_tail<S - 2, L>(left);"),
+    ("staged: barrier of a step removed", STEP_BARRIER, STEP_BARRIER.replace("                MXFP8_BARRIER();\n", "")),
+    ("staged: request into the next ring slot", "issue(t, kt + S, slot);", "issue(t, kt + S, next);"),
+    ("staged: request of the wrong K step", "issue(t, kt + S, slot);", "issue(t, kt + S - 1, slot);"),
+    ("staged: fragments read from the slot of the step that runs", "read_piece(p, kt + 1, next, set ^ 1);", "read_piece(p, kt + 1, slot, set ^ 1);"),
+    ("staged: odd first step computed twice", "            step(0, 1, S);\n            kt = 1;", "            step(0, 1, S);"),
+    ("staged: quarters of row-major scales out of order", "ahead % SPG * SDW);", "(ahead + 1) % SPG * SDW);"),
+    ("staged: row-major scales of another step of the group", "(kt % SPG) * (4 * SDW)", "((kt + 1) % SPG) * (4 * SDW)"),
+    ("staged: scales of a tile that begins inside a 64-row group", "const int sa_row = (TILED ? m0 & 63 : 0) + a_row,", "const int sa_row = a_row,"),
+    ("staged: ragged tile reads past the last row", "goff[i] = (uint32_t)min(row, (is_a ? M - m0 : N - n0) - 1) * (uint32_t)K", "goff[i] = (uint32_t)row * (uint32_t)K"),
+    ("staged: no barrier before the next tile's requests", "            __syncthreads();  // the next tile's requests go where the rows were staged", "            ;"),
+]
 MODES = [{}, {"WAVESIM_ORDER": "down"}, {"WAVESIM_DMA": "eager"}, {"WAVESIM_DMA": "eager", "WAVESIM_ORDER": "down"}]
 
 
@@ -77,40 +108,53 @@ def build(work, text, name="gemm.hip"):
         text = open(src).read().replace('"../../include/mxfp8.h"', f'"{inc}"').replace('"wavesim.h"', f'"{HERE}/wavesim.h"')
         open(os.path.join(path, name), "w").write(text)
     binary = os.path.join(work, "hostmodel")
-    cmd = ["/opt/rocm/llvm/bin/clang++", "-std=c++17", "-x", "c++", "-I", os.path.join(HERE, "shim"), "-O2",
+    cmd = ["/opt/rocm/llvm/bin/clang++", "-std=c++17", "-x", "c++", "-I", os.path.join(HERE, "shim"), "-O0",
            "-Wno-unknown-pragmas", "-Wno-psabi", "-o", binary, os.path.join(work, "driver.cpp")]
     cmd += [os.path.join(csrc, f) for f in sorted(os.listdir(csrc)) if f.endswith(".hip")]
     subprocess.run(cmd, check=True, capture_output=True)
     return binary
 
 
-def caught(binary, work, persistent=0):
-    for M, N, K in ([(256, 384, 384), (2048, 4096, 384)] if persistent else [(256, 256, 512), (200, 136, 384), (2048, 4096, 512)]):
+# kernel -> [(M, N, K steps, tiled scales, bound on workgroups, units, simulated workgroups or 0 = all)]
+CASES = {
+    "one-tile": [(200, 136, 3, False, 0, 256, 0), (130, 129, 2, True, 0, 256, 0), (2047, 4095, 3, False, 0, 256, 2)],
+    # 6 small tiles on 2 workgroups, 128 large tiles on 64: K = 3 steps (odd: parity flips per tile)
+    "resident": [(256, 384, 3, False, 2, 256, 0), (2048, 4096, 3, False, 64, 256, 2)],
+    "ragged": [(760, 744, 5, True, 0, 2, 0)],
+    # 32x32 tiles in both scale layouts, several 128x128 tiles per workgroup
+    "staged": [(70, 72, 9, False, 0, 256, 0), (70, 72, 6, True, 0, 256, 0), (384, 256, 12, False, 2, 256, 0), (384, 384, 11, True, 3, 256, 0)],
+}
+
+
+def caught(binary, work, kernel):
+    for M, N, steps, tiled, bound, units, blocks in CASES[kernel]:
+        K = steps * 128
         rng = np.random.default_rng(M + N)
-        a = rng.standard_normal((M, K)).astype(np.float32)
-        b = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+        a = rng.standard_normal((M, K)).astype(np.float32) * np.exp2(rng.integers(-6, 7, (M, 1))).astype(np.float32)
+        b = (rng.standard_normal((N, K)) * 0.02).astype(np.float32) * np.exp2(rng.integers(-6, 7, (N, 1))).astype(np.float32)
         ops = oracle.quantize_rowwise(a) + oracle.quantize_rowwise(b)
         names = []
         for n, v in zip(("aq", "as", "bq", "bs"), ops):
             names.append(os.path.join(work, n + ".bin"))
-            v.tofile(names[-1])
+            (sl.tile(v, filler=0xFF) if tiled and n.endswith("s") else v).tofile(names[-1])
         out = os.path.join(work, "c.bin")
         case = os.path.join(work, "case.txt")
-        # persistent: 6 small tiles on 2 workgroups, 128 large tiles on 64: K = 3 steps (odd: parity flips per tile)
-        wg = f" wg={2 if M == 256 else 64}" if persistent else ""
-        open(case, "w").write(f"gemm 0 {M} {N} {K} f32 {N} {' '.join(names)} {out}{wg}\n")
+        open(case, "w").write(f"gemm 0 {M} {N} {K} f32 {N} {' '.join(names)} {out}" + (" tiled" if tiled else "") +
+                              (f" wg={bound}" if bound else "") + "\n")
         for mode in MODES:
-            env = dict(os.environ, WAVESIM_BLOCKS="2", **mode)
+            env = dict(os.environ, WAVESIM_BLOCKS=str(blocks or "all"), WAVESIM_CUS=str(units), **mode)
             r = subprocess.run([binary, case], capture_output=True, text=True, env=env)
             if r.returncode != 0:
-                return f"model stopped: {r.stderr.strip().splitlines()[-1][:100]}"
+                return f"model stopped: {(r.stderr.strip().splitlines() or ['exit code ' + str(r.returncode)])[-1][:100]}"
             c = np.fromfile(out, np.uint32).reshape(M, N)
             written = c != 0xA5A5A5A5
+            if not blocks and not written.all():
+                return f"{(~written).sum()} results missing at {M}x{N}x{K} in mode {mode or 'default'}"
             rows = np.unique(np.nonzero(written)[0])
             ref, absum = oracle.gemm_rows(*ops, rows)
             val = c.view(np.float32)[rows]
             w = written[rows]
-            if np.isnan(val[w]).any() or (np.abs(val - ref)[w] > (2.0 ** -23 * absum + 1e-300)[w]).any():
+            if np.isnan(val[w]).any() or (np.abs(val - ref)[w] > (max(steps, 2) * 2.0 ** -24 * absum + 1e-300)[w]).any():
                 return f"wrong result at {M}x{N}x{K} in mode {mode or 'default'}"
     return None
 
@@ -166,49 +210,41 @@ def caught_quant(binary, work):
 
 
 def main():
-    source = open(os.path.join(ROOT, "paper_2506_08027_amd", "csrc", "gemm.hip")).read()
-    survivors = 0
-    todo = [("(unmutated source: must pass)", "", "", 0), ("(unmutated source, persistent kernel: must pass)", "", "", 1)]
-    todo += [m + (0,) for m in MUTANTS] + [m + (1,) for m in PERSISTENT_MUTANTS]
-    only = sys.argv[1:]
-    for desc, old, new, persistent in todo:   # every pattern must still be in the source: a stale one would test nothing
-        assert old == "" or old in source, desc
-    for desc, old, new, persistent in todo:
-        if only and not any(o in desc for o in only):
-            continue
-        assert old == "" or old in source, desc
-        work = tempfile.mkdtemp(prefix="kmut_")
-        try:
-            if old == "":
-                text = source
-            elif persistent:
-                at = source.rindex(old)
-                text = source[:at] + new + source[at + len(old):]
-            else:
-                text = source.replace(old, new, 1)
-            how = caught(build(work, text), work, persistent)
-        finally:
-            shutil.rmtree(work, ignore_errors=True)
-        ok = (how is None) if old == "" else (how is not None)
-        survivors += not ok
-        print(("ok      " if ok else "PROBLEM ") + desc + (f" -> {how}" if how else ""), flush=True)
     csrc = os.path.join(ROOT, "paper_2506_08027_amd", "csrc")
-    quant = [("(unmutated converters: must pass)", "gemm.hip", "", "")] + QUANT_MUTANTS
-    for desc, name, old, new in quant:
+    # (description, source file, old text, new text, kernel whose cases are run; None: the converters'), first occurrence
+    # of the text, in the resident kernel the last one (the one-tile kernel before it has the same)
+    todo = [(f"(unmutated source, {kernel}: must pass)", "gemm.hip", "", "", kernel) for kernel in CASES]
+    todo += [(desc, "gemm.hip", old, new, "one-tile") for desc, old, new in MUTANTS]
+    todo += [(desc, "gemm.hip", old, new, "resident") for desc, old, new in PERSISTENT_MUTANTS]
+    todo += [(desc, "gemm.hip", old, new, "ragged") for desc, old, new in RAGGED_MUTANTS]
+    todo += [(desc, "gemm_staged.h", old, new, "staged") for desc, old, new in STAGED_MUTANTS]
+    todo += [("(unmutated converters: must pass)", "gemm.hip", "", "", None)] + [m + (None,) for m in QUANT_MUTANTS]
+    for desc, name, old, new, kernel in todo:   # every pattern must still be in the source: a stale one would test nothing
         assert old == "" or old in open(os.path.join(csrc, name)).read(), desc
-    for desc, name, old, new in quant:
-        if only and not any(o in desc for o in only):
-            continue
+    only = sys.argv[1:]
+    todo = [m for m in todo if not only or any(o in m[0] for o in only)]
+
+    def run(mutant):
+        desc, name, old, new, kernel = mutant
         text = open(os.path.join(csrc, name)).read()
+        if old:
+            at = (text.rindex if kernel == "resident" else text.index)(old)
+            text = text[:at] + new + text[at + len(old):]
         work = tempfile.mkdtemp(prefix="kmut_")
         try:
-            how = caught_quant(build(work, text.replace(old, new, 1) if old else text, name), work)
+            binary = build(work, text, name)
+            how = caught_quant(binary, work) if kernel is None else caught(binary, work, kernel)
         finally:
             shutil.rmtree(work, ignore_errors=True)
         ok = (how is None) if old == "" else (how is not None)
-        survivors += not ok
         print(("ok      " if ok else "PROBLEM ") + desc + (f" -> {how}" if how else ""), flush=True)
-    sys.exit(1 if survivors else 0)
+        return ok
+
+    with ThreadPoolExecutor(max(1, min(6, (os.cpu_count() or 2) - 1))) as pool:
+        results = list(pool.map(run, todo))
+    planted = sum(m[2] != "" for m in todo)
+    print(f"{len(results) - results.count(False)} of {len(results)} as expected ({planted} planted mistakes)")
+    sys.exit(0 if all(results) else 1)
 
 
 if __name__ == "__main__":

@@ -1,8 +1,8 @@
 """Runs the two mutation checks as tests, so that "every planted mistake is caught" can be reproduced:
 oracle/mutation_check.py plants single plausible mistakes in the oracle's C source and expects the pins
 (tests/test_oracle_pins.py, tests/test_oracle_modes.py) to fail; tests/host_model/mutation_check.py does the
-same to the GEMM kernels on the CPU execution model. The full sets take tens of minutes and run only with
-`--runslow` (`python -m pytest tests/test_mutation_checks.py --runslow`); a three-mutant sample of the oracle
+same to the product kernels and the converters on the CPU execution model. The full sets (tens of minutes; three for
+the kernels on eight cores) run only with `--runslow` (`python -m pytest tests/test_mutation_checks.py --runslow`); a three-mutant sample of the oracle
 check runs every time."""
 import os
 import subprocess
@@ -36,4 +36,5 @@ def test_oracle_pins_catch_every_planted_mistake():
 
 @pytest.mark.slow
 def test_host_model_catches_every_planted_kernel_mistake():
-    _run("tests/host_model/mutation_check.py", timeout=3400)
+    out = _run("tests/host_model/mutation_check.py", timeout=3400)
+    assert "48 of 48 as expected (43 planted mistakes)" in out
