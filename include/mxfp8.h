@@ -164,7 +164,8 @@ mxfp8_status mxfp8_gemm(mxfp8_pass pass, const uint8_t *a_q, const uint8_t *a_s,
 /* mxfp8_gemm with a_s and b_s both stored in `scale_layout` (Section 2, Appendix A.3: same sum), on at
  * most `max_workgroups` compute units. Problems made of full output tiles (M and N multiples of 256, or of
  * 128 when ceil(M/256)*ceil(N/256) < 128; K >= 256; c 16-byte aligned with ldc*sizeof(element) a multiple
- * of 16) can be held to a number of workgroups that walk over their share of the tiles;
+ * of 16 and less than 8 MiB, 16 MiB with the multiples of 128) can be held to a number of workgroups that walk
+ * over their share of the tiles;
  * max_workgroups > 0 caps the number of those workgroups, e.g. to leave compute units to a kernel that
  * runs beside the product, max_workgroups == 0 takes every compute unit of the current device, a negative
  * value returns MXFP8_ERR_MODE. Other shapes ignore the bound. The result

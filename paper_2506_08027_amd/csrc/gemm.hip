@@ -975,15 +975,20 @@ static hipError_t launch_staged_cfg(const uint8_t *a_q, const uint8_t *a_s, cons
 }
 
 // Which tile: an estimate of the time, what a launch costs around its K loop plus (rounds of tiles over the compute units)
-// x (K steps) x (time of a step), from measurements on an MI355X (MXFP8, row-major scales, us):
-//                           128x128   128x64   64x64   32x64   32x32
-//   [1000 x 2880 x 5760]      24.5     34.2     31.7    47.4    62.4
-//   [2048 x 3072 x 4096]      34.9     38.2     42.0    63.6    87.1
-//   [512 x 4096 x 4096]       17.3     14.1     16.4    24.0    31.5
-//   [48 x 6144 x 4096]        14.9     11.4      9.3     8.8     9.8
-//   [384 x 896 x 512]          5.7      4.5      3.7     3.3     3.4
-//   [304 x 704 x 640]          5.8      4.6      3.7     3.3     3.1
-//   [16 x 1024 x 2048]         9.0      7.1      5.5     5.2     4.5
+// x (K steps) x (time of a step), from measurements on an MI355X (MXFP8, row-major scales, BF16 out, us; 256-row tiles on the
+// resident kernel from 256 rows on, else one workgroup per tile):
+//                          256x256 256x192 128x128 128x64 64x128  64x64  32x64  32x32
+//   [2048 x 6144 x 4096]      50.2    48.8    54.8   74.3   75.9   81.5  124.0  171.2
+//   [2048 x 3072 x 4096]      46.0    40.5    35.3   38.6   39.5   43.5   67.9   90.1
+//   [1000 x 2880 x 5760]      61.1    57.3    25.2   35.3   36.1   32.7   48.7   64.5
+//   [512 x 4096 x 4096]       44.4    39.2    17.9   14.7   15.1   17.3   25.1   32.5
+//   [128 x 4096 x 4096]       43.6    36.9    14.9   11.4   13.9    9.0    8.9   10.0
+//   [48 x 6144 x 4096]        41.8    32.8    15.0   11.7   11.8    9.1    9.5    9.6
+//   [384 x 896 x 512]         12.2    10.4     6.2    4.9    4.9    4.2    3.8    3.9
+//   [304 x 704 x 640]         13.2    11.1     6.3    5.0    5.0    4.2    3.8    3.6
+//   [16 x 1024 x 2048]        23.1    18.6     9.4    7.5    7.6    5.9    5.6    4.9
+// Other operands keep the order of the tiles, or nearly: the same operand bytes take 0.9 of the time with tiled scales, 0.85 as
+// BF16, 1.2 as MXFP4 with tiled scales ([1000 x 2880], 45 steps, 128x128: 22.3, 21.3, 31.5; 64x64: 28.3, 26.7, 32.1).
 // A 128x128 step takes longer where all units of the device have several tiles (all of them fetch all the time); under a
 // bound, also one of 200 or 250 of 256 units, the shorter time was the better estimate. The 256x256 tiles of the kernels
 // above take 1.5 us per step, but share each fetched byte among twice as many matrix instructions. Where they cannot go

@@ -76,6 +76,8 @@ template <class F> __device__ __forceinline__ void fp6_block(const float (&v)[kB
     for (int j = 0; j < 6; ++j)
         w[j] = 0;
     if (amax < 0x7F800000u) {
+        // The converter is fed with values as they come from LDS. A variant that staged BF16 tiles as BF16 and fed it with the
+        // shifted halves gave wrong bytes on the hardware (right ones on the CPU model); the cause is not known.
         v16f even, odd;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
