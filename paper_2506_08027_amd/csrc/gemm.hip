@@ -1047,12 +1047,6 @@ static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const u
     const bool whole = M % full == 0 && N % full == 0 && goes_resident(full, full, M, N, K, c, ldc_bytes, esize);
     if (!whole)
         max_workgroups = 0;
-    int device_units = 0;
-    const hipError_t e = compute_units(device_units);
-    if (e != hipSuccess)
-        return e;
-    const bool all_units = max_workgroups == 0 || max_workgroups >= device_units;
-    const int units = all_units ? device_units : max_workgroups;
     // 256-row tiles keep a bound only on the resident kernel (rows of C 8 MiB and more apart do not fit its offsets)
     auto route = [&](int bm, int bn) {
         return goes_resident(bm, bn, M, N, K, c, ldc_bytes, esize) ? Route::resident : max_workgroups == 0 ? Route::one_tile : Route::none;
@@ -1061,6 +1055,12 @@ static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const u
     Tile tile = Tile::k256;
     bool two_buffers = K < 4 * BK && !many;  // 128x128 tiles on the resident or the one-tile kernel instead of the staged one
     if (K >= 4 * BK) {
+        int device_units = 0;
+        const hipError_t e = compute_units(device_units);
+        if (e != hipSuccess)
+            return e;
+        const bool all_units = max_workgroups == 0 || max_workgroups >= device_units;
+        const int units = all_units ? device_units : max_workgroups;
         const TileOption o = choose_tile(M, N, KT, units, all_units, route);
         tile = o.tile;
         const int64_t tiles128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
