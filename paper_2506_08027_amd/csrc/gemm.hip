@@ -34,6 +34,9 @@
 
 namespace mxfp8 {
 
+hipError_t launch_quantize(const void *src, bool bf16, int64_t rows, int64_t cols, int64_t ld, int axis, uint8_t *q_row, uint8_t *s_row,
+                           uint8_t *q_colT, uint8_t *s_colT, bool tiled_scales, int mode, hipStream_t stream);  // quantize.hip
+
 // A_E5M2 / B_E5M2 (kFmtFp8 only): the elements of that operand are E5M2 instead of E4M3 (Section 3.2.2 compares the
 // two per tensor type); nothing but the format fields of the matrix instruction changes.
 template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, int FMT_ = kFmtFp8, bool A_E5M2_ = false, bool B_E5M2_ = false> struct GemmCfg {
@@ -1233,17 +1236,14 @@ hipError_t launch_gemm_bf16(const uint8_t *a, const uint8_t *b, int64_t M, int64
 }
 
 // GEMM with BF16 output and MXFP8 copies of that output (axis bit 0: row-wise, bit 1: column-wise) from
-// the same epilogue. Runs on the persistent kernel, hence full tiles only: returns
-// hipErrorInvalidConfiguration (nothing launched) when M or N is not a multiple of the tile (256 when the
-// problem has at least 128 such tiles, else 128) or K has fewer than two steps.
+// the same call. Full tiles only: returns hipErrorInvalidConfiguration (nothing launched) when M or N is not a multiple of
+// the tile (256 when the problem has at least 128 such tiles, else 128) or K has fewer than two steps.
 template <class Cfg, bool TILED, int AXIS>
 static hipError_t launch_fused_cfg(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s,
                                    int M, int N, int K, void *c, int64_t ldc, uint8_t *cq, uint8_t *cs, uint8_t *cqT,
                                    uint8_t *csT, int max_workgroups, hipStream_t stream)
 {
     const int64_t ldc_bytes = ldc * 2;
-    if (M % Cfg::BM || N % Cfg::BN || K < 2 * BK || ldc_bytes * Cfg::BM >= (int64_t(1) << 31))
-        return hipErrorInvalidConfiguration;
     const int tiles_m = M / Cfg::BM, tiles_n = N / Cfg::BN;
     auto kern = gemm_persistent_kernel<Cfg, true, TILED, spread_fits<Cfg>(), AXIS>;
     int grid = 0;
@@ -1267,6 +1267,19 @@ template <class Cfg, bool TILED, class... Args> static hipError_t launch_fused_a
     }
 }
 
+// Which way (both measured on an MI355X, graph replays, tiled scales, us: in the epilogue | product, then quantizer):
+//   row copy    [8192 x 14336 x 4096] 399.6 | 402.4    [4096 x 14336 x 4096] 220.5 | 227.6   [4096 x 4096 x 4096] 61.0 | 62.5
+//               [2816 x 3072 x 2048]   34.8 |  30.2    [2816 x 3072 x 512]    22.3 |  20.0   [2048 x 2048 x 4096] 27.5 | 25.8
+//               [2048 x 2048 x 512]    10.7 |  13.3    [1024 x 1024 x 2048]   16.8 |  11.5   [256 x 512 x 4096]   20.4 | 12.4
+//   both copies [8192 x 14336 x 4096] 465.6 | 437.0    [4096 x 14336 x 4096] 262.8 | 240.0   [4096 x 4096 x 4096] 72.0 | 65.1
+//               [8192 x 8192 x 512]   119.7 |  91.1    [2816 x 3072 x 512]    30.7 |  22.4   [2048 x 2048 x 4096] 30.1 | 27.1
+//               [2048 x 2048 x 512]    13.4 |  14.9    [1024 x 1024 x 2048]   18.9 |  13.3   [512 x 1024 x 1024]  12.3 | 10.6
+// An epilogue that converts keeps the matrix pipes of its unit idle, and it ties the product to 256x256 (128x128) tiles; the
+// quantizer reads C from the caches at the rate of the memory. So of large problems the column copy is left to the quantizer,
+// and the row copy, which the epilogue makes straight from the accumulators, where the tiles do not fill the units. Small
+// problems stay in one kernel where their tiles fill most of the units and few K steps are multiplied. Under a bound on
+// workgroups neither way wins ([4096 x 14336 x 4096], both copies, on 64: 723.9 | 719.2; [2816 x 3072 x 512], row copy, on
+// 32: 80.1 | 92.7; [2048 x 2048 x 1024], both, on 192: 19.8 | 23.8): one kernel.
 hipError_t launch_gemm_fused(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s,
                              int64_t M, int64_t N, int64_t K, void *c, int64_t ldc, int axis, uint8_t *cq,
                              uint8_t *cs, uint8_t *cqT, uint8_t *csT, bool tiled_scales, int max_workgroups,
@@ -1274,8 +1287,22 @@ hipError_t launch_gemm_fused(const uint8_t *a_q, const uint8_t *a_s, const uint8
 {
     using Big = GemmCfg<256, 256, 2, 2>;
     using Small = GemmCfg<128, 128, 2, 2>;
-    const bool big = ((M + 255) / 256) * ((N + 255) / 256) >= 128;
-    const int m = (int)M, n = (int)N, k = (int)K;
+    const int64_t tiles256 = ((M + 255) / 256) * ((N + 255) / 256);
+    const bool big = tiles256 >= 128;
+    const int m = (int)M, n = (int)N, k = (int)K, bm = big ? 256 : 128;
+    if (M % bm || N % bm || K < 2 * BK || ldc * 2 * bm >= (int64_t(1) << 31))
+        return hipErrorInvalidConfiguration;
+    if (max_workgroups == 0) {
+        int units = 0;
+        hipError_t e = compute_units(units);
+        if (e != hipSuccess)
+            return e;
+        const bool filled = 4 * (M / 128) * (N / 128) >= 3 * (int64_t)units;
+        if (big ? axis != 1 || tiles256 < units : K > (filled ? 8 : axis == 1 ? 4 : 0) * BK) {
+            e = launch_gemm(a_q, a_s, b_q, b_s, M, N, K, c, true, tiled_scales, ldc, 0, stream);
+            return e != hipSuccess ? e : launch_quantize(c, true, M, N, ldc, axis, cq, cs, cqT, csT, tiled_scales, 0, stream);
+        }
+    }
     if (big)
         return tiled_scales ? launch_fused_axis<Big, true>(axis, a_q, a_s, b_q, b_s, m, n, k, c, ldc, cq, cs, cqT, csT, max_workgroups, stream)
                             : launch_fused_axis<Big, false>(axis, a_q, a_s, b_q, b_s, m, n, k, c, ldc, cq, cs, cqT, csT, max_workgroups, stream);
