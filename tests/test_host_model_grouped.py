@@ -174,3 +174,20 @@ def test_grouped_wgrad_bad_ends_are_clamped(hostmodel, tmp_path):
     _, calls = run_case(hostmodel, tmp_path, [line])
     assert calls[0][0] == 0
     _wgrad_check(out, M, N, N, ops, [256, 128, 9999], False)
+
+
+@pytest.mark.parametrize("M,N,bf16,tiled,mode", [(264, 272, True, False, MODES[0]), (256, 512, False, True, MODES[3])],
+                         ids=["ragged-rowmajor", "whole-tiled"])
+def test_grouped_wgrad_resident(hostmodel, tmp_path, M, N, bf16, tiled, mode):
+    """Resident 256x256 tiles: experts of 0 .. 3 K steps side by side, so that requests one and two steps ahead end in the
+    same tile, the next one and the one after it; ragged tiles moved back; workgroups with several tiles and with one."""
+    steps = [1, 1, 0, 2, 0, 3, 1, 1] + [0] * 56
+    ends = [int(e) * 128 for e in np.cumsum(steps)]
+    K = ends[-1]
+    a = oracle.quantize_rowwise(si.gradients(M, K, seed=8, spikes=True))
+    b = oracle.quantize_rowwise(np.asarray(si.activations(N, K, seed=9, bf16=False), np.float32))
+    ops = (a[0], a[1], b[0], b[1])
+    line, out = _wgrad_case(tmp_path, M, N, K, ops, ends, bf16, N + 16, tiled=tiled)
+    _, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_CUS=5, **mode)
+    assert calls[0] == (0, list(range(5)))
+    _wgrad_check(out, M, N, N + 16, ops, ends, bf16)
