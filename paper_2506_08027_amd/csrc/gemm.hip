@@ -28,6 +28,7 @@
 // dwords per row). With 4-bit elements the instruction takes dwords 0..3 only, lane (r, g) holds K =
 // 32g..32g+31 of row r and its own scale byte applies to them (pinned on the hardware by a test that runs
 // single instructions on registers taken from memory).
+#include <type_traits>
 #include "gemm_device.h"
 #include "gemm_staged.h"
 #include "quantize_tile.h"
@@ -66,14 +67,6 @@ template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, int FMT_ = kFmtFp8, bool
     static_assert(BM % 64 == 0 && BN % 64 == 0, "scale rows per instruction");
     static_assert(NB <= 2 * TM, "the B loads of the next step are issued with the MFMAs of the first column");
     static_assert(NA + NB < 64, "wait-count immediate");
-};
-
-// Expert groups of the grouped products (Appendix A.4), see gemm_persistent_kernel (rows of A grouped) and
-// gemm_kernel (the reduction axis grouped).
-struct GemmGroups {
-    const int32_t *ends;  // device memory, `count` non-decreasing row numbers, the last one <= M
-    int count;
-    int64_t b_group_bytes, bs_group_bytes;
 };
 
 // The kernel. LDS holds two A buffers, two B buffers and their scale dwords; the software pipeline
@@ -394,7 +387,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
     const uint8_t *__restrict__ a_q, const uint8_t *__restrict__ a_s, const uint8_t *__restrict__ b_q,
     const uint8_t *__restrict__ b_s, int M, int N, int K, uint8_t *__restrict__ c, int64_t ldc_bytes,
     int tiles_m, int tiles_n, uint8_t *__restrict__ cq, uint8_t *__restrict__ cs, uint8_t *__restrict__ cqT,
-    uint8_t *__restrict__ csT, GemmGroups groups)
+    uint8_t *__restrict__ csT, GemmGroups groups, GemmTail tail)
 {
     static_assert(!(GROUPED || KGROUPED) || (FUSE_Q == 0 && Cfg::ALL_E4M3), "grouped products: MXFP8-E4M3 operands, plain epilogue");
     static_assert(!GROUPED || (!RAGGED && !KGROUPED), "rows and K steps are not grouped at once");
@@ -415,14 +408,8 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
     const int nkb = K / Cfg::SBLK;
     const int KT = K / BK;
     int ntiles = tiles_m * tiles_n;
-    if constexpr (GROUPED) {
-        ntiles = 0;
-        for (int e = 0, prev = 0; e < groups.count; ++e) {
-            const int end = min(max(groups.ends[e], prev), M);
-            ntiles += (end - prev + Cfg::BM - 1) / Cfg::BM * tiles_n;
-            prev = end;
-        }
-    }
+    if constexpr (GROUPED)
+        ntiles = grouped_tiles<Cfg::BM>(groups, M, tiles_n);
     if constexpr (KGROUPED) {
         const int per_expert = ntiles, pieces = N * (OUT_BF16 ? 2 : 4) / 16;
         ntiles = 0;
@@ -440,7 +427,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
     }
     const int stride = gridDim.x;
     // >= 1 when the host knows the number of tiles (the grid has at most that many workgroups)
-    const int my_tiles = (ntiles - (int)blockIdx.x + stride - 1) / stride;
+    const int my_tiles = (tail.first(ntiles) - (int)blockIdx.x + stride - 1) / stride;
     if ((GROUPED || KGROUPED) && my_tiles <= 0)
         return;  // the whole workgroup, before any barrier
 
@@ -463,8 +450,14 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
     constexpr int s_dword = TILED ? 256 : 4;     // ... and from one scale dword of a K step to its next one
     const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
 
-    // operand pointers of a tile at K step 0 (wavefront-uniform)
-    struct Tile {
+    // operand pointers of a tile at K step 0 (wavefront-uniform). What only one form needs is no member of the others: members
+    // that nobody sets keep a copied tile in scratch memory, which costs a launch 1 us.
+    struct Nothing {};
+    struct Range {
+        int steps;   // K steps of the tile's expert
+        uint8_t *c;  // output of the tile's expert
+    };
+    struct Tile : std::conditional_t<KGROUPED, Range, Nothing> {
         const uint8_t *a, *b, *as, *bs;
         int m0, n0;
         uint32_t as_off, bs_off;  // this lane's offset from as / bs
@@ -472,7 +465,6 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
         int rows;  // GROUPED: rows of the tile that belong to its expert (stored)
         int lim;   // GROUPED: last row of the tile, counted from m0, that may be read from A
         int steps;   // KGROUPED: K steps of its expert
-        uint8_t *c;  // KGROUPED: output of its expert
     };
     // Scale requests of the 64 operand rows from `first` on: base and this lane's offset. Tiled scales keep 64 rows
     // together, but a tile that was moved back may begin between two such groups.
@@ -497,22 +489,14 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
         if constexpr (GROUPED) {
             // The workgroups that run side by side have consecutive ids: they work on the same expert (all
             // XCDs then stream the same B operand), and inside the expert's tiles the XCD-aware order applies.
-            int u = (int)blockIdx.x + index * stride;
-            int e = 0, prev = 0, end = 0, tiles_e = 0;
-            for (; e < groups.count; ++e) {  // u < ntiles = the sum of the groups' tiles: the scan ends inside
-                end = min(max(groups.ends[e], prev), M);
-                tiles_e = (end - prev + Cfg::BM - 1) / Cfg::BM * tiles_n;
-                if (u < tiles_e)
-                    break;
-                u -= tiles_e;
-                prev = end;
-            }
-            panel_tile(xcd_logical_id(u, tiles_e), tiles_e / tiles_n, tiles_n, tm, tn);
-            t.m0 = prev + tm * Cfg::BM;
-            t.rows = min(Cfg::BM, end - t.m0);
+            const GroupTile at = grouped_tile<Cfg::BM>(groups, M, tiles_n, (int)blockIdx.x + index * stride);
+            tm = at.tm;
+            tn = at.tn;
+            t.m0 = at.begin + at.tm * Cfg::BM;
+            t.rows = min(Cfg::BM, at.end - t.m0);
             t.lim = M - 1 - t.m0;
-            bq += e * groups.b_group_bytes;
-            bsc += e * groups.bs_group_bytes;
+            bq += at.expert * groups.b_group_bytes;
+            bsc += at.expert * groups.bs_group_bytes;
         } else {
             int u = (int)blockIdx.x + index * stride, count = ntiles;
             if constexpr (KGROUPED) {
@@ -677,10 +661,18 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
 
     Tile cur_tile = tile_at(0);
     // KGROUPED: the tile after the next one; past the last tile, that one again
-    [[maybe_unused]] Tile after_next = KGROUPED && my_tiles > 1 ? tile_at(1) : cur_tile;
+    std::conditional_t<KGROUPED, Tile, Nothing> after_next;
     // prologue of the workgroup's first tile: A(0), B(0) into buffers 0, A(1) into A buffer 1
-    const Tile &second = KGROUPED && cur_tile.steps == 1 ? after_next : cur_tile;
-    const int second_step = KGROUPED && cur_tile.steps == 1 ? 0 : 1;
+    const uint8_t *a_second = cur_tile.a + BK, *as_second = cur_tile.as + s_step;
+    uint32_t as_off_second = cur_tile.as_off;
+    if constexpr (KGROUPED) {
+        after_next = my_tiles > 1 ? tile_at(1) : cur_tile;
+        if (cur_tile.steps == 1) {
+            a_second = after_next.a;
+            as_second = after_next.as;
+            as_off_second = after_next.as_off;
+        }
+    }
 #pragma unroll
     for (int t = 0; t < Cfg::NA; ++t)
         issue_a(t, cur_tile.a, cur_tile.as, cur_tile.as_off, 0, cur_tile.lim);
@@ -689,7 +681,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
         issue_b(t, cur_tile.b, cur_tile.bs, cur_tile.bs_off, 0);
 #pragma unroll
     for (int t = 0; t < Cfg::NA; ++t)
-        issue_a(t, second.a + second_step * BK, second.as + second_step * s_step, second.as_off, 1, cur_tile.lim);
+        issue_a(t, a_second, as_second, as_off_second, 1, cur_tile.lim);
     MXFP8_WAIT_VMCNT(0);
     __syncthreads();
 #pragma unroll
@@ -702,10 +694,18 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
     int par = 0;  // LDS buffer parity of the workgroup's running step count
     for (int ti = 0; ti < my_tiles; ++ti) {
         const bool has_next = ti + 1 < my_tiles;
-        const Tile next_tile = KGROUPED ? after_next : has_next ? tile_at(ti + 1) : cur_tile;
-        if constexpr (KGROUPED)
+        auto following = [&]() __attribute__((always_inline)) {
+            if constexpr (KGROUPED)
+                return after_next;
+            else
+                return has_next ? tile_at(ti + 1) : cur_tile;
+        };
+        const Tile next_tile = following();
+        int steps = KT;
+        if constexpr (KGROUPED) {
             after_next = ti + 2 < my_tiles ? tile_at(ti + 2) : next_tile;
-        const int steps = KGROUPED ? cur_tile.steps : KT;
+            steps = cur_tile.steps;
+        }
         for (int kt = 0; kt < steps; ++kt) {
             // source of the step after this one (B) and of the one after that (A): this tile, else the
             // first steps of the next tile, else (last tile) this tile's last step once more
@@ -759,7 +759,10 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
         // the wavefront's staging area, so that the converted values of only one row group are live at a
         // time next to the A fragments of the next tile.
         constexpr int ESZ = OUT_BF16 ? 2 : 4;
-        uint8_t *ctile = (KGROUPED ? cur_tile.c : c) + (int64_t)cur_tile.m0 * ldc_bytes + (int64_t)cur_tile.n0 * ESZ;
+        uint8_t *ctile = c;
+        if constexpr (KGROUPED)
+            ctile = cur_tile.c;
+        ctile += (int64_t)cur_tile.m0 * ldc_bytes + (int64_t)cur_tile.n0 * ESZ;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             uint8_t *crow = ctile + (int64_t)(i * 16) * ldc_bytes;
@@ -964,7 +967,7 @@ static bool goes_resident(int bm, int bn, int M, int N, int K, const void *c, in
 
 template <class Cfg, bool OUT_BF16, bool TILED>
 static hipError_t launch_cfg(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s,
-                             int M, int N, int K, void *c, int64_t ldc, int max_workgroups, hipStream_t stream)
+                             int M, int N, int K, void *c, int64_t ldc, int max_workgroups, GemmTail tail, hipStream_t stream)
 {
     const int tiles_m = (M + Cfg::BM - 1) / Cfg::BM, tiles_n = (N + Cfg::BN - 1) / Cfg::BN;
     const int64_t ldc_bytes = ldc * (OUT_BF16 ? 2 : 4);
@@ -988,7 +991,7 @@ static hipError_t launch_cfg(const uint8_t *a_q, const uint8_t *a_s, const uint8
         hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Cfg::THREADS), Cfg::LDS_BYTES_PERSISTENT, stream, a_q, a_s, b_q, b_s, M, N, K,
                            static_cast<uint8_t *>(c), ldc_bytes, tiles_m, tiles_n, static_cast<uint8_t *>(nullptr),
                            static_cast<uint8_t *>(nullptr), static_cast<uint8_t *>(nullptr),
-                           static_cast<uint8_t *>(nullptr), GemmGroups{nullptr, 0, 0, 0});
+                           static_cast<uint8_t *>(nullptr), GemmGroups{nullptr, 0, 0, 0}, tail);
         return hipGetLastError();
     }
     auto kern = gemm_kernel<Cfg, OUT_BF16, TILED>;
@@ -1005,27 +1008,30 @@ static hipError_t launch_cfg(const uint8_t *a_q, const uint8_t *a_s, const uint8
 template <class Cfg>
 static hipError_t launch_any(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s, int M,
                              int N, int K, void *c, bool c_bf16, bool tiled, int64_t ldc, int max_workgroups,
-                             hipStream_t stream)
+                             hipStream_t stream, GemmTail tail = {0, 0})
 {
     if constexpr (Cfg::SCALED)
         if (tiled)
-            return c_bf16 ? launch_cfg<Cfg, true, true>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream)
-                          : launch_cfg<Cfg, false, true>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream);
-    return c_bf16 ? launch_cfg<Cfg, true, false>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream)
-                  : launch_cfg<Cfg, false, false>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream);
+            return c_bf16 ? launch_cfg<Cfg, true, true>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, tail, stream)
+                          : launch_cfg<Cfg, false, true>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, tail, stream);
+    return c_bf16 ? launch_cfg<Cfg, true, false>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, tail, stream)
+                  : launch_cfg<Cfg, false, false>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, tail, stream);
 }
 
 // ---- staged kernel (gemm_staged.h): everything that 256x256 tiles cannot spread over the chip -------------------
-template <class Cfg, bool OUT_BF16, bool TILED>
+// TAIL: of the 256x256 tiles that the resident kernel left, `tail_tiles` quarters at most
+template <class Cfg, bool OUT_BF16, bool TILED, int TAIL = kNoTail>
 static hipError_t launch_staged_t(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s, int M, int N, int K,
-                                  void *c, int64_t ldc, int max_workgroups, hipStream_t stream)
+                                  void *c, int64_t ldc, int max_workgroups, hipStream_t stream, GemmTail tail = {0, 0}, int tail_tiles = 0,
+                                  const GemmGroups &groups = {nullptr, 0, 0, 0})
 {
-    const int tiles_m = (M + Cfg::BM - 1) / Cfg::BM, tiles_n = (N + Cfg::BN - 1) / Cfg::BN;
+    constexpr int BM = TAIL == kNoTail ? Cfg::BM : 256, BN = TAIL == kNoTail ? Cfg::BN : 256;
+    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const int64_t ldc_bytes = ldc * (OUT_BF16 ? 2 : 4);
     const bool vec_store = (reinterpret_cast<uintptr_t>(c) % 16 == 0) && (ldc_bytes % 16 == 0);
-    const int ntiles = tiles_m * tiles_n;
+    const int ntiles = TAIL == kNoTail ? tiles_m * tiles_n : tail_tiles;
     const int grid = max_workgroups > 0 && max_workgroups < ntiles ? max_workgroups : ntiles;
-    auto kern = gemm_staged_kernel<Cfg, OUT_BF16, TILED>;
+    auto kern = gemm_staged_kernel<Cfg, OUT_BF16, TILED, TAIL>;
     constexpr int lds = Cfg::lds_bytes(TILED);
     if (lds > 64 * 1024) {  // what a launch may ask for by itself
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -1033,20 +1039,21 @@ static hipError_t launch_staged_t(const uint8_t *a_q, const uint8_t *a_s, const 
             return e;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Cfg::THREADS), lds, stream, a_q, a_s, b_q, b_s, M, N, K,
-                       static_cast<uint8_t *>(c), ldc_bytes, tiles_m, tiles_n, vec_store);
+                       static_cast<uint8_t *>(c), ldc_bytes, tiles_m, tiles_n, vec_store, tail, groups);
     return hipGetLastError();
 }
 
-template <class Cfg>
+template <class Cfg, int TAIL = kNoTail>
 static hipError_t launch_staged_cfg(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s, int M, int N, int K,
-                                    void *c, bool c_bf16, bool tiled, int64_t ldc, int max_workgroups, hipStream_t stream)
+                                    void *c, bool c_bf16, bool tiled, int64_t ldc, int max_workgroups, hipStream_t stream,
+                                    GemmTail tail = {0, 0}, int tail_tiles = 0, const GemmGroups &groups = {nullptr, 0, 0, 0})
 {
     if constexpr (Cfg::SCALED)
         if (tiled)
-            return c_bf16 ? launch_staged_t<Cfg, true, true>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream)
-                          : launch_staged_t<Cfg, false, true>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream);
-    return c_bf16 ? launch_staged_t<Cfg, true, false>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream)
-                  : launch_staged_t<Cfg, false, false>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream);
+            return c_bf16 ? launch_staged_t<Cfg, true, true, TAIL>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream, tail, tail_tiles, groups)
+                          : launch_staged_t<Cfg, false, true, TAIL>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream, tail, tail_tiles, groups);
+    return c_bf16 ? launch_staged_t<Cfg, true, false, TAIL>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream, tail, tail_tiles, groups)
+                  : launch_staged_t<Cfg, false, false, TAIL>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream, tail, tail_tiles, groups);
 }
 
 // Which tile: an estimate of the time, what a launch costs around its K loop plus (rounds of tiles over the compute units)
@@ -1071,7 +1078,7 @@ static hipError_t launch_staged_cfg(const uint8_t *a_q, const uint8_t *a_s, cons
 // 153.8 us as one-tile 256x256 workgroups, 138.4 as staged 64x128 tiles; [6144 x 6922 x 3456]: 211.6 us, 235.0 as staged
 // 128x128 tiles).
 // units: compute units that the launch may use; all_units: it may use all of them; route(bm, bn): how 256-row tiles would run.
-enum class Tile { k256, k256x192, k128, k128x64, k64x128, k64, k32x64, k32 };
+enum class Tile { k256, k256_tail, k256x192, k128, k128x64, k64x128, k64, k32x64, k32 };
 enum class Route { resident, one_tile, none };
 struct TileOption {
     Tile tile;
@@ -1104,6 +1111,17 @@ template <class F> static TileOption choose_tile(int64_t M, int64_t N, int64_t K
             best = o;
         }
     }
+    // 256x256 tiles for the full rounds, a rest of few tiles as quarters on the staged kernel, in a launch of its own (8 us around
+    // its K loop). A round of few 256x256 tiles takes 0.7 us per step, a round of 128x128 tiles 0.43. In us, whole | with the rest as
+    // quarters: [4352 x 4096 x 4096] (272 tiles, BF16 out, tiled) 73.4 | 70.2, [5376 x 3328 x 8192] 133.5 | 123.5, FP32 out, row-major
+    // 156.9 | 138.2; but [4352 x 4096 x 1024] 27.2 | 29.0, [7828 x 4400 x 4480] (46 more than two rounds) 129.1 | 134.3.
+    const TileOption &whole = options[0], &quarter = options[2];
+    const int64_t n = whole.tiles(M, N), rest = n % units;
+    if (all_units && n > units && rest > 0 && 8 * rest <= units && KT >= 28 && route(256, 256) == Route::resident &&
+        whole.around_us + (double)(n / units * KT) * whole.step_us + 8.0 + (double)KT * quarter.step_us < least) {
+        best = whole;
+        best.tile = Tile::k256_tail;
+    }
     return best;
 }
 
@@ -1128,6 +1146,7 @@ static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const u
     };
     const int KT = K / BK;
     Tile tile = Tile::k256;
+    int units = 0;
     bool two_buffers = K < 4 * BK && !many;  // 128x128 tiles on the resident or the one-tile kernel instead of the staged one
     if (K >= 4 * BK) {
         int device_units = 0;
@@ -1135,11 +1154,11 @@ static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const u
         if (e != hipSuccess)
             return e;
         const bool all_units = max_workgroups == 0 || max_workgroups >= device_units;
-        const int units = all_units ? device_units : max_workgroups;
+        units = all_units ? device_units : max_workgroups;
         const TileOption o = choose_tile(M, N, KT, units, all_units, route);
         tile = o.tile;
         const int64_t tiles128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
-        const bool staged = tile != Tile::k256 && tile != Tile::k256x192;
+        const bool staged = tile != Tile::k256 && tile != Tile::k256x192 && tile != Tile::k256_tail;
         if (staged && goes_resident(128, 128, M, N, K, c, ldc_bytes, esize)) {
             // Few K steps and several tiles per workgroup: the resident kernel fetches the next tile under the epilogue of
             // the last, the staged one starts anew. [896 x 2688 x 512] on 40 workgroups (row-major scales): staged 18.0 us,
@@ -1171,6 +1190,13 @@ static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const u
     case Tile::k32: MXFP8_STAGED(32, 32);
     case Tile::k256x192:
         return launch_any<GemmCfg<256, 192, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream);
+    case Tile::k256_tail: {
+        const GemmTail tail = {units, units};
+        const int n = ((M + 255) / 256) * ((N + 255) / 256);
+        const hipError_t e = launch_any<GemmCfg<256, 256, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, 0, stream, tail);
+        return e != hipSuccess ? e : launch_staged_cfg<StagedCfg<128, 128, FMT, A5, B5>, kTailPlain>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, 0,
+                                                                                                    stream, tail, 4 * (n - tail.first(n)));
+    }
     case Tile::k256: break;
     }
 #undef MXFP8_STAGED
@@ -1204,6 +1230,12 @@ static hipError_t launch_grouped_cfg(const uint8_t *a_q, const uint8_t *a_s, con
     hipError_t e = persistent_grid((int)(most_tiles < 0x7FFFFFFF ? most_tiles : 0x7FFFFFFF), max_workgroups, grid);
     if (e != hipSuccess)
         return e;
+    // Where there can be more tiles than units, few tiles of an unfilled last round are computed as quarters, like those of a plain
+    // product (choose_tile), which has other tiles to choose from. Only the device knows how many there are: with none to
+    // compute the second launch costs 3 us.
+    GemmTail tail = {0, 0};
+    if (Cfg::BM == 256 && max_workgroups == 0 && most_tiles > grid && K >= 16 * BK)
+        tail = {grid, K >= 28 * BK ? grid / 4 : grid / 8};
     auto kern = gemm_persistent_kernel<Cfg, OUT_BF16, TILED, spread_fits<Cfg>(), 0, MXFP8_GEMM_SCHED, true>;
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                             Cfg::LDS_BYTES_PERSISTENT);
@@ -1211,8 +1243,13 @@ static hipError_t launch_grouped_cfg(const uint8_t *a_q, const uint8_t *a_s, con
         return e;
     uint8_t *none = nullptr;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Cfg::THREADS), Cfg::LDS_BYTES_PERSISTENT, stream, a_q, a_s, b_q, b_s, M, N, K,
-                       static_cast<uint8_t *>(c), ldc_bytes, 0, tiles_n, none, none, none, none, groups);
-    return hipGetLastError();
+                       static_cast<uint8_t *>(c), ldc_bytes, 0, tiles_n, none, none, none, none, groups, tail);
+    e = hipGetLastError();
+    if constexpr (Cfg::BM == 256 && Cfg::BN == 256)
+        if (e == hipSuccess && tail.units > 0)
+            return launch_staged_t<StagedCfg<128, 128>, OUT_BF16, TILED, kTailGrouped>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, 0, stream, tail,
+                                                                                        4 * tail.most, groups);
+    return e;
 }
 
 // Weight-gradient form of the grouped product: resident workgroups where 256x256 tiles go resident (see gemm_persistent_kernel,
@@ -1243,7 +1280,7 @@ static hipError_t launch_kgrouped_cfg(const uint8_t *a_q, const uint8_t *a_s, co
                 return e;
             uint8_t *none = nullptr;
             hipLaunchKernelGGL(kern, dim3((unsigned)units), dim3(Cfg::THREADS), Cfg::LDS_BYTES_PERSISTENT, stream, a_q, a_s, b_q, b_s, M, N, K,
-                               static_cast<uint8_t *>(c), ldc_bytes, tiles_m, tiles_n, none, none, none, none, groups);
+                               static_cast<uint8_t *>(c), ldc_bytes, tiles_m, tiles_n, none, none, none, none, groups, GemmTail{0, 0});
             return hipGetLastError();
         }
     }
@@ -1347,7 +1384,7 @@ static hipError_t launch_fused_cfg(const uint8_t *a_q, const uint8_t *a_s, const
     if (e != hipSuccess)
         return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Cfg::THREADS), Cfg::LDS_BYTES_PERSISTENT, stream, a_q, a_s, b_q, b_s, M, N, K,
-                       static_cast<uint8_t *>(c), ldc_bytes, tiles_m, tiles_n, cq, cs, cqT, csT, GemmGroups{nullptr, 0, 0, 0});
+                       static_cast<uint8_t *>(c), ldc_bytes, tiles_m, tiles_n, cq, cs, cqT, csT, GemmGroups{nullptr, 0, 0, 0}, GemmTail{0, 0});
     return hipGetLastError();
 }
 

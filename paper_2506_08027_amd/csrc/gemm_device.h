@@ -39,6 +39,56 @@ __device__ __forceinline__ void tile_of_block(int bid, int nblocks, int tiles_m,
     panel_tile(xcd_logical_id(bid, nblocks), tiles_m, tiles_n, tm, tn);
 }
 
+// Expert groups of the grouped products (Appendix A.4): rows of A, or the reduction axis, sorted by expert.
+struct GemmGroups {
+    const int32_t *ends;  // device memory, `count` non-decreasing row numbers, the last one <= M
+    int count;
+    int64_t b_group_bytes, bs_group_bytes;
+};
+
+// Where the tiles of a problem do not fill the last round over the units, the rest of them (at most `most`) is left to a second
+// launch that computes them as quarters (gemm_staged_kernel). units = 0: no such split.
+struct GemmTail {
+    int units, most;
+    // how many of n tiles the first launch computes
+    __host__ __device__ int first(int n) const
+    {
+        const int rest = units > 0 ? n % units : 0;
+        return n > units && rest <= most ? n - rest : n;
+    }
+};
+
+// Tile `u` of the tiles of all experts (BM rows each, tiles_n per row of tiles): its expert, that expert's rows [begin, end) and
+// the tile's place among the expert's. Ends are clamped to [previous end, M]. u is smaller than grouped_tiles().
+struct GroupTile {
+    int expert, begin, end, tm, tn;
+};
+template <int BM> __device__ __forceinline__ int grouped_tiles(const GemmGroups &groups, int M, int tiles_n)
+{
+    int n = 0;
+    for (int e = 0, prev = 0; e < groups.count; ++e) {
+        const int end = min(max(groups.ends[e], prev), M);
+        n += (end - prev + BM - 1) / BM * tiles_n;
+        prev = end;
+    }
+    return n;
+}
+template <int BM> __device__ __forceinline__ GroupTile grouped_tile(const GemmGroups &groups, int M, int tiles_n, int u)
+{
+    GroupTile t = {0, 0, 0, 0, 0};
+    int tiles_e = 0;
+    for (; t.expert < groups.count; ++t.expert) {
+        t.end = min(max(groups.ends[t.expert], t.begin), M);
+        tiles_e = (t.end - t.begin + BM - 1) / BM * tiles_n;
+        if (u < tiles_e)
+            break;
+        u -= tiles_e;
+        t.begin = t.end;
+    }
+    panel_tile(xcd_logical_id(u, tiles_e), tiles_e / tiles_n, tiles_n, t.tm, t.tn);
+    return t;
+}
+
 // Nothing may be scheduled across this point: the instruction order below is the schedule.
 #define MXFP8_PIN() __builtin_amdgcn_sched_barrier(0)
 // s_waitcnt vmcnt(n), other counters untouched (gfx9 encoding: vmcnt is split over bits 3:0 and 15:14)

@@ -176,9 +176,9 @@ def test_grouped_wgrad_bad_ends_are_clamped(hostmodel, tmp_path):
     _wgrad_check(out, M, N, N, ops, [256, 128, 9999], False)
 
 
-@pytest.mark.parametrize("M,N,bf16,tiled,mode", [(264, 272, True, False, MODES[0]), (256, 512, False, True, MODES[3])],
-                         ids=["ragged-rowmajor", "whole-tiled"])
-def test_grouped_wgrad_resident(hostmodel, tmp_path, M, N, bf16, tiled, mode):
+@pytest.mark.parametrize("M,N,bf16,tiled,workgroups,mode", [(264, 272, True, False, 5, MODES[0]), (264, 768, False, True, 8, MODES[3])],
+                         ids=["rowmajor", "tiled-by-xcd"])
+def test_grouped_wgrad_resident(hostmodel, tmp_path, M, N, bf16, tiled, workgroups, mode):
     """Resident 256x256 tiles: experts of 0 .. 3 K steps side by side, so that requests one and two steps ahead end in the
     same tile, the next one and the one after it; ragged tiles moved back; workgroups with several tiles and with one."""
     steps = [1, 1, 0, 2, 0, 3, 1, 1] + [0] * 56
@@ -188,6 +188,6 @@ def test_grouped_wgrad_resident(hostmodel, tmp_path, M, N, bf16, tiled, mode):
     b = oracle.quantize_rowwise(np.asarray(si.activations(N, K, seed=9, bf16=False), np.float32))
     ops = (a[0], a[1], b[0], b[1])
     line, out = _wgrad_case(tmp_path, M, N, K, ops, ends, bf16, N + 16, tiled=tiled)
-    _, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_CUS=5, **mode)
-    assert calls[0] == (0, list(range(5)))
+    _, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_CUS=workgroups, **mode)
+    assert calls[0] == (0, list(range(workgroups)))
     _wgrad_check(out, M, N, N + 16, ops, ends, bf16)
