@@ -28,6 +28,7 @@ _AXIS = {"rowwise": ROWWISE, "colwise": COLWISE, "both": BOTH, ROWWISE: ROWWISE,
 _PASS = {"fprop": FPROP, "dgrad": DGRAD, "wgrad": WGRAD, FPROP: FPROP, DGRAD: DGRAD, WGRAD: WGRAD}
 
 _lib = None
+_fast = None   # the same calls in C++ (csrc/fastcall.cpp), bound to the library that load() opened
 
 
 class MXFP8Error(RuntimeError):
@@ -38,7 +39,7 @@ class MXFP8Error(RuntimeError):
 
 def load() -> ctypes.CDLL:
     """Load the in-tree HIP library; fails loudly when it has not been built."""
-    global _lib
+    global _lib, _fast
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -98,7 +99,28 @@ def load() -> ctypes.CDLL:
     lib.mxfp8_status_string.restype = ctypes.c_char_p
     lib.mxfp8_status_string.argtypes = [ci]
     _lib = lib
+    _fast = _bind_fastcall(lib)
     return lib
+
+
+def _bind_fastcall(lib):
+    """csrc/fastcall.cpp on the entry points of `lib`. Without the module every call takes the checks below."""
+    try:
+        from . import _fastcall
+    except ImportError:
+        return None
+    _fastcall.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
+        "mxfp8_quantize_mode_ex", "mxfp8_gemm_ex", "mxfp8_gemm_mode_ex", "mxfp8_dequantize_mode_ex", "mxfp8_gemm_bf16",
+        "mxfp8_gemm_quantize_ex", "mxfp8_fp4_quantize_ex", "mxfp8_fp4_gemm_ex", "mxfp8_fp6_quantize_ex")})
+    return _fastcall
+
+
+def _done(rc, what) -> bool:
+    """Whether a call of _fast is all: it launched (True), the entry point refused it (raises), or its arguments are not the
+    ordinary ones and the caller goes on with its own checks (False)."""
+    if rc > OK:
+        raise MXFP8Error(rc, what)
+    return rc == OK
 
 
 def status_string(code: int) -> str:
@@ -177,6 +199,8 @@ def mxfp8_quantize_mode_ex(src, axis, element=E4M3, rule=SCALE_ROUND_UP, q_row=N
                            s_colT=None, scale_layout=SCALES_ROWMAJOR, stream=None) -> None:
     """mxfp8_quantize_ex with the element format (E4M3 / E5M2) and the scale rule (SCALE_ROUND_UP /
     SCALE_OCP_V1) of the paper's ablations."""
+    if _fast is not None and _done(_fast.quantize(src, axis, element, rule, q_row, s_row, q_colT, s_colT, scale_layout, _stream(stream)), "mxfp8_quantize"):
+        return
     _need_cuda(src, q_row, s_row, q_colT, s_colT)
     if src.dim() != 2 or (src.numel() and src.stride(1) != 1):
         raise ValueError("src must be 2-D with contiguous rows")
@@ -202,6 +226,8 @@ def mxfp8_gemm(pass_, a_q, a_s, b_q, b_s, c, stream=None) -> None:
 def mxfp8_gemm_ex(pass_, a_q, a_s, b_q, b_s, c, scale_layout=SCALES_ROWMAJOR, max_workgroups=0, stream=None) -> None:
     """mxfp8_gemm with both scale operands stored in `scale_layout`, on at most `max_workgroups` compute
     units (0 = all)."""
+    if _fast is not None and _done(_fast.gemm(pass_, a_q, a_s, b_q, b_s, c, scale_layout, max_workgroups, _stream(stream)), "mxfp8_gemm"):
+        return
     _need_cuda(a_q, a_s, b_q, b_s, c)
     M, K = a_q.shape
     N, Kb = b_q.shape
@@ -224,6 +250,8 @@ def mxfp8_gemm_ex(pass_, a_q, a_s, b_q, b_s, c, scale_layout=SCALES_ROWMAJOR, ma
 def mxfp8_gemm_mode_ex(pass_, a_q, a_s, a_element, b_q, b_s, b_element, c, scale_layout=SCALES_ROWMAJOR, max_workgroups=0,
                        stream=None) -> None:
     """mxfp8_gemm_ex with the element format (E4M3 / E5M2) of each operand chosen by the caller."""
+    if _fast is not None and _done(_fast.gemm_mode(pass_, a_q, a_s, a_element, b_q, b_s, b_element, c, scale_layout, max_workgroups, _stream(stream)), "mxfp8_gemm_mode_ex"):
+        return
     _need_cuda(a_q, a_s, b_q, b_s, c)
     M, K = a_q.shape
     N, Kb = b_q.shape
@@ -299,6 +327,8 @@ def mxfp8_gemm_grouped_ex(pass_, a_q, a_s, b_q, b_s, group_ends, c, scale_layout
 def mxfp8_gemm_bf16(a, b, c, max_workgroups=0, stream=None) -> None:
     """c [M x N] (float32 or bfloat16) = a [M x K] * b[N x K]^T for dense bfloat16 operands: the GEMM of the
     simulated MX path."""
+    if _fast is not None and _done(_fast.gemm_bf16(a, b, c, max_workgroups, _stream(stream)), "mxfp8_gemm_bf16"):
+        return
     _need_cuda(a, b, c)
     M, K = a.shape
     N, Kb = b.shape
@@ -317,6 +347,8 @@ def mxfp8_gemm_quantize_ex(pass_, a_q, a_s, b_q, b_s, c, axis, cq_row=None, cs_r
                            scale_layout=SCALES_ROWMAJOR, max_workgroups=0, stream=None) -> None:
     """mxfp8_gemm_ex with bfloat16 c [M x N] plus the MXFP8 copies of c selected by `axis`:
     cq_row [M x N] / cs_row and cq_colT [N x M] / cs_colT."""
+    if _fast is not None and _done(_fast.gemm_quantize(pass_, a_q, a_s, b_q, b_s, c, axis, cq_row, cs_row, cq_colT, cs_colT, scale_layout, max_workgroups, _stream(stream)), "mxfp8_gemm_quantize_ex"):
+        return
     _need_cuda(a_q, a_s, b_q, b_s, c, cq_row, cs_row, cq_colT, cs_colT)
     M, K = a_q.shape
     N, Kb = b_q.shape
@@ -348,6 +380,8 @@ def mxfp8_dequantize(q, s, dst, stream=None) -> None:
 
 def mxfp8_dequantize_ex(q, s, dst, scale_layout=SCALES_ROWMAJOR, stream=None, element=E4M3) -> None:
     """mxfp8_dequantize with s stored in `scale_layout` and the element bytes in `element` format."""
+    if _fast is not None and _done(_fast.dequantize(q, s, element, dst, scale_layout, _stream(stream)), "mxfp8_dequantize"):
+        return
     _need_cuda(q, s, dst)
     rows, cols = q.shape
     if tuple(dst.shape) != (rows, cols):
@@ -423,6 +457,8 @@ def mxfp8_fp4_quantize_ex(src, axis, q_row=None, s_row=None, q_colT=None, s_colT
                           scale_layout=SCALES_ROWMAJOR, stream=None) -> None:
     """src [rows x cols] float32/bfloat16 -> MXFP4 copies: q_row [rows x cols/2], q_colT [cols x rows/2] (two E2M1
     codes per byte), scales as for MXFP8."""
+    if _fast is not None and _done(_fast.fp4_quantize(src, axis, q_row, s_row, q_colT, s_colT, scale_layout, _stream(stream)), "mxfp8_fp4_quantize_ex"):
+        return
     _need_cuda(src, q_row, s_row, q_colT, s_colT)
     if src.dim() != 2 or (src.numel() and src.stride(1) != 1):
         raise ValueError("src must be 2-D with contiguous rows")
@@ -459,6 +495,8 @@ def mxfp8_fp4_dequantize_ex(q, s, dst, scale_layout=SCALES_ROWMAJOR, stream=None
 def mxfp8_fp4_gemm_ex(pass_, a_q, a_s, b_q, b_s, c, scale_layout=SCALES_ROWMAJOR, max_workgroups=0, stream=None) -> None:
     """c [M x N] (float32/bfloat16) = A . B^T for MXFP4 operands a_q [M x K/2], b_q [N x K/2] (packed E2M1 codes) with
     block scales [. x K/32] in `scale_layout`."""
+    if _fast is not None and _done(_fast.fp4_gemm(pass_, a_q, a_s, b_q, b_s, c, scale_layout, max_workgroups, _stream(stream)), "mxfp8_fp4_gemm_ex"):
+        return
     _need_cuda(a_q, a_s, b_q, b_s, c)
     M, Kh = a_q.shape
     N, Kb = b_q.shape
@@ -486,6 +524,8 @@ def mxfp8_fp6_quantize_ex(src, axis, element, q_row=None, s_row=None, q_colT=Non
                           scale_layout=SCALES_ROWMAJOR, stream=None) -> None:
     """src [rows x cols] float32/bfloat16 -> MXFP6 copies: q_row [rows x cols*3/4], q_colT [cols x rows*3/4] (32 six-bit
     codes per 24 bytes), scales as for MXFP8. element: E2M3 or E3M2."""
+    if _fast is not None and _done(_fast.fp6_quantize(src, axis, element, q_row, s_row, q_colT, s_colT, scale_layout, _stream(stream)), "mxfp8_fp6_quantize_ex"):
+        return
     _need_cuda(src, q_row, s_row, q_colT, s_colT)
     if src.dim() != 2 or (src.numel() and src.stride(1) != 1):
         raise ValueError("src must be 2-D with contiguous rows")

@@ -28,6 +28,29 @@ def build_library(verbose: bool = False) -> str:
     return LIB_PATH
 
 
+FASTCALL_PATH = os.path.join(_HERE, "_fastcall.so")
+
+
+def build_fastcall() -> str:
+    """The binding's calls in C++ against PyTorch's headers (host code only); returns the path of the module."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", sysconfig.get_paths()["include"]]
+    for d in include_paths():
+        cmd += ["-isystem", d]
+    cmd += [os.path.join(CSRC, "fastcall.cpp"), "-o", FASTCALL_PATH]
+    for d in library_paths():
+        cmd += ["-L" + d, "-Wl,-rpath," + d]
+    cmd += ["-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + " ".join(cmd) + "\n" + res.stderr)
+    return FASTCALL_PATH
+
+
 EXAMPLE_SRC = os.path.join(_HERE, "examples", "linear_layer_step.cpp")
 EXAMPLE_BIN = os.path.join(_HERE, "examples", "linear_layer_step")
 
@@ -44,4 +67,5 @@ def build_example() -> str:
 
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_fastcall())
     print(build_example())
