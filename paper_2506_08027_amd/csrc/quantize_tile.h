@@ -340,8 +340,8 @@ __device__ __forceinline__ void quantize_tile(
                     *reinterpret_cast<uint32_t *>(s_row + (((r >> 6) * kt_row + tile_x) * 64 + (r & 63)) * 4) = w;
                 } else {
                     uint8_t *sp = s_row + r * nb_row + wg_col0 / kBlock;
-                    if (wg_col0 + kTile <= cols && (nb_row & 3) == 0 && (reinterpret_cast<uintptr_t>(s_row) & 3) == 0) {
-                        *reinterpret_cast<uint32_t *>(sp) = w;
+                    if (wg_col0 + kTile <= cols) {
+                        store_unaligned(sp, w);
                     } else {
 #pragma unroll
                         for (int b = 0; b < 4; ++b)
@@ -374,8 +374,8 @@ __device__ __forceinline__ void quantize_tile(
                     *reinterpret_cast<uint32_t *>(s_colT + (((c >> 6) * kt_col + tile_y) * 64 + (c & 63)) * 4) = w;
                 } else {
                     uint8_t *sp = s_colT + c * nb_col + wg_row0 / kBlock;
-                    if (wg_row0 + kTile <= rows && (nb_col & 3) == 0 && (reinterpret_cast<uintptr_t>(s_colT) & 3) == 0) {
-                        *reinterpret_cast<uint32_t *>(sp) = w;
+                    if (wg_row0 + kTile <= rows) {
+                        store_unaligned(sp, w);
                     } else {
 #pragma unroll
                         for (int b = 0; b < 4; ++b)
