@@ -4,20 +4,18 @@
 // are RNE(V_i / X) to one of 0, 0.5, 1, 1.5, 2, 3, 4, 6, ties to the even code, saturating. E2M1 has no NaN
 // and no Inf code: a NaN lives in the scale byte (0xFF) only.
 //
-// A workgroup stages its 128 x 128 tile in LDS as FP32 (row pitch 132 words: rows stay 16-byte aligned for 128-bit
-// reads along a row, and walking down a column, neighbouring work-items on neighbouring columns, is conflict-free)
-// and every work-item then converts whole 32-element blocks: along rows for the row copy, down columns for the
-// transposed column copy, 16 packed bytes per block in one 128-bit store. Elements go through the hardware
-// converter (v_cvt_scalef32_pk_fp4_f32: divides by the scale, rounds to nearest even, saturates, keeps the sign);
-// blocks with an infinity take a software encoder, blocks with a NaN are not converted at all.
-#include "mxfp8_device.h"
+// The decomposition is the MXFP8 quantizer's (quantize_tile.h): a workgroup of four wavefronts holds a 128 x 128 tile in
+// registers, 32 rows per wavefront; a row block is spread over 4 (BF16) or 8 (FP32) neighbouring lanes, a column block over the
+// 4 or 2 lanes that share its columns. Elements go through the hardware converter (v_cvt_scalef32_pk_fp4_f32: divides by the
+// scale, rounds to nearest even, saturates, keeps the sign; a form for BF16 pairs and one for FP32); blocks with an infinity or a
+// NaN are mended on their way out. The packed codes of both copies are staged in LDS as [row or column][64 bytes]
+// and leave as 16-byte pieces, the scale bytes as one dword per row and column of the tile.
+// What bounds it: HBM. The tile used to be staged in LDS as FP32 (two workgroups a unit) and converted block by block, which
+// waited for its own LDS traffic and for 16-byte stores 64 lines apart: BF16 [8192 x 4096], both copies, 29.0 -> 23.4 us (4.4 TB/s),
+// [4096 x 4096] 15.7 -> 12.0, its row copy 12.6 -> 9.7; FP32 [8192 x 4096], both, 36.9 -> 35.
+#include "quantize_tile.h"
 
 namespace mxfp8 {
-
-constexpr int kFp4Tile = 128;
-constexpr int kFp4Pitch = kFp4Tile + 4;
-constexpr int kFp4Threads = 256;
-constexpr int kFp4LdsBytes = kFp4Tile * kFp4Pitch * 4;
 
 // n + 127 for the smallest n with amax <= 6 * 2^n = 1.5 * 2^(n + 2), from the magnitude bits of an FP32 amax:
 // amax = (1 + f) * 2^e needs n = e - 2 when f <= 0.5 and e - 1 otherwise, i.e. the exponent field after adding
@@ -32,41 +30,32 @@ __device__ __forceinline__ uint32_t fp4_scale_byte(uint32_t abs_bits)
     return (uint32_t)max(b, 0);
 }
 
-// E2M1 code of v / 2^n: the seven thresholds are the midpoints of neighbouring magnitudes; a midpoint goes to
-// the neighbour with the even code (0, 1, 2, 4 are even codes 0, 2, 4, 6), hence the mix of > and >=.
-__device__ __forceinline__ uint32_t fp4_code(float v, int n)
+// Two elements of a block -> byte SEL of `old` (the first in the low nibble); a BF16 pair as it lies in a word, or two FP32 values.
+template <int SEL> __device__ __forceinline__ uint32_t fp4_pair_bf16(uint32_t old, uint32_t pair, float scale)
 {
-    const float t = fabsf(ldexpf(v, -n));  // exact: a power-of-two scaling (Inf stays Inf and saturates)
-    const uint32_t mag = (uint32_t)(t > 0.25f) + (uint32_t)(t >= 0.75f) + (uint32_t)(t > 1.25f) + (uint32_t)(t >= 1.75f) +
-                         (uint32_t)(t > 2.5f) + (uint32_t)(t >= 3.5f) + (uint32_t)(t > 5.0f);
-    return mag | ((__float_as_uint(v) >> 28) & 8u);
+    return __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(old, __builtin_bit_cast(v2bf, pair), scale, SEL);
 }
-
-// 32 values -> 16 packed bytes and the block's scale byte (element 2k in the low nibble of byte k)
-__device__ __forceinline__ uint4 fp4_block(const float (&v)[kBlock], uint32_t &scale)
+template <int SEL> __device__ __forceinline__ uint32_t fp4_pair_f32(uint32_t old, uint32_t a, uint32_t b, float scale)
 {
-    uint32_t amax = 0;
+    return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(old, __uint_as_float(a), __uint_as_float(b), scale, SEL);
+}
+// The codes of a block whose scale byte is 254 or 255 (rare: it holds an infinity or a NaN), from the converter's answer q and the
+// source once more, its elements `stride` bytes apart: an infinity saturates, a block with a NaN has codes 0 only. Kept out of
+// the conversion: unrolled there it doubled the registers.
+template <bool BF16> __device__ __forceinline__ uint4 fp4_special(uint4 q, uint32_t sb, const uint8_t *src, int64_t stride)
+{
+    if (sb == 0xFFu)
+        return make_uint4(0, 0, 0, 0);
+    uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-    for (int i = 0; i < kBlock; ++i)
-        amax = umax(amax, __float_as_uint(v[i]) & 0x7FFFFFFFu);
-    const uint32_t sb = fp4_scale_byte(amax);
-    scale = sb;
-    uint32_t w[4] = {0, 0, 0, 0};
-    if (amax < 0x7F800000u) {
-        const float x = scale_operand(sb);
-#pragma unroll
-        for (int i = 0; i < kBlock; i += 8) {
-            uint32_t q = 0;
-            q = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q, v[i], v[i + 1], x, 0);
-            q = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q, v[i + 2], v[i + 3], x, 1);
-            q = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q, v[i + 4], v[i + 5], x, 2);
-            q = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q, v[i + 6], v[i + 7], x, 3);
-            w[i / 8] = q;
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll 1
+        for (int i = 0; i < 8; ++i) {
+            const uint8_t *p = src + (8 * k + i) * stride;
+            const uint32_t bits = BF16 ? (uint32_t)*reinterpret_cast<const uint16_t *>(p) << 16 : *reinterpret_cast<const uint32_t *>(p);
+            if ((bits & 0x7FFFFFFFu) == 0x7F800000u)
+                w[k] = (w[k] & ~(15u << (4 * i))) | ((7u | ((bits >> 28) & 8u)) << (4 * i));
         }
-    } else if (sb != 0xFFu) {  // a block with an infinity: +-Inf -> +-6, finite values / 2^127
-#pragma unroll
-        for (int i = 0; i < kBlock; ++i)
-            w[i / 8] |= fp4_code(v[i], 127) << (4 * (i % 8));
     }
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
@@ -77,93 +66,165 @@ template <bool TILED> __device__ __forceinline__ int64_t fp4_scale_index(int64_t
     return TILED ? (((r >> 6) * ((nb + 3) / 4) + (b >> 2)) * 64 + (r & 63)) * 4 + (b & 3) : r * nb + b;
 }
 
-// The grid is resident (a few workgroups per compute unit) and every workgroup walks over tiles blockIdx.x,
-// blockIdx.x + gridDim.x, ...: the 128-bit loads of its next tile are issued into registers before the current
-// tile is converted, so that the memory system always has reads in flight while blocks are being encoded.
-template <bool BF16, bool ROW, bool COL, bool TILED>
-__global__ __launch_bounds__(kFp4Threads) void quantize_fp4_kernel(const uint8_t *__restrict__ src, int64_t rows, int64_t cols,
-                                                                   int64_t ld_bytes, uint8_t *__restrict__ q_row,
-                                                                   uint8_t *__restrict__ s_row, uint8_t *__restrict__ q_colT,
-                                                                   uint8_t *__restrict__ s_colT, uint32_t tiles_x, uint32_t ntiles)
+// The scale bytes of up to four blocks of row r, from block b0 on (a multiple of 4).
+template <bool TILED>
+__device__ __forceinline__ void fp4_store_scales(uint8_t *s, int64_t r, int64_t b0, int64_t nb, uint32_t w)
 {
-    MXFP8_DYNAMIC_LDS(lds_raw);
-    float *tile = reinterpret_cast<float *>(lds_raw);
-    const int tid = threadIdx.x;
-    constexpr int VEC = BF16 ? 8 : 4;                          // elements per 128-bit load
-    constexpr int PER_ROW = kFp4Tile / VEC;                    // loads per tile row
-    constexpr int LOADS = kFp4Tile * PER_ROW / kFp4Threads;    // loads per work-item and tile
-    constexpr int BLOCKS = kFp4Tile / kBlock;                  // 4 blocks per tile row / column
-    uint4 regs[LOADS];
-    // rows % 32 == 0 and cols % 32 == 0: a 16-byte piece is wholly inside or outside; outside reads as zeros
-    auto fetch = [&](uint32_t t) __attribute__((always_inline)) {
-        const uint32_t ty = t / tiles_x, tx = t - ty * tiles_x;
-        const int64_t row0 = (int64_t)ty * kFp4Tile, col0 = (int64_t)tx * kFp4Tile;
+    uint8_t *p = s + fp4_scale_index<TILED>(r, b0, nb);
+    const int blocks = (int)min(nb - b0, (int64_t)4);
+    if (blocks == 4) {
+        store_unaligned(p, w);
+    } else {
+        for (int b = 0; b < blocks; ++b)
+            p[b] = (uint8_t)(w >> (8 * b));
+    }
+}
+
+template <bool BF16, bool ROW, bool COL, bool TILED>
+__global__ __launch_bounds__(kQuantThreads) void quantize_fp4_kernel(const uint8_t *__restrict__ src, int64_t rows, int64_t cols,
+                                                                     int64_t ld_bytes, uint8_t *__restrict__ q_row,
+                                                                     uint8_t *__restrict__ s_row, uint8_t *__restrict__ q_colT,
+                                                                     uint8_t *__restrict__ s_colT, uint32_t tiles_x, uint32_t ntiles)
+{
+    using T = QTraits<BF16>;
+    constexpr int VEC = T::VEC, ROWS = T::ROWS, CC = T::CC, ESIZE = BF16 ? 2 : 4;
+    constexpr int LINE = kTile / 2;  // packed bytes of a tile row or column
+    // Staged lines, with a gap after every eighth so that lanes eight (columns: eight, four) lines apart fall into different banks.
+    constexpr int ROW_GAP = 64, COL_GAP = 16;
+    __shared__ __attribute__((aligned(16))) uint8_t lds_qr[ROW ? kTile * LINE + kTile / 8 * ROW_GAP : 16];
+    __shared__ __attribute__((aligned(16))) uint8_t lds_qc[COL ? kTile * LINE + kTile / 8 * COL_GAP : 16];
+    __shared__ __attribute__((aligned(16))) uint8_t lds_rs[ROW ? kTile * 4 : 16], lds_cs[COL ? kTile * 4 : 16];
+    auto row_line = [](int r) __attribute__((always_inline)) { return r * LINE + (r >> 3) * ROW_GAP; };
+    auto col_line = [](int c) __attribute__((always_inline)) { return c * LINE + (c >> 3) * COL_GAP; };
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int cc = lane % CC, rs = lane / CC;
+    const int lrow0 = wave * 32 + rs * ROWS, lcol0 = cc * VEC;  // first row and column of this lane inside the tile
+    const int64_t nb_row = cols / kBlock, nb_col = rows / kBlock;
+    for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        const uint32_t tile_y = tile / tiles_x, tile_x = tile - tile_y * tiles_x;
+        const int64_t wg_row0 = (int64_t)tile_y * kTile, wg_col0 = (int64_t)tile_x * kTile;
+        const int64_t row0 = wg_row0 + lrow0, col0 = wg_col0 + lcol0;
+        // rows % 32 == 0 and cols % 32 == 0: the lanes of a block are all inside the tensor or all outside
+        const bool active = col0 < cols && row0 < rows;
+        uint4 x[ROWS];
 #pragma unroll
-        for (int k = 0; k < LOADS; ++k) {
-            const int idx = tid + k * kFp4Threads, r = idx / PER_ROW, c = (idx % PER_ROW) * VEC;
-            regs[k] = make_uint4(0, 0, 0, 0);
-            if (row0 + r < rows && col0 + c < cols)
-                regs[k] = stream_load(reinterpret_cast<const uint4 *>(src + (row0 + r) * ld_bytes + (col0 + c) * (BF16 ? 2 : 4)));
+        for (int i = 0; i < ROWS; ++i) {
+            x[i] = make_uint4(0, 0, 0, 0);
+            if (active)
+                x[i] = stream_load(reinterpret_cast<const uint4 *>(src + (row0 + i) * ld_bytes + col0 * ESIZE));
         }
-    };
-    if (blockIdx.x < ntiles)
-        fetch(blockIdx.x);
-    for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const uint32_t tile_y = t / tiles_x, tile_x = t - tile_y * tiles_x;
-        const int64_t row0 = (int64_t)tile_y * kFp4Tile, col0 = (int64_t)tile_x * kFp4Tile;
-        // ---- registers -> LDS, widened to FP32
-#pragma unroll
-        for (int k = 0; k < LOADS; ++k) {
-            const int idx = tid + k * kFp4Threads, r = idx / PER_ROW, c = (idx % PER_ROW) * VEC;
-            const uint4 v = regs[k];
-            float *d = tile + r * kFp4Pitch + c;
-            if constexpr (BF16) {
-                *reinterpret_cast<float4 *>(d) = make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u),
-                                                             __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xFFFF0000u));
-                *reinterpret_cast<float4 *>(d + 4) = make_float4(__uint_as_float(v.z << 16), __uint_as_float(v.z & 0xFFFF0000u),
-                                                                 __uint_as_float(v.w << 16), __uint_as_float(v.w & 0xFFFF0000u));
-            } else {
-                *reinterpret_cast<float4 *>(d) = make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
-            }
-        }
-        __syncthreads();
-        if (t + gridDim.x < ntiles)
-            fetch(t + gridDim.x);  // in flight while this tile is converted
         if constexpr (ROW) {
-            const int64_t nb = cols / kBlock;
-            for (int item = tid; item < kFp4Tile * BLOCKS; item += kFp4Threads) {
-                const int r = item / BLOCKS, b = item % BLOCKS;
-                if (row0 + r < rows && col0 + b * kBlock < cols) {
-                    uint32_t sb;
-                    float v[kBlock];
 #pragma unroll
-                    for (int i = 0; i < kBlock; i += 4) {
-                        const float4 f = *reinterpret_cast<const float4 *>(tile + r * kFp4Pitch + b * kBlock + i);
-                        v[i] = f.x; v[i + 1] = f.y; v[i + 2] = f.z; v[i + 3] = f.w;
-                    }
-                    const uint4 q = fp4_block(v, sb);
-                    *reinterpret_cast<uint4 *>(q_row + (row0 + r) * (cols / 2) + (col0 + b * kBlock) / 2) = q;
-                    s_row[fp4_scale_index<TILED>(row0 + r, col0 / kBlock + b, nb)] = (uint8_t)sb;
-                }
+            for (int i = 0; i < ROWS; ++i) {
+                uint32_t am = lane_amax<BF16>(x[i]);
+                am = umax(am, dpp_xor1(am));
+                am = umax(am, dpp_xor2(am));
+                if constexpr (BF16)
+                    am <<= 16;
+                else
+                    am = umax(am, dpp_half_mirror(am));
+                const uint32_t sb = fp4_scale_byte(am);
+                const float sc = scale_operand(sb);
+                uint32_t q = 0;
+                if constexpr (BF16)
+                    q = fp4_pair_bf16<3>(fp4_pair_bf16<2>(fp4_pair_bf16<1>(fp4_pair_bf16<0>(q, x[i].x, sc), x[i].y, sc), x[i].z, sc), x[i].w, sc);
+                else
+                    q = fp4_pair_f32<1>(fp4_pair_f32<0>(q, x[i].x, x[i].y, sc), x[i].z, x[i].w, sc);
+                uint8_t *dst = lds_qr + row_line(lrow0 + i) + lcol0 / 2;
+                if constexpr (BF16)
+                    *reinterpret_cast<uint32_t *>(dst) = q;
+                else
+                    *reinterpret_cast<uint16_t *>(dst) = (uint16_t)q;
+                if (cc % (kBlock / VEC) == 0)
+                    lds_rs[(lrow0 + i) * 4 + lcol0 / kBlock] = (uint8_t)sb;
             }
         }
         if constexpr (COL) {
-            const int64_t nbT = rows / kBlock;
-            for (int item = tid; item < kFp4Tile * BLOCKS; item += kFp4Threads) {
-                const int c = item % kFp4Tile, b = item / kFp4Tile;  // neighbouring work-items walk down neighbouring columns
-                if (col0 + c < cols && row0 + b * kBlock < rows) {
-                    uint32_t sb;
-                    float v[kBlock];
+            // Maxima of the column block, two columns a word (BF16), of the magnitudes shifted up by the sign: masked as in the row
+            // direction, the compiler keeps all of them from there on, in twice the registers.
+            uint32_t cm[4];
 #pragma unroll
-                    for (int i = 0; i < kBlock; ++i)
-                        v[i] = tile[(b * kBlock + i) * kFp4Pitch + c];
-                    const uint4 q = fp4_block(v, sb);
-                    *reinterpret_cast<uint4 *>(q_colT + (col0 + c) * (rows / 2) + (row0 + b * kBlock) / 2) = q;
-                    s_colT[fp4_scale_index<TILED>(col0 + c, row0 / kBlock + b, nbT)] = (uint8_t)sb;
+            for (int w = 0; w < 4; ++w) {
+                uint32_t m = 0;
+#pragma unroll
+                for (int i = 0; i < ROWS; ++i) {
+                    const uint32_t v = word_at(x[i], w);
+                    m = BF16 ? pk_max_u16(m, __builtin_bit_cast(uint32_t, (v2us)(__builtin_bit_cast(v2us, v) << 1))) : umax(m, v << 1);
+                }
+                uint32_t o = (uint32_t)__shfl_xor((int)m, 32, 64);
+                m = BF16 ? pk_max_u16(m, o) : umax(m, o);
+                if constexpr (BF16) {
+                    o = (uint32_t)__shfl_xor((int)m, 16, 64);
+                    m = pk_max_u16(m, o);
+                }
+                cm[w] = m;
+            }
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) {
+                const uint32_t am = !BF16 ? cm[j & 3] >> 1 : (j & 1) ? (cm[j >> 1] & 0xFFFF0000u) >> 1 : (cm[j >> 1] & 0xFFFFu) << 15;
+                const uint32_t sb = fp4_scale_byte(am);
+                const float sc = scale_operand(sb);
+                uint32_t q[ROWS / 8];
+#pragma unroll
+                for (int r = 0; r < ROWS / 8; ++r) {
+                    const uint4 *y = x + 8 * r;
+                    uint32_t p[4];  // BF16: rows 2i and 2i + 1 of column j side by side
+                    q[r] = 0;
+                    if constexpr (BF16) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            p[i] = __builtin_amdgcn_perm(word_at(y[2 * i + 1], j >> 1), word_at(y[2 * i], j >> 1), (j & 1) ? 0x07060302u : 0x05040100u);
+                        q[r] = fp4_pair_bf16<3>(fp4_pair_bf16<2>(fp4_pair_bf16<1>(fp4_pair_bf16<0>(q[r], p[0], sc), p[1], sc), p[2], sc), p[3], sc);
+                    } else {
+                        q[r] = fp4_pair_f32<0>(q[r], word_at(y[0], j), word_at(y[1], j), sc);
+                        q[r] = fp4_pair_f32<1>(q[r], word_at(y[2], j), word_at(y[3], j), sc);
+                        q[r] = fp4_pair_f32<2>(q[r], word_at(y[4], j), word_at(y[5], j), sc);
+                        q[r] = fp4_pair_f32<3>(q[r], word_at(y[6], j), word_at(y[7], j), sc);
+                    }
+                }
+                uint8_t *dst = lds_qc + col_line(lcol0 + j) + lrow0 / 2;
+                if constexpr (BF16)
+                    *reinterpret_cast<uint32_t *>(dst) = q[0];
+                else
+                    *reinterpret_cast<uint2 *>(dst) = make_uint2(q[0], q[ROWS / 8 - 1]);
+                if (rs == 0)
+                    lds_cs[(lcol0 + j) * 4 + wave] = (uint8_t)sb;
+            }
+        }
+        __syncthreads();
+        // ---- write-out: four lanes a line of 64 bytes; a 16-byte piece is one block
+#pragma unroll
+        for (int k = 0; k < kTile * LINE / 16 / kQuantThreads; ++k) {
+            const int piece = k * kQuantThreads + tid, line = piece >> 2, b = piece & 3;
+            if constexpr (ROW) {
+                const int64_t r = wg_row0 + line, c = wg_col0 + b * kBlock;
+                if (r < rows && c < cols) {
+                    uint4 q = *reinterpret_cast<const uint4 *>(lds_qr + row_line(line) + b * 16);
+                    const uint32_t sb = lds_rs[line * 4 + b];
+                    if (sb >= 254)
+                        q = fp4_special<BF16>(q, sb, src + r * ld_bytes + c * ESIZE, ESIZE);
+                    *reinterpret_cast<uint4 *>(q_row + r * (cols / 2) + c / 2) = q;
+                }
+            }
+            if constexpr (COL) {
+                const int64_t c = wg_col0 + line, r = wg_row0 + b * kBlock;
+                if (c < cols && r < rows) {
+                    uint4 q = *reinterpret_cast<const uint4 *>(lds_qc + col_line(line) + b * 16);
+                    const uint32_t sb = lds_cs[line * 4 + b];
+                    if (sb >= 254)
+                        q = fp4_special<BF16>(q, sb, src + r * ld_bytes + c * ESIZE, ld_bytes);
+                    *reinterpret_cast<uint4 *>(q_colT + c * (rows / 2) + r / 2) = q;
                 }
             }
         }
-        __syncthreads();  // the tile in LDS is overwritten by the next round
+        if constexpr (ROW)
+            if (tid < kTile && wg_row0 + tid < rows)
+                fp4_store_scales<TILED>(s_row, wg_row0 + tid, wg_col0 / kBlock, nb_row, *reinterpret_cast<const uint32_t *>(lds_rs + tid * 4));
+        if constexpr (COL)  // the upper half of the workgroup, beside the row scales
+            if (tid >= kTile && wg_col0 + tid - kTile < cols)
+                fp4_store_scales<TILED>(s_colT, wg_col0 + tid - kTile, wg_row0 / kBlock, nb_col,
+                                        *reinterpret_cast<const uint32_t *>(lds_cs + (tid - kTile) * 4));
+        __syncthreads();  // the next tile reuses the staging arrays
     }
 }
 
@@ -171,36 +232,29 @@ template <bool BF16, bool TILED>
 static hipError_t launch_quantize_fp4_t(const void *src, int64_t rows, int64_t cols, int64_t ld, int axis, uint8_t *q_row,
                                         uint8_t *s_row, uint8_t *q_colT, uint8_t *s_colT, hipStream_t stream)
 {
-    const int64_t tiles_x = (cols + kFp4Tile - 1) / kFp4Tile, tiles_y = (rows + kFp4Tile - 1) / kFp4Tile;
+    const int64_t tiles_x = (cols + kTile - 1) / kTile, tiles_y = (rows + kTile - 1) / kTile;
     if (tiles_x * tiles_y > 0x7FFFFFFF)
         return hipErrorInvalidConfiguration;
-    int dev = 0, cus = 0;
-    hipError_t err = hipGetDevice(&dev);
-    if (err == hipSuccess)
-        err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (err != hipSuccess)
-        return err;
-    const int64_t ntiles = tiles_x * tiles_y, resident = 2 * (int64_t)(cus > 0 ? cus : 1);  // two tiles of LDS fit a compute unit
-    const dim3 grid((unsigned)(ntiles < resident ? ntiles : resident)), block(kFp4Threads);
+    // One workgroup per tile, except where a resident grid measured faster: both copies of BF16 sources on 4 workgroups per unit
+    // ([8192 x 4096] 25.6 -> 23.4 us; FP32 34.6 and 34.8, its row copy alone 30.7 and 32.6).
+    int64_t groups = tiles_x * tiles_y;
+    if (BF16 && axis == 3) {
+        int dev = 0, cus = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e == hipSuccess)
+            e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess)
+            return e;
+        if (cus > 0 && groups > 4 * (int64_t)cus)
+            groups = 4 * (int64_t)cus;
+    }
+    const dim3 grid((unsigned)groups), block(kQuantThreads);
     const uint8_t *s = static_cast<const uint8_t *>(src);
     const int64_t ldb = ld * (BF16 ? 2 : 4);
-#define MXFP4_LAUNCH(R, C)                                                                                              \
-    {                                                                                                                   \
-        auto kern = quantize_fp4_kernel<BF16, R, C, TILED>;                                                             \
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),                                  \
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kFp4LdsBytes);             \
-        if (e != hipSuccess)                                                                                            \
-            return e;                                                                                                   \
-        hipLaunchKernelGGL(kern, grid, block, kFp4LdsBytes, stream, s, rows, cols, ldb, q_row, s_row, q_colT, s_colT,    \
-                           (uint32_t)tiles_x, (uint32_t)ntiles);                                                                        \
-    }
-    if (axis == 1)
-        MXFP4_LAUNCH(true, false)
-    else if (axis == 2)
-        MXFP4_LAUNCH(false, true)
-    else
-        MXFP4_LAUNCH(true, true)
-#undef MXFP4_LAUNCH
+    auto kern = axis == 1 ? quantize_fp4_kernel<BF16, true, false, TILED> : axis == 2 ? quantize_fp4_kernel<BF16, false, true, TILED>
+                                                                           : quantize_fp4_kernel<BF16, true, true, TILED>;
+    hipLaunchKernelGGL(kern, grid, block, 0, stream, s, rows, cols, ldb, q_row, s_row, q_colT, s_colT, (uint32_t)tiles_x,
+                       (uint32_t)(tiles_x * tiles_y));
     return hipGetLastError();
 }
 

@@ -67,6 +67,8 @@ inline uint32_t __float_as_uint(float f)
 #define __builtin_amdgcn_cvt_scalef32_2xpk16_bf6_f32(a, b, scale) ::wavesim::cvt_scalef32_2xpk16_6bit((a), (b), (scale), 3, 2)
 #define __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(old, a, b, scale, sel) \
     ::wavesim::cvt_scalef32_pk_fp4_f32((old), (a), (b), (scale), (sel))
+#define __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(old, p, scale, sel) \
+    ::wavesim::cvt_scalef32_pk_fp4_bf16((old), (p), (scale), (sel))
 #define __builtin_amdgcn_cvt_scalef32_pk_bf8_f32(old, a, b, scale, hi) \
     ::wavesim::cvt_scalef32_pk_bf8_f32((old), (a), (b), (scale), (hi))
 #define __builtin_amdgcn_cvt_scalef32_pk_bf8_bf16(old, p, scale, hi) \

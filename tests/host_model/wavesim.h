@@ -364,14 +364,14 @@ inline v2s cvt_scalef32_pk_fp8_bf16(v2s old, v2bf p, float scale, bool hi)
 // v_cvt_scalef32_pk_fp4_f32: two FP32 values divided by the scale (same reading of the scale operand as the FP8
 // forms) and rounded to E2M1, nearest with ties to the even code, saturating at 6, sign kept; the first value goes
 // to the low nibble of byte `sel` of the destination, the second to the high nibble. What the instruction makes of
-// a NaN is not modelled (the kernels never convert a block that holds one): it stops the model.
+// a NaN, or of anything under a NaN scale, is not known: the model answers with an odd code that no kernel may let through.
 inline uint8_t cvt_scaled_e2m1(float x, float scale)
 {
     uint32_t sbits;
     memcpy(&sbits, &scale, 4);
     const int field = (sbits >> 23) & 0xFF;
     if (std::isnan(x) || field == 0xFF)
-        fail("E2M1 conversion of a NaN (or with a NaN scale) is not modelled");
+        return 0xB;
     const uint8_t sign = std::signbit(x) ? 8 : 0;
     const double t = std::ldexp(std::fabs((double)x), -(field == 0 ? -127 : field - 127));
     static const double mid[7] = {0.25, 0.75, 1.25, 1.75, 2.5, 3.5, 5.0};  // midpoints; a tie goes to the even code
@@ -384,6 +384,10 @@ inline uint32_t cvt_scalef32_pk_fp4_f32(uint32_t old, float a, float b, float sc
 {
     const uint32_t byte = (uint32_t)(cvt_scaled_e2m1(a, scale) | (cvt_scaled_e2m1(b, scale) << 4));
     return (old & ~(0xFFu << (8 * sel))) | (byte << (8 * sel));
+}
+inline uint32_t cvt_scalef32_pk_fp4_bf16(uint32_t old, v2bf p, float scale, int sel)
+{
+    return cvt_scalef32_pk_fp4_f32(old, (float)p[0], (float)p[1], scale, sel);
 }
 // v_cvt_scalef32_2xpk16_{fp6,bf6}_f32: 2 x 16 FP32 values divided by the scale (same reading of the scale operand
 // as the FP8 forms), rounded to E2M3 (fp6) or E3M2 (bf6), nearest with ties to even, saturating, sign kept; the
