@@ -199,7 +199,7 @@ def mxfp8_quantize_mode_ex(src, axis, element=E4M3, rule=SCALE_ROUND_UP, q_row=N
                            s_colT=None, scale_layout=SCALES_ROWMAJOR, stream=None) -> None:
     """mxfp8_quantize_ex with the element format (E4M3 / E5M2) and the scale rule (SCALE_ROUND_UP /
     SCALE_OCP_V1) of the paper's ablations."""
-    if _fast is not None and _done(_fast.quantize(src, axis, element, rule, q_row, s_row, q_colT, s_colT, scale_layout, _stream(stream)), "mxfp8_quantize"):
+    if _fast is not None and _done(_fast.quantize(src, _AXIS.get(axis, axis), element, rule, q_row, s_row, q_colT, s_colT, scale_layout, _stream(stream)), "mxfp8_quantize"):
         return
     _need_cuda(src, q_row, s_row, q_colT, s_colT)
     if src.dim() != 2 or (src.numel() and src.stride(1) != 1):
@@ -226,7 +226,7 @@ def mxfp8_gemm(pass_, a_q, a_s, b_q, b_s, c, stream=None) -> None:
 def mxfp8_gemm_ex(pass_, a_q, a_s, b_q, b_s, c, scale_layout=SCALES_ROWMAJOR, max_workgroups=0, stream=None) -> None:
     """mxfp8_gemm with both scale operands stored in `scale_layout`, on at most `max_workgroups` compute
     units (0 = all)."""
-    if _fast is not None and _done(_fast.gemm(pass_, a_q, a_s, b_q, b_s, c, scale_layout, max_workgroups, _stream(stream)), "mxfp8_gemm"):
+    if _fast is not None and _done(_fast.gemm(_PASS.get(pass_, pass_), a_q, a_s, b_q, b_s, c, scale_layout, max_workgroups, _stream(stream)), "mxfp8_gemm"):
         return
     _need_cuda(a_q, a_s, b_q, b_s, c)
     M, K = a_q.shape
@@ -250,7 +250,7 @@ def mxfp8_gemm_ex(pass_, a_q, a_s, b_q, b_s, c, scale_layout=SCALES_ROWMAJOR, ma
 def mxfp8_gemm_mode_ex(pass_, a_q, a_s, a_element, b_q, b_s, b_element, c, scale_layout=SCALES_ROWMAJOR, max_workgroups=0,
                        stream=None) -> None:
     """mxfp8_gemm_ex with the element format (E4M3 / E5M2) of each operand chosen by the caller."""
-    if _fast is not None and _done(_fast.gemm_mode(pass_, a_q, a_s, a_element, b_q, b_s, b_element, c, scale_layout, max_workgroups, _stream(stream)), "mxfp8_gemm_mode_ex"):
+    if _fast is not None and _done(_fast.gemm_mode(_PASS.get(pass_, pass_), a_q, a_s, a_element, b_q, b_s, b_element, c, scale_layout, max_workgroups, _stream(stream)), "mxfp8_gemm_mode_ex"):
         return
     _need_cuda(a_q, a_s, b_q, b_s, c)
     M, K = a_q.shape
@@ -347,7 +347,7 @@ def mxfp8_gemm_quantize_ex(pass_, a_q, a_s, b_q, b_s, c, axis, cq_row=None, cs_r
                            scale_layout=SCALES_ROWMAJOR, max_workgroups=0, stream=None) -> None:
     """mxfp8_gemm_ex with bfloat16 c [M x N] plus the MXFP8 copies of c selected by `axis`:
     cq_row [M x N] / cs_row and cq_colT [N x M] / cs_colT."""
-    if _fast is not None and _done(_fast.gemm_quantize(pass_, a_q, a_s, b_q, b_s, c, axis, cq_row, cs_row, cq_colT, cs_colT, scale_layout, max_workgroups, _stream(stream)), "mxfp8_gemm_quantize_ex"):
+    if _fast is not None and _done(_fast.gemm_quantize(_PASS.get(pass_, pass_), a_q, a_s, b_q, b_s, c, _AXIS.get(axis, axis), cq_row, cs_row, cq_colT, cs_colT, scale_layout, max_workgroups, _stream(stream)), "mxfp8_gemm_quantize_ex"):
         return
     _need_cuda(a_q, a_s, b_q, b_s, c, cq_row, cs_row, cq_colT, cs_colT)
     M, K = a_q.shape
@@ -457,7 +457,7 @@ def mxfp8_fp4_quantize_ex(src, axis, q_row=None, s_row=None, q_colT=None, s_colT
                           scale_layout=SCALES_ROWMAJOR, stream=None) -> None:
     """src [rows x cols] float32/bfloat16 -> MXFP4 copies: q_row [rows x cols/2], q_colT [cols x rows/2] (two E2M1
     codes per byte), scales as for MXFP8."""
-    if _fast is not None and _done(_fast.fp4_quantize(src, axis, q_row, s_row, q_colT, s_colT, scale_layout, _stream(stream)), "mxfp8_fp4_quantize_ex"):
+    if _fast is not None and _done(_fast.fp4_quantize(src, _AXIS.get(axis, axis), q_row, s_row, q_colT, s_colT, scale_layout, _stream(stream)), "mxfp8_fp4_quantize_ex"):
         return
     _need_cuda(src, q_row, s_row, q_colT, s_colT)
     if src.dim() != 2 or (src.numel() and src.stride(1) != 1):
@@ -495,7 +495,7 @@ def mxfp8_fp4_dequantize_ex(q, s, dst, scale_layout=SCALES_ROWMAJOR, stream=None
 def mxfp8_fp4_gemm_ex(pass_, a_q, a_s, b_q, b_s, c, scale_layout=SCALES_ROWMAJOR, max_workgroups=0, stream=None) -> None:
     """c [M x N] (float32/bfloat16) = A . B^T for MXFP4 operands a_q [M x K/2], b_q [N x K/2] (packed E2M1 codes) with
     block scales [. x K/32] in `scale_layout`."""
-    if _fast is not None and _done(_fast.fp4_gemm(pass_, a_q, a_s, b_q, b_s, c, scale_layout, max_workgroups, _stream(stream)), "mxfp8_fp4_gemm_ex"):
+    if _fast is not None and _done(_fast.fp4_gemm(_PASS.get(pass_, pass_), a_q, a_s, b_q, b_s, c, scale_layout, max_workgroups, _stream(stream)), "mxfp8_fp4_gemm_ex"):
         return
     _need_cuda(a_q, a_s, b_q, b_s, c)
     M, Kh = a_q.shape
@@ -524,7 +524,7 @@ def mxfp8_fp6_quantize_ex(src, axis, element, q_row=None, s_row=None, q_colT=Non
                           scale_layout=SCALES_ROWMAJOR, stream=None) -> None:
     """src [rows x cols] float32/bfloat16 -> MXFP6 copies: q_row [rows x cols*3/4], q_colT [cols x rows*3/4] (32 six-bit
     codes per 24 bytes), scales as for MXFP8. element: E2M3 or E3M2."""
-    if _fast is not None and _done(_fast.fp6_quantize(src, axis, element, q_row, s_row, q_colT, s_colT, scale_layout, _stream(stream)), "mxfp8_fp6_quantize_ex"):
+    if _fast is not None and _done(_fast.fp6_quantize(src, _AXIS.get(axis, axis), element, q_row, s_row, q_colT, s_colT, scale_layout, _stream(stream)), "mxfp8_fp6_quantize_ex"):
         return
     _need_cuda(src, q_row, s_row, q_colT, s_colT)
     if src.dim() != 2 or (src.numel() and src.stride(1) != 1):
