@@ -1077,8 +1077,17 @@ static hipError_t launch_staged_cfg(const uint8_t *a_q, const uint8_t *a_s, cons
 // resident, their prologue and epilogue are paid in every round and a step is slower ([137 x 74069 x 4864], BF16 out, tiled:
 // 153.8 us as one-tile 256x256 workgroups, 138.4 as staged 64x128 tiles; [6144 x 6922 x 3456]: 211.6 us, 235.0 as staged
 // 128x128 tiles).
+// Tiles of 96 columns fill a round that 128 leave a quarter empty, in one run with operands that rotate (tiled scales, BF16 out):
+//                          128x128 128x96 128x64 64x96 64x64
+//   [1000 x 2880 x 5760]      30.1   27.9   35.8  37.0  32.6   (34.4, 32.6, 41.5, 43.3, 38.2 with row-major scales)
+//   [1000 x 2880 x 2048]      11.2   11.7   14.2  14.2  12.3
+//   [200 x 5120 x 8192]       36.6   31.7   27.7  23.5  25.5
+//   [200 x 5120 x 2048]       10.2   10.7    8.0   8.0   8.6
+//   [850 x 1200 x 4096]       16.5   15.1   12.3  11.4  14.2   (FP32 out)
+// A ring of eight K steps for the small tiles was no faster (64x64: 8.7 -> 9.0 us at [128 x 4096 x 4096], 18.1 -> 19.3 at [512 x
+// 4096 x 4096]): workgroups side by side on a unit hide more than a deeper ring does, and LDS is what they need.
 // units: compute units that the launch may use; all_units: it may use all of them; route(bm, bn): how 256-row tiles would run.
-enum class Tile { k256, k256_tail, k256x192, k128, k128x64, k64x128, k64, k32x64, k32 };
+enum class Tile { k256, k256_tail, k256x192, k128, k128x96, k128x64, k64x128, k64x96, k64, k32x64, k32 };
 enum class Route { resident, one_tile, none };
 struct TileOption {
     Tile tile;
@@ -1090,8 +1099,8 @@ struct TileOption {
 template <class F> static TileOption choose_tile(int64_t M, int64_t N, int64_t KT, int64_t units, bool all_units, F route)
 {
     static const TileOption options[] = {{Tile::k256, 256, 256, 5.0, 0, 1.45, 1.45}, {Tile::k256x192, 256, 192, 5.0, 0, 1.2, 1.2},
-                                         {Tile::k128, 128, 128, 4.0, 0, 0.43, 0.55}, {Tile::k128x64, 128, 64, 3.5, 0, 0.32, 0.36},
-                                         {Tile::k64x128, 64, 128, 3.5, 0, 0.32, 0.36}, {Tile::k64, 64, 64, 2.6, 0, 0.215, 0.215},
+                                         {Tile::k128, 128, 128, 4.0, 0, 0.43, 0.55}, {Tile::k128x96, 128, 96, 4.6, 0, 0.40, 0.48}, {Tile::k128x64, 128, 64, 3.5, 0, 0.32, 0.36},
+                                         {Tile::k64x128, 64, 128, 3.5, 0, 0.32, 0.36}, {Tile::k64x96, 64, 96, 3.2, 0, 0.27, 0.30}, {Tile::k64, 64, 64, 2.6, 0, 0.215, 0.215},
                                          {Tile::k32x64, 32, 64, 2.4, 0, 0.19, 0.19}, {Tile::k32, 32, 32, 2.2, 0, 0.165, 0.165}};
     static const TileOption one_tile[] = {{Tile::k256, 256, 256, 3.0, 1.5, 1.5, 1.5}, {Tile::k256x192, 256, 192, 2.0, 2.5, 1.22, 1.22}};
     TileOption best = options[0];
@@ -1104,6 +1113,8 @@ template <class F> static TileOption choose_tile(int64_t M, int64_t N, int64_t K
             if (r == Route::one_tile)
                 o = one_tile[o.tile == Tile::k256 ? 0 : 1];
         }
+        if (o.bn == 96 && KT < 16)
+            continue;  // no faster anywhere ([1000 x 2880 x 1664] 10.6 us against 10.0, [200 x 5120 x 1664] 7.4 and 7.4)
         const double step = o.tiles(M, N) > units && all_units ? o.step_us_full : o.step_us;
         const double us = o.around_us + (double)o.rounds(M, N, units) * (o.round_us + (double)KT * step);
         if (us < least) {
@@ -1115,7 +1126,7 @@ template <class F> static TileOption choose_tile(int64_t M, int64_t N, int64_t K
     // its K loop). A round of few 256x256 tiles takes 0.7 us per step, a round of 128x128 tiles 0.43. In us, whole | with the rest as
     // quarters: [4352 x 4096 x 4096] (272 tiles, BF16 out, tiled) 73.4 | 70.2, [5376 x 3328 x 8192] 133.5 | 123.5, FP32 out, row-major
     // 156.9 | 138.2; but [4352 x 4096 x 1024] 27.2 | 29.0, [7828 x 4400 x 4480] (46 more than two rounds) 129.1 | 134.3.
-    const TileOption &whole = options[0], &quarter = options[2];
+    const TileOption &whole = options[0], &quarter = options[2];  // 256x256, 128x128
     const int64_t n = whole.tiles(M, N), rest = n % units;
     if (all_units && n > units && rest > 0 && 8 * rest <= units && KT >= 28 && route(256, 256) == Route::resident &&
         whole.around_us + (double)(n / units * KT) * whole.step_us + 8.0 + (double)KT * quarter.step_us < least) {
@@ -1183,6 +1194,8 @@ static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const u
     return launch_staged_cfg<StagedCfg<BM, BN, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream)
     switch (tile) {
     case Tile::k128: MXFP8_STAGED(128, 128);
+    case Tile::k128x96: MXFP8_STAGED(128, 96);
+    case Tile::k64x96: MXFP8_STAGED(64, 96);
     case Tile::k128x64: MXFP8_STAGED(128, 64);
     case Tile::k64x128: MXFP8_STAGED(64, 128);
     case Tile::k64: MXFP8_STAGED(64, 64);

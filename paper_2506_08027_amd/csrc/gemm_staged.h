@@ -35,7 +35,9 @@ struct StagedCfg {
     }
     static_assert(BM % 16 == 0 && BN % 16 == 0 && WM % 16 == 0 && WN % 16 == 0, "whole matrix instructions");
     static_assert((BM + BN) % (8 * WAVES) == 0 && BM % 8 == 0, "8-row requests spread evenly over the wavefronts");
-    static_assert((BM % 64 == 0 || 64 % BM == 0) && (BN % 64 == 0 || 64 % BN == 0), "a tile's scale rows start inside one 64-row group");
+    // a tile's scale rows are those of AG (BG) groups of 64: its first row is a multiple of 64 or it ends within the group's 64
+    // (96 rows from a multiple of 32 on reach into two groups wherever they start)
+    static_assert((BM % 64 == 0 || 64 % BM == 0) && (BN % 64 == 0 || 64 % BN == 0 || BN == 96), "a tile's scale rows lie in AG and BG groups");
     static_assert((STAGES - 1) * L < 64, "wait counts");
     static_assert(SPG * QUADS > STAGES + 2 * SPG - 3, "a quad buffer is refilled only after its last step was read");
 };
