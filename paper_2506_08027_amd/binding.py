@@ -109,9 +109,10 @@ def _bind_fastcall(lib):
         from . import _fastcall
     except ImportError:
         return None
-    _fastcall.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
+    table = {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
         "mxfp8_quantize_mode_ex", "mxfp8_gemm_ex", "mxfp8_gemm_mode_ex", "mxfp8_dequantize_mode_ex", "mxfp8_gemm_bf16",
-        "mxfp8_gemm_quantize_ex", "mxfp8_fp4_quantize_ex", "mxfp8_fp4_gemm_ex", "mxfp8_fp6_quantize_ex")})
+        "mxfp8_gemm_quantize_ex", "mxfp8_fp4_quantize_ex", "mxfp8_fp4_gemm_ex", "mxfp8_fp6_quantize_ex")}
+    _fastcall.bind(dict(table, passes=_PASS, axes=_AXIS, stream=_stream))
     return _fastcall
 
 
@@ -199,7 +200,7 @@ def mxfp8_quantize_mode_ex(src, axis, element=E4M3, rule=SCALE_ROUND_UP, q_row=N
                            s_colT=None, scale_layout=SCALES_ROWMAJOR, stream=None) -> None:
     """mxfp8_quantize_ex with the element format (E4M3 / E5M2) and the scale rule (SCALE_ROUND_UP /
     SCALE_OCP_V1) of the paper's ablations."""
-    if _fast is not None and _done(_fast.quantize(src, _AXIS.get(axis, axis), element, rule, q_row, s_row, q_colT, s_colT, scale_layout, _stream(stream)), "mxfp8_quantize"):
+    if _fast is not None and _done(_fast.quantize(src, axis, element, rule, q_row, s_row, q_colT, s_colT, scale_layout, stream), "mxfp8_quantize"):
         return
     _need_cuda(src, q_row, s_row, q_colT, s_colT)
     if src.dim() != 2 or (src.numel() and src.stride(1) != 1):
@@ -226,7 +227,7 @@ def mxfp8_gemm(pass_, a_q, a_s, b_q, b_s, c, stream=None) -> None:
 def mxfp8_gemm_ex(pass_, a_q, a_s, b_q, b_s, c, scale_layout=SCALES_ROWMAJOR, max_workgroups=0, stream=None) -> None:
     """mxfp8_gemm with both scale operands stored in `scale_layout`, on at most `max_workgroups` compute
     units (0 = all)."""
-    if _fast is not None and _done(_fast.gemm(_PASS.get(pass_, pass_), a_q, a_s, b_q, b_s, c, scale_layout, max_workgroups, _stream(stream)), "mxfp8_gemm"):
+    if _fast is not None and _done(_fast.gemm(pass_, a_q, a_s, b_q, b_s, c, scale_layout, max_workgroups, stream), "mxfp8_gemm"):
         return
     _need_cuda(a_q, a_s, b_q, b_s, c)
     M, K = a_q.shape
@@ -250,7 +251,7 @@ def mxfp8_gemm_ex(pass_, a_q, a_s, b_q, b_s, c, scale_layout=SCALES_ROWMAJOR, ma
 def mxfp8_gemm_mode_ex(pass_, a_q, a_s, a_element, b_q, b_s, b_element, c, scale_layout=SCALES_ROWMAJOR, max_workgroups=0,
                        stream=None) -> None:
     """mxfp8_gemm_ex with the element format (E4M3 / E5M2) of each operand chosen by the caller."""
-    if _fast is not None and _done(_fast.gemm_mode(_PASS.get(pass_, pass_), a_q, a_s, a_element, b_q, b_s, b_element, c, scale_layout, max_workgroups, _stream(stream)), "mxfp8_gemm_mode_ex"):
+    if _fast is not None and _done(_fast.gemm_mode(pass_, a_q, a_s, a_element, b_q, b_s, b_element, c, scale_layout, max_workgroups, stream), "mxfp8_gemm_mode_ex"):
         return
     _need_cuda(a_q, a_s, b_q, b_s, c)
     M, K = a_q.shape
@@ -327,7 +328,7 @@ def mxfp8_gemm_grouped_ex(pass_, a_q, a_s, b_q, b_s, group_ends, c, scale_layout
 def mxfp8_gemm_bf16(a, b, c, max_workgroups=0, stream=None) -> None:
     """c [M x N] (float32 or bfloat16) = a [M x K] * b[N x K]^T for dense bfloat16 operands: the GEMM of the
     simulated MX path."""
-    if _fast is not None and _done(_fast.gemm_bf16(a, b, c, max_workgroups, _stream(stream)), "mxfp8_gemm_bf16"):
+    if _fast is not None and _done(_fast.gemm_bf16(a, b, c, max_workgroups, stream), "mxfp8_gemm_bf16"):
         return
     _need_cuda(a, b, c)
     M, K = a.shape
@@ -347,7 +348,7 @@ def mxfp8_gemm_quantize_ex(pass_, a_q, a_s, b_q, b_s, c, axis, cq_row=None, cs_r
                            scale_layout=SCALES_ROWMAJOR, max_workgroups=0, stream=None) -> None:
     """mxfp8_gemm_ex with bfloat16 c [M x N] plus the MXFP8 copies of c selected by `axis`:
     cq_row [M x N] / cs_row and cq_colT [N x M] / cs_colT."""
-    if _fast is not None and _done(_fast.gemm_quantize(_PASS.get(pass_, pass_), a_q, a_s, b_q, b_s, c, _AXIS.get(axis, axis), cq_row, cs_row, cq_colT, cs_colT, scale_layout, max_workgroups, _stream(stream)), "mxfp8_gemm_quantize_ex"):
+    if _fast is not None and _done(_fast.gemm_quantize(pass_, a_q, a_s, b_q, b_s, c, axis, cq_row, cs_row, cq_colT, cs_colT, scale_layout, max_workgroups, stream), "mxfp8_gemm_quantize_ex"):
         return
     _need_cuda(a_q, a_s, b_q, b_s, c, cq_row, cs_row, cq_colT, cs_colT)
     M, K = a_q.shape
@@ -380,7 +381,7 @@ def mxfp8_dequantize(q, s, dst, stream=None) -> None:
 
 def mxfp8_dequantize_ex(q, s, dst, scale_layout=SCALES_ROWMAJOR, stream=None, element=E4M3) -> None:
     """mxfp8_dequantize with s stored in `scale_layout` and the element bytes in `element` format."""
-    if _fast is not None and _done(_fast.dequantize(q, s, element, dst, scale_layout, _stream(stream)), "mxfp8_dequantize"):
+    if _fast is not None and _done(_fast.dequantize(q, s, element, dst, scale_layout, stream), "mxfp8_dequantize"):
         return
     _need_cuda(q, s, dst)
     rows, cols = q.shape
@@ -457,7 +458,7 @@ def mxfp8_fp4_quantize_ex(src, axis, q_row=None, s_row=None, q_colT=None, s_colT
                           scale_layout=SCALES_ROWMAJOR, stream=None) -> None:
     """src [rows x cols] float32/bfloat16 -> MXFP4 copies: q_row [rows x cols/2], q_colT [cols x rows/2] (two E2M1
     codes per byte), scales as for MXFP8."""
-    if _fast is not None and _done(_fast.fp4_quantize(src, _AXIS.get(axis, axis), q_row, s_row, q_colT, s_colT, scale_layout, _stream(stream)), "mxfp8_fp4_quantize_ex"):
+    if _fast is not None and _done(_fast.fp4_quantize(src, axis, q_row, s_row, q_colT, s_colT, scale_layout, stream), "mxfp8_fp4_quantize_ex"):
         return
     _need_cuda(src, q_row, s_row, q_colT, s_colT)
     if src.dim() != 2 or (src.numel() and src.stride(1) != 1):
@@ -495,7 +496,7 @@ def mxfp8_fp4_dequantize_ex(q, s, dst, scale_layout=SCALES_ROWMAJOR, stream=None
 def mxfp8_fp4_gemm_ex(pass_, a_q, a_s, b_q, b_s, c, scale_layout=SCALES_ROWMAJOR, max_workgroups=0, stream=None) -> None:
     """c [M x N] (float32/bfloat16) = A . B^T for MXFP4 operands a_q [M x K/2], b_q [N x K/2] (packed E2M1 codes) with
     block scales [. x K/32] in `scale_layout`."""
-    if _fast is not None and _done(_fast.fp4_gemm(_PASS.get(pass_, pass_), a_q, a_s, b_q, b_s, c, scale_layout, max_workgroups, _stream(stream)), "mxfp8_fp4_gemm_ex"):
+    if _fast is not None and _done(_fast.fp4_gemm(pass_, a_q, a_s, b_q, b_s, c, scale_layout, max_workgroups, stream), "mxfp8_fp4_gemm_ex"):
         return
     _need_cuda(a_q, a_s, b_q, b_s, c)
     M, Kh = a_q.shape
@@ -524,7 +525,7 @@ def mxfp8_fp6_quantize_ex(src, axis, element, q_row=None, s_row=None, q_colT=Non
                           scale_layout=SCALES_ROWMAJOR, stream=None) -> None:
     """src [rows x cols] float32/bfloat16 -> MXFP6 copies: q_row [rows x cols*3/4], q_colT [cols x rows*3/4] (32 six-bit
     codes per 24 bytes), scales as for MXFP8. element: E2M3 or E3M2."""
-    if _fast is not None and _done(_fast.fp6_quantize(src, _AXIS.get(axis, axis), element, q_row, s_row, q_colT, s_colT, scale_layout, _stream(stream)), "mxfp8_fp6_quantize_ex"):
+    if _fast is not None and _done(_fast.fp6_quantize(src, axis, element, q_row, s_row, q_colT, s_colT, scale_layout, stream), "mxfp8_fp6_quantize_ex"):
         return
     _need_cuda(src, q_row, s_row, q_colT, s_colT)
     if src.dim() != 2 or (src.numel() and src.stride(1) != 1):

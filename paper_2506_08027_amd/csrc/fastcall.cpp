@@ -1,6 +1,7 @@
 // The calls of the binding for the ordinary case: every argument as the entry points want it, tensors in GPU memory. Anything
 // else (NOT_HANDLED) goes through binding.py, which checks again, converts what can be converted and names what cannot be.
 //
+// The last argument of each is the binding's `stream`, passes and axes are what its caller gave.
 // Why: a small kernel lasts 3 .. 5 us and HIP takes 2.9 us to launch it, while the checks in Python (a dozen attributes of five
 // or six tensors) took 2.3 .. 3 us and the call through ctypes 0.6 us. Here the checks cost 0.1 us and the call 0.2 us.
 // The library's entry points are handed over by address, so that this module and the binding call the same library.
@@ -20,6 +21,8 @@ const char *const kNames[ENTRY_POINTS] = {"mxfp8_quantize_mode_ex", "mxfp8_gemm_
                                           "mxfp8_gemm_bf16", "mxfp8_gemm_quantize_ex", "mxfp8_fp4_quantize_ex",
                                           "mxfp8_fp4_gemm_ex", "mxfp8_fp6_quantize_ex"};
 void *entry[ENTRY_POINTS];
+// The binding's own: names and constants of passes and axes (dicts), and the function that turns its `stream` argument into a handle.
+PyObject *passes, *axes, *stream_handle;
 
 // Arguments of a call, taken one after the other; `ok` turns false at the first one that is not what it has to be.
 struct Args {
@@ -48,19 +51,14 @@ struct Args {
             ok = false;
         return v;
     }
-    void *stream()
+    // what `table` has for the next argument
+    int64_t code(PyObject *table, int64_t lo, int64_t hi)
     {
-        PyObject *o = next();
-        if (!PyLong_CheckExact(o)) {
+        PyObject *v = table ? PyDict_GetItem(table, next()) : nullptr;  // (nullptr also for what cannot be looked up)
+        const long long c = v && PyLong_CheckExact(v) ? PyLong_AsLong(v) : lo - 1;
+        if (c < lo || c > hi)
             ok = false;
-            return nullptr;
-        }
-        void *p = PyLong_AsVoidPtr(o);
-        if (PyErr_Occurred()) {
-            PyErr_Clear();
-            ok = false;
-        }
-        return p;
+        return c;
     }
     // a tensor in GPU memory; nullptr for None where that is allowed
     const at::Tensor *tensor(bool none_allowed = false)
@@ -104,17 +102,28 @@ Values values(const at::Tensor &t, int64_t rows, int64_t cols)
     return {ok, type == at::kBFloat16 ? 1 : 0, ok && rows > 1 ? t.stride(0) : cols};
 }
 
-template <class F, class... A> PyObject *call(int which, A... args)
+PyObject *not_handled() { return PyLong_FromLong(NOT_HANDLED); }
+// The binding asks for the stream after its checks, so that a wrong tensor is reported as one on a machine without a GPU too.
+template <class F, class... A> PyObject *call(int which, PyObject *stream, A... args)
 {
-    if (!entry[which])
-        return PyLong_FromLong(NOT_HANDLED);
+    if (!entry[which] || !stream_handle)
+        return not_handled();
+    PyObject *h = PyObject_CallFunctionObjArgs(stream_handle, stream, nullptr);
+    if (!h)
+        return nullptr;
+    void *handle = PyLong_CheckExact(h) ? PyLong_AsVoidPtr(h) : nullptr;
+    const bool ok = PyLong_CheckExact(h) && !PyErr_Occurred();
+    Py_DECREF(h);
+    if (!ok) {
+        PyErr_Clear();
+        return not_handled();
+    }
     int rc;
     Py_BEGIN_ALLOW_THREADS
-    rc = reinterpret_cast<F>(entry[which])(args...);
+    rc = reinterpret_cast<F>(entry[which])(args..., handle);
     Py_END_ALLOW_THREADS
     return PyLong_FromLong(rc);
 }
-PyObject *not_handled() { return PyLong_FromLong(NOT_HANDLED); }
 
 // The copies of a quantizer: q_row, s_row, q_colT, s_colT; `num` / `den` bytes per element, element bytes checked where `exact`
 struct Copies {
@@ -136,14 +145,14 @@ template <int WHICH> PyObject *quantize(PyObject *, PyObject *const *args, Py_ss
 {
     Args a{args, n};
     const at::Tensor *src = a.tensor();
-    const int64_t axis = a.number(1, 3), element = WHICH == FP4_QUANTIZE ? 0 : a.number(0, 1), rule = WHICH == QUANTIZE ? a.number(0, 1) : 0;
+    const int64_t axis = a.code(axes, 1, 3), element = WHICH == FP4_QUANTIZE ? 0 : a.number(0, 1), rule = WHICH == QUANTIZE ? a.number(0, 1) : 0;
     Copies c;
     c.q_row = a.tensor(true);
     c.s_row = a.tensor(true);
     c.q_colT = a.tensor(true);
     c.s_colT = a.tensor(true);
     const int64_t layout = a.number(0, 1);
-    void *stream = a.stream();
+    PyObject *stream = a.next();
     if (!a.ok || a.left || src->dim() != 2)
         return not_handled();
     const int64_t rows = src->size(0), cols = src->size(1);
@@ -152,28 +161,28 @@ template <int WHICH> PyObject *quantize(PyObject *, PyObject *const *args, Py_ss
         return not_handled();
     if constexpr (WHICH == QUANTIZE)
         return call<int (*)(P, int, I, I, I, int, int, int, Q, Q, Q, Q, int, void *)>(
-            WHICH, ptr(src), v.dtype, rows, cols, v.ld, (int)axis, (int)element, (int)rule, ptr(c.q_row), ptr(c.s_row), ptr(c.q_colT),
-            ptr(c.s_colT), (int)layout, stream);
+            WHICH, stream, ptr(src), v.dtype, rows, cols, v.ld, (int)axis, (int)element, (int)rule, ptr(c.q_row), ptr(c.s_row), ptr(c.q_colT),
+            ptr(c.s_colT), (int)layout);
     else if constexpr (WHICH == FP6_QUANTIZE)
-        return call<int (*)(P, int, I, I, I, int, int, Q, Q, Q, Q, int, void *)>(WHICH, ptr(src), v.dtype, rows, cols, v.ld, (int)axis, (int)element,
-                                                                                ptr(c.q_row), ptr(c.s_row), ptr(c.q_colT), ptr(c.s_colT), (int)layout, stream);
+        return call<int (*)(P, int, I, I, I, int, int, Q, Q, Q, Q, int, void *)>(WHICH, stream, ptr(src), v.dtype, rows, cols, v.ld, (int)axis, (int)element,
+                                                                                ptr(c.q_row), ptr(c.s_row), ptr(c.q_colT), ptr(c.s_colT), (int)layout);
     else
-        return call<int (*)(P, int, I, I, I, int, Q, Q, Q, Q, int, void *)>(WHICH, ptr(src), v.dtype, rows, cols, v.ld, (int)axis, ptr(c.q_row),
-                                                                           ptr(c.s_row), ptr(c.q_colT), ptr(c.s_colT), (int)layout, stream);
+        return call<int (*)(P, int, I, I, I, int, Q, Q, Q, Q, int, void *)>(WHICH, stream, ptr(src), v.dtype, rows, cols, v.ld, (int)axis, ptr(c.q_row),
+                                                                           ptr(c.s_row), ptr(c.q_colT), ptr(c.s_colT), (int)layout);
 }
 
 // pass, a_q, a_s, [a_element,] b_q, b_s, [b_element,] c, layout, max_workgroups, stream
 template <int WHICH> PyObject *gemm(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     Args a{args, n};
-    const int64_t pass = a.number(0, 2);
+    const int64_t pass = a.code(passes, 0, 2);
     const at::Tensor *a_q = a.tensor(), *a_s = a.tensor();
     const int64_t a_element = WHICH == GEMM_MODE ? a.number(0, 1) : 0;
     const at::Tensor *b_q = a.tensor(), *b_s = a.tensor();
     const int64_t b_element = WHICH == GEMM_MODE ? a.number(0, 1) : 0;
     const at::Tensor *c = a.tensor();
     const int64_t layout = a.number(0, 1), bound = a.number(0, INT32_MAX);
-    void *stream = a.stream();
+    PyObject *stream = a.next();
     if (!a.ok || a.left || a_q->dim() != 2 || b_q->dim() != 2)
         return not_handled();
     const int64_t M = a_q->size(0), N = b_q->size(0), bytes = a_q->size(1), K = WHICH == FP4_GEMM ? 2 * bytes : bytes;
@@ -182,11 +191,11 @@ template <int WHICH> PyObject *gemm(PyObject *, PyObject *const *args, Py_ssize_
         return not_handled();
     if constexpr (WHICH == GEMM_MODE)
         return call<int (*)(int, P, P, int, P, P, int, I, I, I, void *, int, I, int, int32_t, void *)>(
-            WHICH, (int)pass, ptr(a_q), ptr(a_s), (int)a_element, ptr(b_q), ptr(b_s), (int)b_element, M, N, K, (void *)ptr(c), v.dtype, v.ld,
-            (int)layout, (int32_t)bound, stream);
+            WHICH, stream, (int)pass, ptr(a_q), ptr(a_s), (int)a_element, ptr(b_q), ptr(b_s), (int)b_element, M, N, K, (void *)ptr(c), v.dtype, v.ld,
+            (int)layout, (int32_t)bound);
     else
         return call<int (*)(int, P, P, P, P, I, I, I, void *, int, I, int, int32_t, void *)>(
-            WHICH, (int)pass, ptr(a_q), ptr(a_s), ptr(b_q), ptr(b_s), M, N, K, (void *)ptr(c), v.dtype, v.ld, (int)layout, (int32_t)bound, stream);
+            WHICH, stream, (int)pass, ptr(a_q), ptr(a_s), ptr(b_q), ptr(b_s), M, N, K, (void *)ptr(c), v.dtype, v.ld, (int)layout, (int32_t)bound);
 }
 
 // q, s, element, dst, layout, stream
@@ -197,15 +206,15 @@ PyObject *dequantize(PyObject *, PyObject *const *args, Py_ssize_t n)
     const int64_t element = a.number(0, 1);
     const at::Tensor *dst = a.tensor();
     const int64_t layout = a.number(0, 1);
-    void *stream = a.stream();
+    PyObject *stream = a.next();
     if (!a.ok || a.left || q->dim() != 2)
         return not_handled();
     const int64_t rows = q->size(0), cols = q->size(1);
     const Values v = values(*dst, rows, cols);
     if (!v.ok || !dense_bytes(*q) || !scales(*s, rows, cols, layout))
         return not_handled();
-    return call<int (*)(P, P, I, I, int, void *, int, I, int, void *)>(DEQUANTIZE, ptr(q), ptr(s), rows, cols, (int)element, (void *)ptr(dst), v.dtype, v.ld,
-                                                                      (int)layout, stream);
+    return call<int (*)(P, P, I, I, int, void *, int, I, int, void *)>(DEQUANTIZE, stream, ptr(q), ptr(s), rows, cols, (int)element, (void *)ptr(dst), v.dtype, v.ld,
+                                                                      (int)layout);
 }
 
 // a, b, c, max_workgroups, stream
@@ -214,30 +223,30 @@ PyObject *gemm_bf16(PyObject *, PyObject *const *args, Py_ssize_t n)
     Args a{args, n};
     const at::Tensor *x = a.tensor(), *y = a.tensor(), *c = a.tensor();
     const int64_t bound = a.number(0, INT32_MAX);
-    void *stream = a.stream();
+    PyObject *stream = a.next();
     if (!a.ok || a.left || x->dim() != 2 || y->dim() != 2)
         return not_handled();
     const int64_t M = x->size(0), N = y->size(0), K = x->size(1);
     const Values v = values(*c, M, N);
     if (!v.ok || y->size(1) != K || x->scalar_type() != at::kBFloat16 || y->scalar_type() != at::kBFloat16 || !x->is_contiguous() || !y->is_contiguous())
         return not_handled();
-    return call<int (*)(P, P, I, I, I, void *, int, I, int32_t, void *)>(GEMM_BF16, ptr(x), ptr(y), M, N, K, (void *)ptr(c), v.dtype, v.ld, (int32_t)bound, stream);
+    return call<int (*)(P, P, I, I, I, void *, int, I, int32_t, void *)>(GEMM_BF16, stream, ptr(x), ptr(y), M, N, K, (void *)ptr(c), v.dtype, v.ld, (int32_t)bound);
 }
 
 // pass, a_q, a_s, b_q, b_s, c, axis, cq_row, cs_row, cq_colT, cs_colT, layout, max_workgroups, stream
 PyObject *gemm_quantize(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     Args a{args, n};
-    const int64_t pass = a.number(0, 2);
+    const int64_t pass = a.code(passes, 0, 2);
     const at::Tensor *a_q = a.tensor(), *a_s = a.tensor(), *b_q = a.tensor(), *b_s = a.tensor(), *c = a.tensor();
-    const int64_t axis = a.number(1, 3);
+    const int64_t axis = a.code(axes, 1, 3);
     Copies q;
     q.q_row = a.tensor(true);
     q.s_row = a.tensor(true);
     q.q_colT = a.tensor(true);
     q.s_colT = a.tensor(true);
     const int64_t layout = a.number(0, 1), bound = a.number(0, INT32_MAX);
-    void *stream = a.stream();
+    PyObject *stream = a.next();
     if (!a.ok || a.left || a_q->dim() != 2 || b_q->dim() != 2)
         return not_handled();
     const int64_t M = a_q->size(0), N = b_q->size(0), K = a_q->size(1);
@@ -246,16 +255,30 @@ PyObject *gemm_quantize(PyObject *, PyObject *const *args, Py_ssize_t n)
         !copies(a, q, M, N, axis, layout, 1, 1) || ((axis & kRowwise) && !dense_matrix(*q.q_row, M, N)) || ((axis & kColwise) && !dense_matrix(*q.q_colT, N, M)))
         return not_handled();
     return call<int (*)(int, P, P, P, P, I, I, I, void *, I, int, Q, Q, Q, Q, int, int32_t, void *)>(
-        GEMM_QUANTIZE, (int)pass, ptr(a_q), ptr(a_s), ptr(b_q), ptr(b_s), M, N, K, (void *)ptr(c), v.ld, (int)axis, ptr(q.q_row), ptr(q.s_row),
-        ptr(q.q_colT), ptr(q.s_colT), (int)layout, (int32_t)bound, stream);
+        GEMM_QUANTIZE, stream, (int)pass, ptr(a_q), ptr(a_s), ptr(b_q), ptr(b_s), M, N, K, (void *)ptr(c), v.ld, (int)axis, ptr(q.q_row), ptr(q.s_row),
+        ptr(q.q_colT), ptr(q.s_colT), (int)layout, (int32_t)bound);
 }
 
-// {name: address} of the entry points
+// {name: address} of the entry points, and the binding's "passes", "axes" and "stream"
 PyObject *bind(PyObject *, PyObject *table)
 {
     if (!PyDict_Check(table)) {
         PyErr_SetString(PyExc_TypeError, "bind() takes a dict of addresses");
         return nullptr;
+    }
+    const struct {
+        const char *name;
+        PyObject **to;
+        bool dict;
+    } own[] = {{"passes", &passes, true}, {"axes", &axes, true}, {"stream", &stream_handle, false}};
+    for (const auto &o : own) {
+        PyObject *v = PyDict_GetItemString(table, o.name);
+        if (v && (o.dict ? !PyDict_Check(v) : !PyCallable_Check(v))) {
+            PyErr_Format(PyExc_TypeError, "bind(): bad \"%s\"", o.name);
+            return nullptr;
+        }
+        Py_XINCREF(v);
+        Py_XSETREF(*o.to, v);
     }
     for (int i = 0; i < ENTRY_POINTS; ++i) {
         PyObject *v = PyDict_GetItemString(table, kNames[i]);
