@@ -910,6 +910,14 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
         cur_tile = next_tile;
     }
     MXFP8_WAIT_VMCNT(0);  // the redundant prefetches of the last steps must land before LDS is released
+    if constexpr (GROUPED && Cfg::BM == 256 && Cfg::BN == 256) {
+        using Quarter = StagedCfg<128, 128>;
+        static_assert(Quarter::lds_bytes(TILED) <= Cfg::LDS_BYTES_PERSISTENT && Quarter::THREADS == Cfg::THREADS, "quarters on the same workgroup");
+        if (tail.first(ntiles) < ntiles) {
+            __syncthreads();  // the quarters' requests go where fragments and staged rows were read
+            staged_tiles<Quarter, OUT_BF16, TILED, kTailGrouped>(lds, a_q, a_s, b_q, b_s, M, N, K, c, ldc_bytes, tiles_m, tiles_n, true, tail, groups);
+        }
+    }
 }
 
 // Compute units of the current device.
@@ -1022,8 +1030,7 @@ static hipError_t launch_any(const uint8_t *a_q, const uint8_t *a_s, const uint8
 // TAIL: of the 256x256 tiles that the resident kernel left, `tail_tiles` quarters at most
 template <class Cfg, bool OUT_BF16, bool TILED, int TAIL = kNoTail>
 static hipError_t launch_staged_t(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s, int M, int N, int K,
-                                  void *c, int64_t ldc, int max_workgroups, hipStream_t stream, GemmTail tail = {0, 0}, int tail_tiles = 0,
-                                  const GemmGroups &groups = {nullptr, 0, 0, 0})
+                                  void *c, int64_t ldc, int max_workgroups, hipStream_t stream, GemmTail tail = {0, 0}, int tail_tiles = 0)
 {
     constexpr int BM = TAIL == kNoTail ? Cfg::BM : 256, BN = TAIL == kNoTail ? Cfg::BN : 256;
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
@@ -1039,21 +1046,21 @@ static hipError_t launch_staged_t(const uint8_t *a_q, const uint8_t *a_s, const 
             return e;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Cfg::THREADS), lds, stream, a_q, a_s, b_q, b_s, M, N, K,
-                       static_cast<uint8_t *>(c), ldc_bytes, tiles_m, tiles_n, vec_store, tail, groups);
+                       static_cast<uint8_t *>(c), ldc_bytes, tiles_m, tiles_n, vec_store, tail);
     return hipGetLastError();
 }
 
 template <class Cfg, int TAIL = kNoTail>
 static hipError_t launch_staged_cfg(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s, int M, int N, int K,
                                     void *c, bool c_bf16, bool tiled, int64_t ldc, int max_workgroups, hipStream_t stream,
-                                    GemmTail tail = {0, 0}, int tail_tiles = 0, const GemmGroups &groups = {nullptr, 0, 0, 0})
+                                    GemmTail tail = {0, 0}, int tail_tiles = 0)
 {
     if constexpr (Cfg::SCALED)
         if (tiled)
-            return c_bf16 ? launch_staged_t<Cfg, true, true, TAIL>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream, tail, tail_tiles, groups)
-                          : launch_staged_t<Cfg, false, true, TAIL>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream, tail, tail_tiles, groups);
-    return c_bf16 ? launch_staged_t<Cfg, true, false, TAIL>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream, tail, tail_tiles, groups)
-                  : launch_staged_t<Cfg, false, false, TAIL>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream, tail, tail_tiles, groups);
+            return c_bf16 ? launch_staged_t<Cfg, true, true, TAIL>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream, tail, tail_tiles)
+                          : launch_staged_t<Cfg, false, true, TAIL>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream, tail, tail_tiles);
+    return c_bf16 ? launch_staged_t<Cfg, true, false, TAIL>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream, tail, tail_tiles)
+                  : launch_staged_t<Cfg, false, false, TAIL>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, max_workgroups, stream, tail, tail_tiles);
 }
 
 // Which tile: an estimate of the time, what a launch costs around its K loop plus (rounds of tiles over the compute units)
@@ -1243,9 +1250,11 @@ static hipError_t launch_grouped_cfg(const uint8_t *a_q, const uint8_t *a_s, con
     hipError_t e = persistent_grid((int)(most_tiles < 0x7FFFFFFF ? most_tiles : 0x7FFFFFFF), max_workgroups, grid);
     if (e != hipSuccess)
         return e;
-    // Where there can be more tiles than units, few tiles of an unfilled last round are computed as quarters, like those of a plain
-    // product (choose_tile), which has other tiles to choose from. Only the device knows how many there are: with none to
-    // compute the second launch costs 3 us.
+    // Where there are more tiles than units, few tiles of an unfilled last round are computed as quarters, like those of a plain
+    // product (choose_tile), which has other tiles to choose from. Only the device knows how many there are, so the same workgroups
+    // go on with them. In us, whole | as quarters in a launch of their own | this way: [8192 x 2048 x 5632] in 8 experts, 272 tiles,
+    // 134.8 | 104.6 | 100.6; [8192 x 2048 x 2048], 288 tiles, 59.3 | 49.7 | 46.9; and where there is no such rest [4096 x 4096 x
+    // 2048], 304 tiles, 57.4 | 59.3 | 57.6, [8192 x 2048 x 2048], 256 tiles, 38.0 | 39.3 | 37.6 (BF16 out, both scale layouts).
     GemmTail tail = {0, 0};
     if (Cfg::BM == 256 && max_workgroups == 0 && most_tiles > grid && K >= 16 * BK)
         tail = {grid, K >= 28 * BK ? grid / 4 : grid / 8};
@@ -1257,12 +1266,7 @@ static hipError_t launch_grouped_cfg(const uint8_t *a_q, const uint8_t *a_s, con
     uint8_t *none = nullptr;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Cfg::THREADS), Cfg::LDS_BYTES_PERSISTENT, stream, a_q, a_s, b_q, b_s, M, N, K,
                        static_cast<uint8_t *>(c), ldc_bytes, 0, tiles_n, none, none, none, none, groups, tail);
-    e = hipGetLastError();
-    if constexpr (Cfg::BM == 256 && Cfg::BN == 256)
-        if (e == hipSuccess && tail.units > 0)
-            return launch_staged_t<StagedCfg<128, 128>, OUT_BF16, TILED, kTailGrouped>(a_q, a_s, b_q, b_s, M, N, K, c, ldc, 0, stream, tail,
-                                                                                        4 * tail.most, groups);
-    return e;
+    return hipGetLastError();
 }
 
 // Weight-gradient form of the grouped product: resident workgroups where 256x256 tiles go resident (see gemm_persistent_kernel,

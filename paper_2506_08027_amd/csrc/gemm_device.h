@@ -46,11 +46,11 @@ struct GemmGroups {
     int64_t b_group_bytes, bs_group_bytes;
 };
 
-// Where the tiles of a problem do not fill the last round over the units, the rest of them (at most `most`) is left to a second
-// launch that computes them as quarters (gemm_staged_kernel). units = 0: no such split.
+// Where the tiles of a problem do not fill the last round over the units, the rest of them (at most `most`) is computed as quarters
+// (staged_tiles), by a second launch or at the end of the first. units = 0: no such split.
 struct GemmTail {
     int units, most;
-    // how many of n tiles the first launch computes
+    // how many of n tiles are computed whole
     __host__ __device__ int first(int n) const
     {
         const int rest = units > 0 ? n % units : 0;

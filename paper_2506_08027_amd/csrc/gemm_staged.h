@@ -66,18 +66,17 @@ template <int N, int L> __device__ __forceinline__ void wait_tail(int newer)
 // [1000 x 2880 x 5760], 128x128 tiles: 32.3 us with one dword per row and step, 25.2 this way, 22.3 with tiled scales.
 //
 // TAIL: the tiles are the quarters of the 256x256 tiles that the resident kernel left (GemmTail; tiles_m and tiles_n count those
-// tiles), of a plain product or (kTailGrouped) of the row-grouped one, whose number only the device knows; quarters that lie
-// outside the problem or behind the expert's last row are nothing to do. 256-row tiles one of which per unit more than fits
-// leave most units idle for a round: [8192 x 2048 x 5632] in 7 experts, under 300 tiles on 256 units, 128.9 -> 102.7 us;
-// plain [4352 x 4096 x 4096], 272 tiles, 74.1 -> 69.2 us (BF16 out, tiled scales), 88.0 -> 78.5 (FP32 out, row-major).
+// tiles), of a plain product, in a launch of their own, or (kTailGrouped) of the row-grouped one, whose number only the device
+// knows, at the end of the resident kernel; quarters that lie outside the problem or behind the expert's last row are nothing to
+// do. 256-row tiles one of which per unit more than fits leave most units idle for a round: plain [4352 x 4096 x 4096], 272 tiles,
+// 74.1 -> 69.2 us (BF16 out, tiled scales), 88.0 -> 78.5 (FP32 out, row-major); the grouped product beside its launch.
 enum { kNoTail, kTailPlain, kTailGrouped };
-template <class Cfg, bool OUT_BF16, bool TILED, int TAIL = kNoTail>
-__global__ __launch_bounds__(Cfg::THREADS) void gemm_staged_kernel(
-    const uint8_t *__restrict__ a_q, const uint8_t *__restrict__ a_s, const uint8_t *__restrict__ b_q_all, const uint8_t *__restrict__ b_s_all,
-    int M_all, int N, int K, uint8_t *__restrict__ c, int64_t ldc_bytes, int tiles_m, int tiles_n, bool vec_store, GemmTail tail, GemmGroups groups)
+template <class Cfg, bool OUT_BF16, bool TILED, int TAIL>
+__device__ __forceinline__ void staged_tiles(
+    uint8_t *lds, const uint8_t *__restrict__ a_q, const uint8_t *__restrict__ a_s, const uint8_t *__restrict__ b_q_all, const uint8_t *__restrict__ b_s_all,
+    int M_all, int N, int K, uint8_t *__restrict__ c, int64_t ldc_bytes, int tiles_m, int tiles_n, bool vec_store, GemmTail tail, const GemmGroups &groups)
 {
     static_assert(TAIL == kNoTail || (Cfg::BM == 128 && Cfg::BN == 128), "quarters of 256x256 tiles");
-    MXFP8_DYNAMIC_LDS(lds);
     constexpr int TM = Cfg::TM, TN = Cfg::TN, S = Cfg::STAGES, SDW = Cfg::SDW;
     constexpr int L = Cfg::L, SPG = Cfg::SPG;
     constexpr int STAGE = Cfg::DATA_BYTES + (TILED ? Cfg::STAGE_SCALE_BYTES : 0);
@@ -89,7 +88,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_staged_kernel(
     const int nkb = K / Cfg::SBLK, KT = K / BK;
     const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
     const int whole_tiles = TAIL == kTailGrouped ? grouped_tiles<256>(groups, M_all, tiles_n) : tiles_m * tiles_n;
-    const int done = TAIL == kNoTail ? 0 : tail.first(whole_tiles);  // whole tiles computed by the first launch
+    const int done = TAIL == kNoTail ? 0 : tail.first(whole_tiles);  // tiles computed whole, before
     const int ntiles = TAIL == kNoTail ? whole_tiles : 4 * (whole_tiles - done);
 
     // fragment addresses inside a stage (see gemm.hip for the swizzle)
@@ -365,6 +364,15 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_staged_kernel(
         if (tile + (int)gridDim.x < ntiles)
             __syncthreads();  // the next tile's requests go where the rows were staged
     }
+}
+
+template <class Cfg, bool OUT_BF16, bool TILED, int TAIL = kNoTail>
+__global__ __launch_bounds__(Cfg::THREADS) void gemm_staged_kernel(
+    const uint8_t *__restrict__ a_q, const uint8_t *__restrict__ a_s, const uint8_t *__restrict__ b_q, const uint8_t *__restrict__ b_s,
+    int M, int N, int K, uint8_t *__restrict__ c, int64_t ldc_bytes, int tiles_m, int tiles_n, bool vec_store, GemmTail tail)
+{
+    MXFP8_DYNAMIC_LDS(lds);
+    staged_tiles<Cfg, OUT_BF16, TILED, TAIL>(lds, a_q, a_s, b_q, b_s, M, N, K, c, ldc_bytes, tiles_m, tiles_n, vec_store, tail, GemmGroups{nullptr, 0, 0, 0});
 }
 
 }  // namespace mxfp8

@@ -19,7 +19,8 @@
 //              (BF16 product <prefix>.c plus the MXFP8 copies of it: .q_row .s_row .q_colT .s_colT)
 // "tiled" selects MXFP8_SCALES_TILED for every scale buffer of the call (sizes from mxfp8_scale_bytes);
 // "wg=<n>" is the max_workgroups argument of gemm / gemmq (default 0 = one per compute unit).
-// Each call prints "status <code> blocks <ids of the simulated workgroups...>".
+// Each call prints "status <code> blocks <ids of the simulated workgroups of the last launch...>" and "launches
+// <workgroups>:<LDS bytes> ..."; WAVESIM_ONLY=<n> simulates the n-th launch of a call (from 0 on) alone.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -144,6 +145,9 @@ void report(int status)
     if (status == 0)
         for (unsigned b : wavesim::g.simulated)
             printf(" %u", b);
+    printf("\nlaunches");
+    for (const auto &l : wavesim::g.call_launches)
+        printf(" %u:%zu", l.first, l.second);
     printf("\n");
     fflush(stdout);
 }
@@ -165,6 +169,7 @@ int main(int argc, char **argv)
             continue;
         wavesim::clear_buffers();
         wavesim::g.simulated.clear();
+        wavesim::g.call_launches.clear();
         if (op == "quantize") {
             std::string dt, src, prefix;
             long rows, cols, ld;

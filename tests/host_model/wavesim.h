@@ -26,6 +26,7 @@
 #include <cstring>
 #include <deque>
 #include <functional>
+#include <utility>
 #include <vector>
 
 #if defined(__has_feature)
@@ -112,6 +113,7 @@ struct Machine {
     std::vector<Buffer> buffers;
     std::vector<unsigned> simulated;  // block ids of the last launch that were run
     size_t launch_lds = 0;            // dynamic LDS bytes of the last launch
+    std::vector<std::pair<unsigned, size_t>> call_launches;  // workgroups and dynamic LDS bytes of the launches of this call
     uint64_t launches = 0;
 #ifdef WAVESIM_ASAN
     const void *main_bottom = nullptr;
@@ -776,6 +778,11 @@ inline void launch(dim3 grid, dim3 block, size_t shmem, const std::function<void
     g.launch_lds = shmem;
     g.simulated.clear();
     ++g.launches;
+    g.call_launches.push_back({grid.x, shmem});
+    if (const char *only = getenv("WAVESIM_ONLY"); only && (size_t)atoi(only) + 1 != g.call_launches.size()) {
+        g.body = nullptr;
+        return;  // the call's launches but this one (from 0 on) are left out
+    }
     // all workgroups, or max_blocks of them spread evenly over the grid (first and last included)
     const unsigned n = grid.x;
     const unsigned take = g.max_blocks < 0 || (unsigned long)g.max_blocks >= n ? n : (unsigned)g.max_blocks;
