@@ -450,8 +450,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
     constexpr int s_dword = TILED ? 256 : 4;     // ... and from one scale dword of a K step to its next one
     const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
 
-    // operand pointers of a tile at K step 0 (wavefront-uniform). What only one form needs is no member of the others: members
-    // that nobody sets keep a copied tile in scratch memory, which costs a launch 1 us.
+    // operand pointers of a tile at K step 0 (wavefront-uniform). What only the K-grouped form needs is no member of the others.
     struct Nothing {};
     struct Range {
         int steps;   // K steps of the tile's expert
@@ -464,7 +463,6 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
         int row_lo, col_lo;  // rows and columns of the tile before these are another tile's (not stored)
         int rows;  // GROUPED: rows of the tile that belong to its expert (stored)
         int lim;   // GROUPED: last row of the tile, counted from m0, that may be read from A
-        int steps;   // KGROUPED: K steps of its expert
     };
     // Scale requests of the 64 operand rows from `first` on: base and this lane's offset. Tiled scales keep 64 rows
     // together, but a tile that was moved back may begin between two such groups.
