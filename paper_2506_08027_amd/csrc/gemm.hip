@@ -367,6 +367,22 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_kernel(
 #ifndef MXFP8_GEMM_SCHED
 #define MXFP8_GEMM_SCHED 242  // B requests behind every 2nd MFMA, a gap of 2, A requests behind every 4th
 #endif
+struct KExpert {
+    int steps, first, expert;  // K steps, the first of them, whose they are
+};
+constexpr int kMostKExperts = 128;  // that the K-grouped form sorts
+// Who computes which tile of the K-grouped form: rounds over the workgroups, every other one backwards; the first `busy` workgroups
+// have no tile in rounds 1 .. skipped.
+struct KShares {
+    int busy, skipped;
+    // number of the tile that workgroup b computes as its `index`th (from 0 on; growing with it)
+    __device__ __forceinline__ int tile(int b, int index) const
+    {
+        const int round = index > 0 && b < busy ? index + skipped : index;
+        const int out = round > 0 && round <= skipped ? busy : 0, width = (int)gridDim.x - out, place = b - out;
+        return round * (int)gridDim.x - min(max(round - 1, 0), skipped) * busy + (round & 1 ? width - 1 - place : place);
+    }
+};
 // GROUPED (Appendix A.4, mixture-of-experts layers): the rows of A are tokens sorted by expert, rows
 // [group_ends[e-1], group_ends[e]) belong to expert e, whose B operand starts b_group_bytes (scales:
 // bs_group_bytes) after the previous expert's. group_ends lives in DEVICE memory (routing happens on the
@@ -377,10 +393,16 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_kernel(
 // the tile. Ends are clamped to [previous end, M], so bad ends cannot send a load out of A.
 // RAGGED: M or N is no multiple of the tile (a kernel of its own, so that whole tiles carry no masks: 1 % of their time).
 // KGROUPED (weight gradient of a mixture-of-experts layer, see the kernel above): the tiles of all experts that have whole K
-// steps, one expert after the other, each with a K range of its own; down to one step, so that the A requests, two steps
-// ahead, can reach into the tile after the next one. Experts without a step get zeros, rows spread over the workgroups. What
-// bounds it: the FP32 output (8 experts x [5632 x 2048] from 8192 tokens: 369 MB, 60 us of writing) and 9 steps of 1.5 us per
-// tile, one after the other where all units store at the same time. One tile per workgroup 163 us, this way 137 us.
+// steps, each with a K range of its own; down to one step, so that the A requests, two steps ahead, can reach into the tile after
+// the next one. Experts without a step get zeros, rows spread over the workgroups. What bounds it: the FP32 output (8 experts x
+// [5632 x 2048] from 8192 tokens: 369 MB, 60 us of writing) and 9 steps of 1.5 us per tile, one after the other where all units
+// store at the same time.
+// A workgroup's share is fixed before it starts, so it is shared out by what tiles take: the experts with the most steps first, every
+// other round over the workgroups backwards, and where one expert has most of the steps its workgroups sit out some rounds
+// (KShares). One after the other in the experts' order, loads that repeat with the rounds gave all long tiles to the same
+// workgroups. In us, one tile per workgroup | in the experts' order | this way (tiled scales, FP32 out): [2048 x 2048], experts of
+// 49,5,5,5,49,5,5,5 steps 95.6 | 133.7 | 90.8; [4096 x 2048], 64 experts of 31 and 1 by turns 1490 | 2157 | 1260; [2816 x 2048], 64
+// experts, one with half of 512 steps 790 | 866 | 721, and eight each 670 | 615 | 559; [5632 x 2048], eight of eight steps 159 | 137 | 134.
 template <class Cfg, bool OUT_BF16, bool TILED, bool SPREAD, int FUSE_Q = 0, int SCHED = MXFP8_GEMM_SCHED, bool GROUPED = false, bool RAGGED = false,
           bool KGROUPED = false>
 __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
@@ -410,12 +432,19 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
     int ntiles = tiles_m * tiles_n;
     if constexpr (GROUPED)
         ntiles = grouped_tiles<Cfg::BM>(groups, M, tiles_n);
+    [[maybe_unused]] KExpert *const by_steps = reinterpret_cast<KExpert *>(lds + Cfg::LDS_BYTES_PERSISTENT);
+    [[maybe_unused]] KShares shares = {0, 0};
     if constexpr (KGROUPED) {
+        static_assert(Cfg::THREADS >= kMostKExperts, "a work-item per expert");
         const int per_expert = ntiles, pieces = N * (OUT_BF16 ? 2 : 4) / 16;
+        KExpert own = {0, 0, tid};  // expert `tid`
+        int all = 0;                // steps of all experts
         ntiles = 0;
         for (int e = 0, prev = 0; e < groups.count; ++e) {
-            const int end = min(max(groups.ends[e], prev), K);
-            if (end / BK > prev / BK) {
+            const int end = min(max(groups.ends[e], prev), K), steps = end / BK - prev / BK;
+            if (e == tid)
+                own = {steps, prev / BK, e};
+            if (steps > 0) {
                 ntiles += per_expert;
             } else {
                 for (int m = blockIdx.x; m < M; m += gridDim.x)
@@ -423,11 +452,56 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
                         *reinterpret_cast<uint4 *>(c + ((int64_t)e * M + m) * ldc_bytes + (int64_t)i * 16) = make_uint4(0, 0, 0, 0);
             }
             prev = end;
+            all = end / BK;
+        }
+        // the experts in the order of their steps, most of them first
+        int32_t *const all_steps = reinterpret_cast<int32_t *>(lds);
+        if (tid < groups.count)
+            all_steps[tid] = own.steps;
+        __syncthreads();
+        if (tid < groups.count) {
+            int rank = 0;
+            for (int e = 0; e < groups.count; ++e)
+                rank += all_steps[e] > own.steps || (all_steps[e] == own.steps && e < tid);
+            by_steps[rank] = own;
+        }
+        __syncthreads();
+        // Where one expert has far more steps than the others have on average, the workgroups with its tiles sit out the rounds
+        // in which the others catch up, if that makes the longest share shorter (in steps; an estimate).
+        constexpr int STORE = OUT_BF16 ? 4 : 8;  // what a tile takes besides its K loop
+        const int active = ntiles / per_expert, most = active > 0 ? __builtin_amdgcn_readfirstlane(by_steps[0].steps) : 0;
+        const int others = all - most + STORE * (active - 1);
+        const int rounds = active > 1 && per_expert < (int)gridDim.x ? (most + STORE) * (active - 1) / others - 1 : 0;
+        if (rounds > 0) {
+            int longest[2] = {0, 0};  // without and with
+            for (int b = tid; b < (int)gridDim.x; b += Cfg::THREADS)
+                for (int with = 0; with < 2; ++with) {
+                    const KShares how = {with ? per_expert : 0, with ? rounds : 0};
+                    int share = 0;
+                    for (int i = 0, u; (u = how.tile(b, i)) < ntiles; ++i)
+                        share += by_steps[u / per_expert].steps + STORE;
+                    longest[with] = max(longest[with], share);
+                }
+            for (int with = 0; with < 2; ++with) {
+                for (int mask = 32; mask > 0; mask >>= 1)
+                    longest[with] = max(longest[with], __shfl_xor(longest[with], mask, 64));
+                all_steps[2 * wave + with] = longest[with];
+            }
+            __syncthreads();
+            for (int w = 0; w < Cfg::WAVES; ++w)
+                for (int with = 0; with < 2; ++with)
+                    longest[with] = max(longest[with], all_steps[2 * w + with]);
+            if (__builtin_amdgcn_readfirstlane(longest[1]) < __builtin_amdgcn_readfirstlane(longest[0]))
+                shares = {per_expert, rounds};
+            __syncthreads();
         }
     }
     const int stride = gridDim.x;
     // >= 1 when the host knows the number of tiles (the grid has at most that many workgroups)
-    const int my_tiles = (tail.first(ntiles) - (int)blockIdx.x + stride - 1) / stride;
+    int my_tiles = (tail.first(ntiles) - (int)blockIdx.x + stride - 1) / stride;
+    if constexpr (KGROUPED)
+        for (my_tiles = 0; shares.tile((int)blockIdx.x, my_tiles) < ntiles;)
+            ++my_tiles;
     if ((GROUPED || KGROUPED) && my_tiles <= 0)
         return;  // the whole workgroup, before any barrier
 
@@ -498,20 +572,13 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
         } else {
             int u = (int)blockIdx.x + index * stride, count = ntiles;
             if constexpr (KGROUPED) {
+                u = shares.tile((int)blockIdx.x, index);
                 count = tiles_m * tiles_n;
-                int e = 0, prev = 0;
-                for (; e < groups.count; ++e) {  // u < ntiles = the tiles of all experts with steps: the scan ends inside
-                    const int end = min(max(groups.ends[e], prev), K);
-                    first_step = prev / BK;
-                    t.steps = end / BK - first_step;
-                    if (t.steps > 0) {
-                        if (u < count)
-                            break;
-                        u -= count;
-                    }
-                    prev = end;
-                }
-                t.c = c + (int64_t)e * M * ldc_bytes;
+                const int rank = u / count;
+                u -= rank * count;
+                t.steps = __builtin_amdgcn_readfirstlane(by_steps[rank].steps);
+                first_step = __builtin_amdgcn_readfirstlane(by_steps[rank].first);
+                t.c = c + (int64_t)__builtin_amdgcn_readfirstlane(by_steps[rank].expert) * M * ldc_bytes;
             }
             tile_of_block(u, count, tiles_m, tiles_n, tm, tn);
             // the last tile of a ragged row or column of tiles ends with the operand
@@ -1267,8 +1334,8 @@ static hipError_t launch_grouped_cfg(const uint8_t *a_q, const uint8_t *a_s, con
     return hipGetLastError();
 }
 
-// Weight-gradient form of the grouped product: resident workgroups where 256x256 tiles go resident (see gemm_persistent_kernel,
-// KGROUPED), else one workgroup per (expert, tile) (gemm_kernel, KGROUPED).
+// Weight-gradient form of the grouped product: resident workgroups where 256x256 tiles go resident and there are no more experts
+// than those sort (see gemm_persistent_kernel, KGROUPED), else one workgroup per (expert, tile) (gemm_kernel, KGROUPED).
 template <class Cfg, bool OUT_BF16, bool TILED>
 static hipError_t launch_kgrouped_cfg(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s,
                                       const GemmGroups &groups, int M, int N, int K, void *c, int64_t ldc, hipStream_t stream)
@@ -1280,21 +1347,21 @@ static hipError_t launch_kgrouped_cfg(const uint8_t *a_q, const uint8_t *a_s, co
     if (grid > 0x7FFFFFFF)
         return hipErrorInvalidConfiguration;
     if constexpr (Cfg::BM == 256) {
-        if (goes_resident(Cfg::BM, Cfg::BN, M, N, K, c, ldc_bytes, OUT_BF16 ? 2 : 4)) {
+        if (groups.count <= kMostKExperts && goes_resident(Cfg::BM, Cfg::BN, M, N, K, c, ldc_bytes, OUT_BF16 ? 2 : 4)) {
             const bool full = M % Cfg::BM == 0 && N % Cfg::BN == 0;
             int units = 0;
             hipError_t e = persistent_grid((int)grid, 0, units);
             if (e != hipSuccess)
                 return e;
-            constexpr int sched = sched_for<Cfg>();
+            constexpr int sched = sched_for<Cfg>(), lds = Cfg::LDS_BYTES_PERSISTENT + kMostKExperts * (int)sizeof(KExpert);
+            static_assert(lds <= 160 * 1024, "LDS of a unit");
             auto kern = full ? gemm_persistent_kernel<Cfg, OUT_BF16, TILED, true, 0, sched, false, false, true>
                              : gemm_persistent_kernel<Cfg, OUT_BF16, TILED, true, 0, sched, false, true, true>;
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    Cfg::LDS_BYTES_PERSISTENT);
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
             if (e != hipSuccess)
                 return e;
             uint8_t *none = nullptr;
-            hipLaunchKernelGGL(kern, dim3((unsigned)units), dim3(Cfg::THREADS), Cfg::LDS_BYTES_PERSISTENT, stream, a_q, a_s, b_q, b_s, M, N, K,
+            hipLaunchKernelGGL(kern, dim3((unsigned)units), dim3(Cfg::THREADS), lds, stream, a_q, a_s, b_q, b_s, M, N, K,
                                static_cast<uint8_t *>(c), ldc_bytes, tiles_m, tiles_n, none, none, none, none, groups, GemmTail{0, 0});
             return hipGetLastError();
         }
