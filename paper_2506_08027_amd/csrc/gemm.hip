@@ -996,6 +996,14 @@ static hipError_t compute_units(int &units)
     return e;
 }
 
+// The same, and whether a launch may use all of them: a bound that is no smaller than the device is none.
+static hipError_t compute_units(int max_workgroups, int &units, bool &all)
+{
+    const hipError_t e = compute_units(units);
+    all = max_workgroups == 0 || max_workgroups >= units;
+    return e;
+}
+
 // Number of workgroups of a persistent launch: one per compute unit of the current device, at most
 // `max_workgroups` when the caller gives a positive bound, never more than there are tiles.
 static hipError_t persistent_grid(int ntiles, int max_workgroups, int &grid)
@@ -1232,12 +1240,11 @@ static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const u
     int units = 0;
     bool two_buffers = K < 4 * BK && !many;  // 128x128 tiles on the resident or the one-tile kernel instead of the staged one
     if (K >= 4 * BK) {
-        int device_units = 0;
-        const hipError_t e = compute_units(device_units);
+        bool all_units = false;
+        const hipError_t e = compute_units(max_workgroups, units, all_units);
         if (e != hipSuccess)
             return e;
-        const bool all_units = max_workgroups == 0 || max_workgroups >= device_units;
-        units = all_units ? device_units : max_workgroups;
+        units = all_units ? units : max_workgroups;
         const TileOption o = choose_tile(M, N, KT, units, all_units, route);
         tile = o.tile;
         const int64_t tiles128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
@@ -1311,8 +1318,11 @@ static hipError_t launch_grouped_cfg(const uint8_t *a_q, const uint8_t *a_s, con
         return hipErrorInvalidConfiguration;
     const int tiles_n = N / Cfg::BN;
     const int64_t most_tiles = ((int64_t)(M + Cfg::BM - 1) / Cfg::BM + groups.count) * tiles_n;
-    int grid = 0;
-    hipError_t e = persistent_grid((int)(most_tiles < 0x7FFFFFFF ? most_tiles : 0x7FFFFFFF), max_workgroups, grid);
+    int units = 0, grid = 0;
+    bool all_units = false;
+    hipError_t e = compute_units(max_workgroups, units, all_units);
+    if (e == hipSuccess)
+        e = persistent_grid((int)(most_tiles < 0x7FFFFFFF ? most_tiles : 0x7FFFFFFF), max_workgroups, grid);
     if (e != hipSuccess)
         return e;
     // Where there are more tiles than units, few tiles of an unfilled last round are computed as quarters, like those of a plain
@@ -1321,7 +1331,7 @@ static hipError_t launch_grouped_cfg(const uint8_t *a_q, const uint8_t *a_s, con
     // 134.8 | 104.6 | 100.6; [8192 x 2048 x 2048], 288 tiles, 59.3 | 49.7 | 46.9; and where there is no such rest [4096 x 4096 x
     // 2048], 304 tiles, 57.4 | 59.3 | 57.6, [8192 x 2048 x 2048], 256 tiles, 38.0 | 39.3 | 37.6 (BF16 out, both scale layouts).
     GemmTail tail = {0, 0};
-    if (Cfg::BM == 256 && max_workgroups == 0 && most_tiles > grid && K >= 16 * BK)
+    if (Cfg::BM == 256 && all_units && most_tiles > grid && K >= 16 * BK)
         tail = {grid, K >= 28 * BK ? grid / 4 : grid / 8};
     auto kern = gemm_persistent_kernel<Cfg, OUT_BF16, TILED, spread_fits<Cfg>(), 0, MXFP8_GEMM_SCHED, true>;
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1504,11 +1514,12 @@ hipError_t launch_gemm_fused(const uint8_t *a_q, const uint8_t *a_s, const uint8
     const int m = (int)M, n = (int)N, k = (int)K, bm = big ? 256 : 128;
     if (M % bm || N % bm || K < 2 * BK || ldc * 2 * bm >= (int64_t(1) << 31))
         return hipErrorInvalidConfiguration;
-    if (max_workgroups == 0) {
-        int units = 0;
-        hipError_t e = compute_units(units);
-        if (e != hipSuccess)
-            return e;
+    int units = 0;
+    bool all_units = false;
+    hipError_t e = compute_units(max_workgroups, units, all_units);
+    if (e != hipSuccess)
+        return e;
+    if (all_units) {
         const bool filled = 4 * (M / 128) * (N / 128) >= 3 * (int64_t)units;
         if (big ? axis != 1 || tiles256 < units : K > (filled ? 8 : axis == 1 ? 4 : 0) * BK) {
             e = launch_gemm(a_q, a_s, b_q, b_s, M, N, K, c, true, tiled_scales, ldc, 0, stream);

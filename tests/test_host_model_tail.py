@@ -47,14 +47,16 @@ def test_plain_product(hostmodel, tmp_path, which, bf16, tiled):  # noqa: F811
         assert written.sum() >= 2 * 188 * 248 and not (written & ninth).any()
 
 
-@pytest.mark.parametrize("tiled,blocks", [(True, 1), pytest.param(False, 3, marks=pytest.mark.slow), pytest.param(True, 3, marks=pytest.mark.slow)])
-def test_grouped_product(hostmodel, tmp_path, tiled, blocks):  # noqa: F811
+@pytest.mark.parametrize("tiled,blocks,wg", [(True, 1, 0), pytest.param(False, 3, 0, marks=pytest.mark.slow),
+                                             pytest.param(True, 3, 128, marks=pytest.mark.slow)])
+def test_grouped_product(hostmodel, tmp_path, tiled, blocks, wg):  # noqa: F811
     """144 tiles of three experts on 128 units, in one launch: the workgroups go on with the quarters of the last sixteen, which
-    are four columns of the last expert's tiles; rows behind an expert's end are left alone. First, middle and last workgroup."""
+    are four columns of the last expert's tiles; rows behind an expert's end are left alone. First, middle and last workgroup. A
+    bound of as many workgroups as there are units is none."""
     M, N, K = 2048, 4096, 16 * 128
     ends = [448, 1024, 2048] if tiled else [400, 1003, 2001]
     ops = _operands(M, N, K, len(ends), seed=61)
-    line, out = _case(tmp_path, M, N, K, ops, ends, bf16=True, tiled=tiled)
+    line, out = _case(tmp_path, M, N, K, ops, ends, bf16=True, tiled=tiled, wg=wg)
     res, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_CUS=128, WAVESIM_BLOCKS=blocks)
     assert calls[0] == (0, [0, 63, 127][:blocks])
     assert _launches(res) == [(128, launch(("fp8", M, N, 16, True, 0, tiled, 0), "resident", 256, 256)[1])]
