@@ -28,6 +28,7 @@
 // dwords per row). With 4-bit elements the instruction takes dwords 0..3 only, lane (r, g) holds K =
 // 32g..32g+31 of row r and its own scale byte applies to them (pinned on the hardware by a test that runs
 // single instructions on registers taken from memory).
+#include <algorithm>
 #include <type_traits>
 #include "gemm_device.h"
 #include "gemm_staged.h"
@@ -1489,19 +1490,43 @@ template <class Cfg, bool TILED, class... Args> static hipError_t launch_fused_a
     }
 }
 
-// Which way (both measured on an MI355X, graph replays, tiled scales, us: in the epilogue | product, then quantizer):
-//   row copy    [8192 x 14336 x 4096] 399.6 | 402.4    [4096 x 14336 x 4096] 220.5 | 227.6   [4096 x 4096 x 4096] 61.0 | 62.5
-//               [2816 x 3072 x 2048]   34.8 |  30.2    [2816 x 3072 x 512]    22.3 |  20.0   [2048 x 2048 x 4096] 27.5 | 25.8
-//               [2048 x 2048 x 512]    10.7 |  13.3    [1024 x 1024 x 2048]   16.8 |  11.5   [256 x 512 x 4096]   20.4 | 12.4
-//   both copies [8192 x 14336 x 4096] 465.6 | 437.0    [4096 x 14336 x 4096] 262.8 | 240.0   [4096 x 4096 x 4096] 72.0 | 65.1
-//               [8192 x 8192 x 512]   119.7 |  91.1    [2816 x 3072 x 512]    30.7 |  22.4   [2048 x 2048 x 4096] 30.1 | 27.1
-//               [2048 x 2048 x 512]    13.4 |  14.9    [1024 x 1024 x 2048]   18.9 |  13.3   [512 x 1024 x 1024]  12.3 | 10.6
+// Which way (both measured on an MI355X in one run, graph replays over three sets of operands, tiled scales, us: one kernel |
+// product, then quantizer, by K steps):
+//   row copy     tiles256          2             8             32
+//   [2816 x 3072]     132    19.9 |  19.4   26.0 |  23.1   50.9 |  43.5
+//   [3328 x 4096]     208    20.0 |  21.2   26.9 |  28.0   53.7 |  55.5
+//   [4352 x 4096]     272    33.4 |  29.9   46.0 |  38.1  100.2 |  77.3
+//   [6144 x 4096]     384    33.7 |  33.0   47.4 |  46.4  105.4 | 103.2
+//   [8192 x 4096]     512    35.4 |  38.2   52.0 |  55.2  120.2 | 119.0
+//   [8192 x 14336]   1792   105.8 | 108.9  165.8 | 171.1  395.2 | 398.2   (row-major scales 105.6 | 116.4, 167.7 | 181.4, 429.2 | 433.7)
+//   both copies
+//   [2816 x 3072]     132    28.2 |  21.5   34.2 |  25.2   59.2 |  45.7
+//   [8192 x 4096]     512    60.0 |  44.3   77.7 |  60.3  141.3 | 123.4
+//   [8192 x 14336]   1792   190.5 | 134.5  246.9 | 201.1  454.1 | 430.9
+//   row copy     tiles128          2             4             8            12            16
+//   [512 x 1024]       32     7.3 |   9.1    8.2 |   7.7    9.9 |   8.2   11.9 |   9.2   14.2 |  10.2
+//   [1024 x 1536]      96     7.6 |  10.4    8.7 |  10.3   11.3 |  11.4   13.6 |  12.2   16.0 |  12.9
+//   [1280 x 2048]     160     8.1 |  11.3    9.2 |  12.8   12.0 |  13.3   14.0 |  14.5   16.4 |  15.7
+//   [2048 x 2048]     256     8.8 |  13.4   10.1 |  12.7   12.7 |  15.5   15.4 |  16.2   18.0 |  17.9   (both 11.3 | 14.3 .. 20.1 | 19.7)
+//   [1920 x 2432]     285    13.4 |  15.2   15.6 |  16.6   19.5 |  18.3   23.7 |  21.3   28.0 |  24.2   (both 17.2 | 16.7 .. 31.7 | 25.9)
+//   [2560 x 2560]     400    13.6 |  15.5   15.6 |  17.3   19.4 |  20.9   24.0 |  26.2   29.1 |  27.0   (both 17.8 | 17.6 .. 33.1 | 29.0)
 // An epilogue that converts keeps the matrix pipes of its unit idle, and it ties the product to 256x256 (128x128) tiles; the
-// quantizer reads C from the caches at the rate of the memory. So of large problems the column copy is left to the quantizer,
-// and the row copy, which the epilogue makes straight from the accumulators, where the tiles do not fill the units. Small
-// problems stay in one kernel where their tiles fill most of the units and few K steps are multiplied. Under a bound on
+// quantizer reads C from the caches at the rate of the memory. So of large problems the column copy is left to the quantizer, and
+// the row copy, which the epilogue makes straight from the accumulators, where the tiles fill three quarters of their rounds or
+// less. Small problems stay in one kernel while the second launch costs more than the smaller tiles of the plain product save:
+// the more tiles, the more K steps, up to a full round; in a second round all of it when both copies are wanted. Under a bound on
 // workgroups neither way wins ([4096 x 14336 x 4096], both copies, on 64: 723.9 | 719.2; [2816 x 3072 x 512], row copy, on
 // 32: 80.1 | 92.7; [2048 x 2048 x 1024], both, on 192: 19.8 | 23.8): one kernel.
+static bool fused_in_one_kernel(bool big, int axis, int64_t tiles, int64_t steps, int64_t units)
+{
+    const int64_t rounds = (tiles + units - 1) / units;
+    if (big)
+        return axis == 1 && 4 * tiles > 3 * rounds * units;
+    if (rounds == 1)
+        return steps <= std::min<int64_t>(12, std::max<int64_t>(3, 20 * tiles / units));
+    return axis != 3 && steps <= (2 * tiles < 3 * units ? 7 : 12);
+}
+
 hipError_t launch_gemm_fused(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s,
                              int64_t M, int64_t N, int64_t K, void *c, int64_t ldc, int axis, uint8_t *cq,
                              uint8_t *cs, uint8_t *cqT, uint8_t *csT, bool tiled_scales, int max_workgroups,
@@ -1520,8 +1545,7 @@ hipError_t launch_gemm_fused(const uint8_t *a_q, const uint8_t *a_s, const uint8
     if (e != hipSuccess)
         return e;
     if (all_units) {
-        const bool filled = 4 * (M / 128) * (N / 128) >= 3 * (int64_t)units;
-        if (big ? axis != 1 || tiles256 < units : K > (filled ? 8 : axis == 1 ? 4 : 0) * BK) {
+        if (!fused_in_one_kernel(big, (int)axis, big ? tiles256 : (M / 128) * (N / 128), K / BK, units)) {
             e = launch_gemm(a_q, a_s, b_q, b_s, M, N, K, c, true, tiled_scales, ldc, 0, stream);
             return e != hipSuccess ? e : launch_quantize(c, true, M, N, ldc, axis, cq, cs, cqT, csT, tiled_scales, 0, stream);
         }
