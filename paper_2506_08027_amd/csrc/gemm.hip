@@ -981,7 +981,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
         static_assert(Quarter::lds_bytes(TILED) <= Cfg::LDS_BYTES_PERSISTENT && Quarter::THREADS == Cfg::THREADS, "quarters on the same workgroup");
         if (tail.first(ntiles) < ntiles) {
             __syncthreads();  // the quarters' requests go where fragments and staged rows were read
-            staged_tiles<Quarter, OUT_BF16, TILED, kTailGrouped>(lds, a_q, a_s, b_q, b_s, M, N, K, c, ldc_bytes, tiles_m, tiles_n, true, tail, groups);
+            staged_grouped_rest<Quarter, OUT_BF16, TILED>(lds, a_q, a_s, b_q, b_s, M, N, K, c, ldc_bytes, tiles_n, tail, groups);
         }
     }
 }

@@ -47,7 +47,7 @@ struct GemmGroups {
 };
 
 // Where the tiles of a problem do not fill the last round over the units, the rest of them (at most `most`) is computed as quarters
-// (staged_tiles), by a second launch or at the end of the first. units = 0: no such split.
+// (gemm_staged.h), by a second launch or at the end of the first. units = 0: no such split.
 struct GemmTail {
     int units, most;
     // how many of n tiles are computed whole

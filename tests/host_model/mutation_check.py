@@ -80,7 +80,7 @@ RAGGED_MUTANTS = [
     ("ragged: first own row of a moved tile not stored", "(m >= cur_tile.row_lo &&", "(m > cur_tile.row_lo - (cur_tile.row_lo == 0) &&"),
 ]
 STEP_BARRIER = ("                MXFP8_BARRIER();\n                MXFP8_FENCE();\n            }\n            MXFP8_PIN();")
-STAGED_MUTANTS = [  # gemm_staged.h
+STAGED_MUTANTS = [  # gemm_staged_tiles.h
     ("staged: prologue wait one request too loose", "MXFP8_WAIT_VMCNT_AND_LDS((S - 1) * L);", "MXFP8_WAIT_VMCNT_AND_LDS((S - 1) * L + 1);"),
     ("staged: wait of a step one request too loose", "MXFP8_WAIT_VMCNT_AND_LDS((S - 2) * L);", "MXFP8_WAIT_VMCNT_AND_LDS((S - 2) * L + 1);"),
     ("staged: waits of the last steps one step too loose", "wait_tail<S - 2, L>(left - 1);", "wait_tail<S - 2, L>(left);"),
@@ -217,7 +217,7 @@ def main():
     todo += [(desc, "gemm.hip", old, new, "one-tile") for desc, old, new in MUTANTS]
     todo += [(desc, "gemm.hip", old, new, "resident") for desc, old, new in PERSISTENT_MUTANTS]
     todo += [(desc, "gemm.hip", old, new, "ragged") for desc, old, new in RAGGED_MUTANTS]
-    todo += [(desc, "gemm_staged.h", old, new, "staged") for desc, old, new in STAGED_MUTANTS]
+    todo += [(desc, "gemm_staged_tiles.h", old, new, "staged") for desc, old, new in STAGED_MUTANTS]
     todo += [("(unmutated converters: must pass)", "gemm.hip", "", "", None)] + [m + (None,) for m in QUANT_MUTANTS]
     for desc, name, old, new, kernel in todo:   # every pattern must still be in the source: a stale one would test nothing
         assert old == "" or old in open(os.path.join(csrc, name)).read(), desc
