@@ -1165,6 +1165,9 @@ static hipError_t launch_staged_cfg(const uint8_t *a_q, const uint8_t *a_s, cons
 //   [200 x 5120 x 8192]       36.6   31.7   27.7  23.5  25.5
 //   [200 x 5120 x 2048]       10.2   10.7    8.0   8.0   8.6
 //   [850 x 1200 x 4096]       16.5   15.1   12.3  11.4  14.2   (FP32 out)
+// Their own numbers are those that lose least against the other tiles over 780 products of 33 .. 2400 rows and 6 .. 72 steps, with
+// operands that rotate and that stay: chosen for 184 of them, 6 % faster there, one slower by more than 2 % both ways (5 %). Several
+// rounds of 64x96 tiles cost more than the smaller step shows ([768 x 6144 x 2048] as 768 of them 26.4 us, 20.8 as 64x64 tiles).
 // A ring of eight K steps for the small tiles was no faster (64x64: 8.7 -> 9.0 us at [128 x 4096 x 4096], 18.1 -> 19.3 at [512 x
 // 4096 x 4096]): workgroups side by side on a unit hide more than a deeper ring does, and LDS is what they need.
 // units: compute units that the launch may use; all_units: it may use all of them; route(bm, bn): how 256-row tiles would run.
@@ -1180,8 +1183,8 @@ struct TileOption {
 template <class F> static TileOption choose_tile(int64_t M, int64_t N, int64_t KT, int64_t units, bool all_units, F route)
 {
     static const TileOption options[] = {{Tile::k256, 256, 256, 5.0, 0, 1.45, 1.45}, {Tile::k256x192, 256, 192, 5.0, 0, 1.2, 1.2},
-                                         {Tile::k128, 128, 128, 4.0, 0, 0.43, 0.55}, {Tile::k128x96, 128, 96, 4.6, 0, 0.40, 0.48}, {Tile::k128x64, 128, 64, 3.5, 0, 0.32, 0.36},
-                                         {Tile::k64x128, 64, 128, 3.5, 0, 0.32, 0.36}, {Tile::k64x96, 64, 96, 3.2, 0, 0.27, 0.30}, {Tile::k64, 64, 64, 2.6, 0, 0.215, 0.215},
+                                         {Tile::k128, 128, 128, 4.0, 0, 0.43, 0.55}, {Tile::k128x96, 128, 96, 5.2, 0, 0.395, 0.50}, {Tile::k128x64, 128, 64, 3.5, 0, 0.32, 0.36},
+                                         {Tile::k64x128, 64, 128, 3.5, 0, 0.32, 0.36}, {Tile::k64x96, 64, 96, 3.5, 1.3, 0.265, 0.32}, {Tile::k64, 64, 64, 2.6, 0, 0.215, 0.215},
                                          {Tile::k32x64, 32, 64, 2.4, 0, 0.19, 0.19}, {Tile::k32, 32, 32, 2.2, 0, 0.165, 0.165}};
     static const TileOption one_tile[] = {{Tile::k256, 256, 256, 3.0, 1.5, 1.5, 1.5}, {Tile::k256x192, 256, 192, 2.0, 2.5, 1.22, 1.22}};
     TileOption best = options[0];
@@ -1194,8 +1197,6 @@ template <class F> static TileOption choose_tile(int64_t M, int64_t N, int64_t K
             if (r == Route::one_tile)
                 o = one_tile[o.tile == Tile::k256 ? 0 : 1];
         }
-        if (o.bn == 96 && KT < 16)
-            continue;  // no faster anywhere ([1000 x 2880 x 1664] 10.6 us against 10.0, [200 x 5120 x 1664] 7.4 and 7.4)
         const double step = o.tiles(M, N) > units && all_units ? o.step_us_full : o.step_us;
         const double us = o.around_us + (double)o.rounds(M, N, units) * (o.round_us + (double)KT * step);
         if (us < least) {
@@ -1204,13 +1205,14 @@ template <class F> static TileOption choose_tile(int64_t M, int64_t N, int64_t K
         }
     }
     // 256x256 tiles for the full rounds, a rest of few tiles as quarters on the staged kernel, in a launch of its own (8 us around
-    // its K loop). A round of few 256x256 tiles takes 0.7 us per step, a round of 128x128 tiles 0.43. In us, whole | with the rest as
+    // its K loop), where that is expected to save 4 % (with less, [12544 x 2688 x 6528] took 180 us for 172 as 256x192 tiles). A round
+    // of few 256x256 tiles takes 0.7 us per step, a round of 128x128 tiles 0.43. In us, whole | with the rest as
     // quarters: [4352 x 4096 x 4096] (272 tiles, BF16 out, tiled) 73.4 | 70.2, [5376 x 3328 x 8192] 133.5 | 123.5, FP32 out, row-major
     // 156.9 | 138.2; but [4352 x 4096 x 1024] 27.2 | 29.0, [7828 x 4400 x 4480] (46 more than two rounds) 129.1 | 134.3.
     const TileOption &whole = options[0], &quarter = options[2];  // 256x256, 128x128
     const int64_t n = whole.tiles(M, N), rest = n % units;
     if (all_units && n > units && rest > 0 && 8 * rest <= units && KT >= 28 && route(256, 256) == Route::resident &&
-        whole.around_us + (double)(n / units * KT) * whole.step_us + 8.0 + (double)KT * quarter.step_us < least) {
+        1.04 * (whole.around_us + (double)(n / units * KT) * whole.step_us + 8.0 + (double)KT * quarter.step_us) < least) {
         best = whole;
         best.tile = Tile::k256_tail;
     }

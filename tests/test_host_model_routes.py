@@ -70,6 +70,15 @@ FASTEST = [
     (("fp8", 200, 49152, 32, True, 0, True, 0), ("one-tile", 256, 192)),
     (("fp8", 6144, 6922, 27, True, 0, False, 0), ("one-tile", 256, 256)),
     (("fp8", 6144, 6928, 27, True, 0, False, 0), ("resident", 256, 256)),
+    # tiles of 96 columns in several rounds, or with few K steps, against the others; from 24 (35) steps on they are faster
+    (("fp8", 768, 6144, 16, True, 0, True, 0), ("staged", 64, 64)),
+    (("fp8", 850, 5120, 20, True, 0, False, 0), ("staged", 64, 64)),
+    (("fp8", 251, 5504, 20, True, 0, True, 0), ("staged", 128, 64)),
+    (("fp8", 265, 3360, 16, False, 0, False, 0), ("staged", 32, 64)),
+    (("fp8", 441, 2352, 20, True, 0, True, 0), ("staged", 128, 64)),
+    (("fp8", 200, 5120, 48, True, 0, True, 0), ("staged", 64, 96)),
+    # a rest of few tiles that quarters would hardly compute sooner
+    (("fp8", 12544, 2688, 51, True, 0, True, 0), ("resident", 256, 192)),
 ]
 
 
