@@ -51,3 +51,7 @@ ROUTES = [
     (("fp8", 6144, 6921, 5, True, 0, False, 0), ("one-tile", 256, 256)),
     (("fp8", 200, 49152, 8, True, 0, True, 0), ("one-tile", 256, 192)),
 ]
+
+# M, N, K bytes of an operand row: 256x256 tiles for full rounds on 256 units and a rest of 16 or 32 tiles as quarters, whatever the
+# operands and the output (17 x 16, 17 x 16 and 17 x 32 tiles; ragged ones, and one row in the last tiles)
+TAIL_SHAPES = [(4352, 4096, 3584), (4290, 4016, 3712), (4097, 8000, 8192)]

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import paper_2506_08027_amd as mx
+from route_cases import TAIL_SHAPES
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif("MXFP8_HOSTMODEL_LIB" in os.environ, reason="sizes for the hardware")]
 LAYOUTS = {"tiled": mx.SCALES_TILED, "rowmajor": mx.SCALES_ROWMAJOR}
@@ -16,7 +17,7 @@ def _tensor(rows, cols, seed):
     return torch.randn((rows, cols), generator=g, device="cuda").to(torch.bfloat16)
 
 
-@pytest.mark.parametrize("shape", [(4352, 4096, 3584), (4290, 4016, 3712), (4097, 8000, 3584)])  # 17x16, 17x16, 17x32 tiles on 256 units
+@pytest.mark.parametrize("shape", TAIL_SHAPES)
 @pytest.mark.parametrize("layout", ["tiled", "rowmajor"])
 @pytest.mark.parametrize("kind", ["bf16", "f32", "fp4", "simulated"])
 def test_plain_products(shape, layout, kind):

@@ -5,7 +5,7 @@ import subprocess
 
 import pytest
 
-from route_cases import K_STEP, ROUTES, launch
+from route_cases import K_STEP, ROUTES, TAIL_SHAPES, launch
 from test_host_model import hostmodel  # noqa: F401  (fixture)
 
 
@@ -88,3 +88,16 @@ def test_calls_take_the_kernel_named_for_them(hostmodel, tmp_path, table):
              for (fmt, M, N, steps, bf16, pad, tiled, bound), _ in table]
     for (call, want), got in zip(table, routes(hostmodel, tmp_path, calls)):
         assert got == launch(call, *want), call
+
+
+def test_rest_as_quarters(hostmodel, tmp_path):
+    """The last launch of the call is that of the quarters, of every format, output and layout."""
+    calls, want = [], []
+    for M, N, kbytes in TAIL_SHAPES:
+        rest = -(-M // 256) * -(-N // 256) % 256
+        for fmt, steps in (("fp8", kbytes // 128), ("fp4", kbytes // 128), ("bf16", kbytes // 64)):   # (BF16 of the same K: twice the bytes)
+            for bf16 in (True, False):
+                for tiled in (True, False):
+                    calls.append((fmt, M, N, steps, bf16, N, 0, tiled, 0))
+                    want.append((4 * rest, launch((fmt, M, N, steps, bf16, 0, tiled, 0), "staged", 128, 128)[1]))
+    assert routes(hostmodel, tmp_path, calls) == want
