@@ -34,7 +34,10 @@
  *     Element bytes are OCP E4M3 (bias 7, max 448, 0x7F/0xFF = NaN, no infinity).
  *   - Errors are reported by return code only, detected on the host before any launch; when a
  *     call fails no output byte has been written. MXFP8_ERR_HIP means the launch itself was
- *     rejected by the runtime (the HIP error stays readable through hipGetLastError()).
+ *     rejected by the runtime (the HIP error stays readable through hipGetLastError()). Some calls
+ *     enqueue two or three kernels (large products whose tiles overflow the compute units by a few,
+ *     mxfp8_gemm_quantize_ex): should the runtime take the first launch and reject a later one, the
+ *     call returns MXFP8_ERR_HIP and its outputs may be partly written.
  *   - The code objects are built for gfx950 only: on any other device the launch is rejected and
  *     the call returns MXFP8_ERR_HIP.
  */

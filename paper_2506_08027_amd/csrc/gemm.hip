@@ -1101,7 +1101,17 @@ static hipError_t launch_any(const uint8_t *a_q, const uint8_t *a_s, const uint8
 }
 
 // ---- staged kernel (gemm_staged.h): everything that 256x256 tiles cannot spread over the chip -------------------
-// TAIL: of the 256x256 tiles that the resident kernel left, `tail_tiles` quarters at most
+// What comes before a launch and can fail: a call of two launches has it done for both before the first one.
+template <class Cfg, bool OUT_BF16, bool TILED, int TAIL> static hipError_t prepare_staged()
+{
+    constexpr int lds = Cfg::lds_bytes(TILED);
+    if (lds <= 64 * 1024)  // what a launch may ask for by itself
+        return hipSuccess;
+    auto kern = gemm_staged_kernel<Cfg, OUT_BF16, TILED, TAIL>;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+}
+
+// TAIL: of the 256x256 tiles that the resident kernel left, `tail_tiles` quarters at most (prepared by the caller)
 template <class Cfg, bool OUT_BF16, bool TILED, int TAIL = kNoTail>
 static hipError_t launch_staged_t(const uint8_t *a_q, const uint8_t *a_s, const uint8_t *b_q, const uint8_t *b_s, int M, int N, int K,
                                   void *c, int64_t ldc, int max_workgroups, hipStream_t stream, GemmTail tail = {0, 0}, int tail_tiles = 0)
@@ -1112,16 +1122,23 @@ static hipError_t launch_staged_t(const uint8_t *a_q, const uint8_t *a_s, const 
     const bool vec_store = (reinterpret_cast<uintptr_t>(c) % 16 == 0) && (ldc_bytes % 16 == 0);
     const int ntiles = TAIL == kNoTail ? tiles_m * tiles_n : tail_tiles;
     const int grid = max_workgroups > 0 && max_workgroups < ntiles ? max_workgroups : ntiles;
-    auto kern = gemm_staged_kernel<Cfg, OUT_BF16, TILED, TAIL>;
-    constexpr int lds = Cfg::lds_bytes(TILED);
-    if (lds > 64 * 1024) {  // what a launch may ask for by itself
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (TAIL == kNoTail) {
+        const hipError_t e = prepare_staged<Cfg, OUT_BF16, TILED, TAIL>();
         if (e != hipSuccess)
             return e;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Cfg::THREADS), lds, stream, a_q, a_s, b_q, b_s, M, N, K,
+    auto kern = gemm_staged_kernel<Cfg, OUT_BF16, TILED, TAIL>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Cfg::THREADS), Cfg::lds_bytes(TILED), stream, a_q, a_s, b_q, b_s, M, N, K,
                        static_cast<uint8_t *>(c), ldc_bytes, tiles_m, tiles_n, vec_store, tail);
     return hipGetLastError();
+}
+
+template <class Cfg, int TAIL> static hipError_t prepare_staged_cfg(bool c_bf16, bool tiled)
+{
+    if constexpr (Cfg::SCALED)
+        if (tiled)
+            return c_bf16 ? prepare_staged<Cfg, true, true, TAIL>() : prepare_staged<Cfg, false, true, TAIL>();
+    return c_bf16 ? prepare_staged<Cfg, true, false, TAIL>() : prepare_staged<Cfg, false, false, TAIL>();
 }
 
 template <class Cfg, int TAIL = kNoTail>
@@ -1286,11 +1303,14 @@ static hipError_t launch_product(const uint8_t *a_q, const uint8_t *a_s, const u
     case Tile::k256x192:
         return launch_any<GemmCfg<256, 192, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, max_workgroups, stream);
     case Tile::k256_tail: {
+        using Quarter = StagedCfg<128, 128, FMT, A5, B5>;
         const GemmTail tail = {units, units};
         const int n = ((M + 255) / 256) * ((N + 255) / 256);
-        const hipError_t e = launch_any<GemmCfg<256, 256, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, 0, stream, tail);
-        return e != hipSuccess ? e : launch_staged_cfg<StagedCfg<128, 128, FMT, A5, B5>, kTailPlain>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, 0,
-                                                                                                    stream, tail, 4 * (n - tail.first(n)));
+        hipError_t e = prepare_staged_cfg<Quarter, kTailPlain>(c_bf16, tiled);
+        if (e == hipSuccess)
+            e = launch_any<GemmCfg<256, 256, 2, 2, FMT, A5, B5>>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, 0, stream, tail);
+        return e != hipSuccess ? e : launch_staged_cfg<Quarter, kTailPlain>(a_q, a_s, b_q, b_s, M, N, K, c, c_bf16, tiled, ldc, 0, stream, tail,
+                                                                            4 * (n - tail.first(n)));
     }
     case Tile::k256: break;
     }

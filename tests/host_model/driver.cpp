@@ -415,6 +415,7 @@ int main(int argc, char **argv)
                            : fmt == "fp4" ? mxfp8_fp4_gemm_ex(MXFP8_FPROP, a, a, a, a, M, N, K, c, dtype_of(dt), ldc, lay, g_max_workgroups, nullptr)
                                           : mxfp8_gemm_ex(MXFP8_FPROP, a, a, a, a, M, N, K, c, dtype_of(dt), ldc, lay, g_max_workgroups, nullptr);
             printf("route %d %u %zu\n", st, wavesim::g.grid.x, wavesim::g.launch_lds);
+            report(st);
         } else if (op == "expandfp6") {
             long rows, cols;
             int element;

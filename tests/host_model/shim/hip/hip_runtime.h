@@ -81,7 +81,11 @@ inline uint32_t __float_as_uint(float f)
 typedef void *hipStream_t;
 enum hipError_t { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorInvalidConfiguration = 9 };
 enum hipFuncAttribute { hipFuncAttributeMaxDynamicSharedMemorySize = 8 };
-inline hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+inline hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int)
+{
+    static int left = getenv("WAVESIM_FAIL_ATTRIBUTE") ? atoi(getenv("WAVESIM_FAIL_ATTRIBUTE")) : -1;  // the call (from 0 on) that fails
+    return left-- == 0 ? hipErrorInvalidValue : hipSuccess;
+}
 inline hipError_t hipGetLastError() { return hipSuccess; }
 enum hipDeviceAttribute_t { hipDeviceAttributeMultiprocessorCount = 63 };
 inline hipError_t hipGetDevice(int *dev)

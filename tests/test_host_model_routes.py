@@ -101,3 +101,14 @@ def test_rest_as_quarters(hostmodel, tmp_path):
                     calls.append((fmt, M, N, steps, bf16, N, 0, tiled, 0))
                     want.append((4 * rest, launch((fmt, M, N, steps, bf16, 0, tiled, 0), "staged", 128, 128)[1]))
     assert routes(hostmodel, tmp_path, calls) == want
+
+
+def test_nothing_is_launched_where_a_kernel_is_refused(hostmodel, tmp_path):
+    """A product of two launches: whatever is refused before a launch is refused before the first one."""
+    M, N, kbytes = TAIL_SHAPES[0]
+    case = tmp_path / "case.txt"
+    case.write_text(f"route fp8 {M} {N} {kbytes} bf16 {N} 0 tiled\n")
+    for fails, status, launched in ((0, 6, 0), (1, 6, 0), (2, 0, 2)):   # both kernels ask for LDS
+        res = subprocess.run([hostmodel, str(case)], capture_output=True, text=True, env=dict(os.environ, WAVESIM_BLOCKS="0", WAVESIM_FAIL_ATTRIBUTE=str(fails)))
+        lines = {v.split()[0]: v.split()[1:] for v in res.stdout.splitlines()}
+        assert (int(lines["status"][0]), len(lines["launches"])) == (status, launched), fails
