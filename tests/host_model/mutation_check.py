@@ -3,7 +3,7 @@ or tests/test_mutation_checks.py with --runslow). Plants one mistake at a time i
 copy of the product kernels' sources -- a removed barrier, a wait count that is one too loose, a missing wait,
 a swizzle mismatch, a prefetch into the wrong buffer or of the wrong K step, a missing ragged-tile clamp, a scale
 of another row or step, a wrong output row -- builds the host model from it and runs a few products on that kernel
-(one-tile, resident, resident on ragged problems, staged) against the oracle in all four scheduling modes (lazy /
+(one-tile, resident, resident on ragged problems, staged, a rest of tiles as quarters, grouped weight gradients) against the oracle in the scheduling modes (lazy /
 eager DMA completion, either wavefront running ahead). Every mutant must be caught, by a wrong, NaN or missing
 result or by the model's range check. A second group plants mistakes into the
 converters (scale-rule constants, the staging swizzle of the transposed copy, a removed barrier, the infinity patch,
@@ -95,6 +95,28 @@ STAGED_MUTANTS = [  # gemm_staged_tiles.h
     ("staged: ragged tile reads past the last row", "goff[i] = (uint32_t)min(row, (is_a ? M - m0 : N - n0) - 1) * (uint32_t)K", "goff[i] = (uint32_t)row * (uint32_t)K"),
     ("staged: no barrier before the next tile's requests", "            __syncthreads();  // the next tile's requests go where the rows were staged", "            ;"),
 ]
+# a rest of 256x256 tiles as quarters: the second launch of a plain product, the end of a grouped one's
+QUARTER_MUTANTS = [
+    ("quarters: the first tiles instead of the rest", "tile_of_block(done + (tile >> 2), whole_tiles", "tile_of_block(tile >> 2, whole_tiles"),
+    ("quarters: two of four computed twice", "n0 = tile_n * 256 + (tile & 1) * 128;", "n0 = tile_n * 256 + (tile >> 1 & 1) * 128;"),
+]
+REST_MUTANTS = [
+    ("grouped rest: rows counted from the first expert's", "m0 = first_row + tile_m * 256", "m0 = tile_m * 256"),
+    ("grouped rest: rows behind the expert's end stored", "M = at.end;", "M = M_all;"),
+    ("grouped rest: weights of the first expert", "b_q += at.expert * groups.b_group_bytes;", ""),
+]
+# grouped weight gradients on resident workgroups, first occurrence in gemm.hip
+WGRAD_MUTANTS = [
+    ("wgrad: A requests two steps ahead stay in the next tile", "const bool a_next = kt + 2 - steps < next_tile.steps;", "const bool a_next = true;"),
+    ("wgrad: B scales of the next tile read at the current tile's offset", "bs_off = b_here ? cur_tile.bs_off : next_tile.bs_off;", "bs_off = cur_tile.bs_off;"),
+    ("wgrad: B of every expert from the first step on", "            t.b += first_step * BK;\n", ""),
+    ("wgrad: second step of a one-step tile fetched past its expert", "        if (cur_tile.steps == 1) {", "        if (false) {"),
+    ("wgrad: experts without a step not cleared", "(int64_t)i * 16) = make_uint4(0, 0, 0, 0);\n            }\n            prev = end;",
+     "(int64_t)i * 16) = make_uint4(1, 0, 0, 0);\n            }\n            prev = end;"),
+    ("wgrad: experts of the same number of steps share a place", " || (all_steps[e] == own.steps && e < tid);", ";"),
+    ("wgrad: tiles lost behind rounds that workgroups sit out", "min(max(round - 1, 0), skipped) * busy", "min(round, skipped) * busy"),
+    ("wgrad: rounds that go backwards counted from the end of the whole round", "(round & 1 ? width - 1 - place : place)", "(round & 1 ? (int)gridDim.x - 1 - place : place)"),
+]
 MODES = [{}, {"WAVESIM_ORDER": "down"}, {"WAVESIM_DMA": "eager"}, {"WAVESIM_DMA": "eager", "WAVESIM_ORDER": "down"}]
 
 
@@ -159,6 +181,67 @@ def caught(binary, work, kernel):
     return None
 
 
+def caught_quarters(binary, work, kernel):
+    """Every quarter of the second launch of a plain product (nine ragged tiles on eight units)."""
+    M, N, K = 700, 760, 28 * 128
+    rng = np.random.default_rng(7)
+    ops = oracle.quantize_rowwise(rng.standard_normal((M, K)).astype(np.float32)) + oracle.quantize_rowwise(rng.standard_normal((N, K)).astype(np.float32))
+    out, names = os.path.join(work, "c.bin"), [os.path.join(work, n + ".bin") for n in ("aq", "as", "bq", "bs")]
+    for path, v in zip(names, ops):
+        (sl.tile(v, filler=0xFF) if path.endswith("s.bin") else v).tofile(path)
+    case = os.path.join(work, "case.txt")
+    open(case, "w").write(f"gemm 0 {M} {N} {K} f32 {N} {' '.join(names)} {out} tiled\n")
+    r = subprocess.run([binary, case], capture_output=True, text=True, env=dict(os.environ, WAVESIM_CUS="8", WAVESIM_ONLY="1"))
+    if r.returncode != 0:
+        return f"model stopped: {(r.stderr.strip().splitlines() or ['exit code ' + str(r.returncode)])[-1][:100]}"
+    c = np.fromfile(out, np.uint32).reshape(M, N)
+    want = np.zeros((M, N), bool)
+    want[512:, 512:] = True
+    if not np.array_equal(c != 0xA5A5A5A5, want):
+        return "quarters missing, or others written"
+    ref, absum = oracle.gemm_rows(*ops, np.arange(512, M))
+    bad = np.abs(c.view(np.float32)[512:, 512:] - ref[:, 512:]) > (K // 128 * 2.0 ** -24 * absum + 1e-300)[:, 512:]
+    return "wrong result" if bad.any() else None
+
+
+def caught_grouped(binary, work, kernel):
+    """grouped rest: three workgroups of a product of three experts whose last sixteen tiles are quarters; wgrad: experts of 0 .. 10 steps,
+    whole and ragged tiles, workgroups that sit out a round."""
+    rng = np.random.default_rng(8)
+    rest = kernel == "grouped rest"
+    for M, N, steps, units, tiled, blocks in ([(2048, 4096, 16, 128, False, 3)] if rest else [(264, 520, [1, 1, 0, 2, 0, 3, 1, 1] + [0] * 56, 5, True, 0),
+                                                                                           (512, 256, [1, 1, 0, 10, 1, 1, 1, 1] + [0] * 56, 5, False, 0)]):
+        K = steps * 128 if rest else sum(steps) * 128
+        ends = [400, 1003, 2001] if rest else [int(e) * 128 for e in np.cumsum(steps)]
+        a = oracle.quantize_rowwise(rng.standard_normal((M, K)).astype(np.float32) * np.exp2(rng.integers(-6, 7, (M, 1))).astype(np.float32))
+        bs = [oracle.quantize_rowwise((rng.standard_normal((N, K)) * 0.02).astype(np.float32) * np.exp2(rng.integers(-6, 7, (N, 1))).astype(np.float32))
+              for _ in range(len(ends) if rest else 1)]
+        ops = a + ((np.stack([q for q, _ in bs]), np.stack([s for _, s in bs])) if rest else bs[0])
+        scales = (lambda s: np.concatenate([sl.tile(x, filler=0xFF).ravel() for x in (s if s.ndim == 3 else [s])])) if tiled else (lambda s: s)
+        names = [os.path.join(work, n + ".bin") for n in ("aq", "as", "bq", "bs", "ends")]
+        for path, v in zip(names, (ops[0], scales(ops[1]), ops[2], scales(ops[3]), np.asarray(ends, np.int32))):
+            v.tofile(path)
+        out, case, bf16 = os.path.join(work, "c.bin"), os.path.join(work, "case.txt"), not tiled and not rest
+        open(case, "w").write(f"{'gemmgrp' if rest else 'gemmgrpk'} {M} {N} {K} {'bf16' if bf16 else 'f32'} {N} {len(ends)} {' '.join(names)} {out}" + (" tiled" if tiled else "") + "\n")
+        for mode in MODES[:1] if rest else MODES[::3]:
+            r = subprocess.run([binary, case], capture_output=True, text=True,
+                               env=dict(os.environ, WAVESIM_CUS=str(units), WAVESIM_BLOCKS=str(blocks or "all"), **mode))
+            if r.returncode != 0:
+                return f"model stopped: {(r.stderr.strip().splitlines() or ['exit code ' + str(r.returncode)])[-1][:100]}"
+            raw = np.fromfile(out, np.uint16 if bf16 else np.uint32).reshape(-1, N)
+            written = raw != (0xA5A5 if bf16 else 0xA5A5A5A5)
+            val = (raw.astype(np.uint32) << 16).view(np.float32) if bf16 else raw.view(np.float32)
+            ref, absum = (oracle.grouped_gemm if rest else oracle.grouped_gemm_wgrad)(*ops, ends)
+            ref, absum = np.reshape(ref, raw.shape), np.reshape(absum, raw.shape)
+            owned = ~np.isnan(ref)
+            if (written & ~owned).any() or not (written.all() if not rest else written[ends[1]:ends[1] + 128, 6 * 256:6 * 256 + 128].all()):
+                return "rows missing, or others written"
+            tol = K // 128 * 2.0 ** -24 * absum + (2.0 ** -8 * np.abs(ref) if bf16 else 0.0) + 1e-300
+            if np.isnan(val[written]).any() or (np.abs(val - ref)[written] > tol[written]).any():
+                return f"wrong result at {M}x{N} in mode {mode or 'default'}"
+    return None
+
+
 # mistakes in the converters: (description, source file, old text, new text), first occurrence
 QUANT_MUTANTS = [
     ("quantizer: FP32 scale rule carries at 1.875 instead of 1.75", "mxfp8_device.h",
@@ -174,6 +257,9 @@ QUANT_MUTANTS = [
      "f0 |= ((q0 >> (8 * j)) & 0xFFu) << (8 * j);"),
     ("quantizer: MXFP4 scale rule carries at 1.75 instead of 1.5", "mxfp4.hip",
      "(abs_bits + 0x3FFFFFu) >> 23) - 2", "(abs_bits + 0x1FFFFFu) >> 23) - 2"),
+    ("quantizer: MXFP4 of BF16 sources, the other column of a pair in the column copy", "mxfp4.hip", "(j & 1) ? 0x07060302u : 0x05040100u", "(j & 1) ? 0x05040100u : 0x07060302u"),
+    ("quantizer: MXFP4 of BF16 sources, maxima of the other column of a pair", "mxfp4.hip", "(j & 1) ? (cm[j >> 1] & 0xFFFF0000u) >> 1", "!(j & 1) ? (cm[j >> 1] & 0xFFFF0000u) >> 1"),
+    ("quantizer: MXFP4 blocks with a NaN keep the converter's codes", "mxfp4.hip", "    if (sb == 0xFFu)\n        return make_uint4(0, 0, 0, 0);", ""),
     ("quantizer: MXFP6 scale exponent one too large", "mxfp6.hip",
      "(0x7FFFFFu - F::TOP_FRAC)) >> 23) - F::EMAX;", "(0x7FFFFFu - F::TOP_FRAC)) >> 23) - F::EMAX + 1;"),
 ]
@@ -191,7 +277,8 @@ def caught_quant(binary, work):
         cases.append((f"quantize {'bf16' if bf16 else 'f32'} 256 256 256 3", src,
                       (oracle.quantize_rowwise(src), oracle.quantize_colwise(src))))
     h4 = si.fp4_hard_cases(160, 96, seed=12)
-    cases.append(("quantfp4 f32 160 96 96 3", h4, (mxfp4.quantize_rowwise(h4), mxfp4.quantize_colwise(h4))))
+    for src in (h4, si.to_bf16_bits(h4)):
+        cases.append((f"quantfp4 {'f32' if src is h4 else 'bf16'} 160 96 96 3", src, (mxfp4.quantize_rowwise(src), mxfp4.quantize_colwise(src))))
     h6 = si.fp6_hard_cases(160, 96, seed=12, top=7.5)
     cases.append(("quantfp6 f32 160 96 96 3 0", h6, (mxfp6.quantize_rowwise(h6, "e2m3"), mxfp6.quantize_colwise(h6, "e2m3"))))
     for head, src, ((q, s), (qT, sT)) in cases:
@@ -218,6 +305,10 @@ def main():
     todo += [(desc, "gemm.hip", old, new, "resident") for desc, old, new in PERSISTENT_MUTANTS]
     todo += [(desc, "gemm.hip", old, new, "ragged") for desc, old, new in RAGGED_MUTANTS]
     todo += [(desc, "gemm_staged_tiles.h", old, new, "staged") for desc, old, new in STAGED_MUTANTS]
+    todo += [(f"(unmutated source, {kernel}: must pass)", "gemm.hip", "", "", kernel) for kernel in ("quarters", "grouped rest", "wgrad")]
+    todo += [(desc, "gemm_staged_tiles.h", old, new, "quarters") for desc, old, new in QUARTER_MUTANTS]
+    todo += [(desc, "gemm_staged_tiles.h", old, new, "grouped rest") for desc, old, new in REST_MUTANTS]
+    todo += [(desc, "gemm.hip", old, new, "wgrad") for desc, old, new in WGRAD_MUTANTS]
     todo += [("(unmutated converters: must pass)", "gemm.hip", "", "", None)] + [m + (None,) for m in QUANT_MUTANTS]
     for desc, name, old, new, kernel in todo:   # every pattern must still be in the source: a stale one would test nothing
         assert old == "" or old in open(os.path.join(csrc, name)).read(), desc
@@ -233,7 +324,8 @@ def main():
         work = tempfile.mkdtemp(prefix="kmut_")
         try:
             binary = build(work, text, name)
-            how = caught_quant(binary, work) if kernel is None else caught(binary, work, kernel)
+            look = {None: lambda b, w, k: caught_quant(b, w), "quarters": caught_quarters, "grouped rest": caught_grouped, "wgrad": caught_grouped}
+            how = look.get(kernel, caught)(binary, work, kernel)
         finally:
             shutil.rmtree(work, ignore_errors=True)
         ok = (how is None) if old == "" else (how is not None)

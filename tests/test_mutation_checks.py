@@ -1,7 +1,7 @@
 """Runs the two mutation checks as tests, so that "every planted mistake is caught" can be reproduced:
 oracle/mutation_check.py plants single plausible mistakes in the oracle's C source and expects the pins
 (tests/test_oracle_pins.py, tests/test_oracle_modes.py) to fail; tests/host_model/mutation_check.py does the
-same to the product kernels and the converters on the CPU execution model. The full sets (tens of minutes; three for
+same to the product kernels and the converters on the CPU execution model. The full sets (tens of minutes; five for
 the kernels on eight cores) run only with `--runslow` (`python -m pytest tests/test_mutation_checks.py --runslow`); a three-mutant sample of the oracle
 check runs every time."""
 import os
@@ -37,4 +37,4 @@ def test_oracle_pins_catch_every_planted_mistake():
 @pytest.mark.slow
 def test_host_model_catches_every_planted_kernel_mistake():
     out = _run("tests/host_model/mutation_check.py", timeout=3400)
-    assert "48 of 48 as expected (43 planted mistakes)" in out
+    assert "67 of 67 as expected (59 planted mistakes)" in out
