@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -104,10 +105,12 @@ def load() -> ctypes.CDLL:
 
 
 def _bind_fastcall(lib):
-    """csrc/fastcall.cpp on the entry points of `lib`. Without the module every call takes the checks below."""
+    """csrc/fastcall.cpp on the entry points of `lib`. Without the module every call takes the checks below, 2 to 3 us longer."""
     try:
         from . import _fastcall
-    except ImportError:
+    except ImportError as e:
+        warnings.warn(f"the binding's calls in C++ cannot be loaded ({e}): calls take 2 to 3 us longer; "
+                      "`python -m paper_2506_08027_amd.build` builds them for this PyTorch", RuntimeWarning, stacklevel=2)
         return None
     table = {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
         "mxfp8_quantize_mode_ex", "mxfp8_gemm_ex", "mxfp8_gemm_mode_ex", "mxfp8_dequantize_mode_ex", "mxfp8_gemm_bf16",

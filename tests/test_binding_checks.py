@@ -1,6 +1,7 @@
 """What the binding says first about a call with several mistakes: the tensors are looked at before the stream is asked for, on a
 machine without a GPU too, with and without the calls in C++."""
 import os
+import sys
 
 import pytest
 import torch
@@ -36,3 +37,11 @@ def test_host_tensors_are_reported_before_the_stream(monkeypatch, fast, stream, 
     for call in _calls(stream, which):
         with pytest.raises(ValueError, match="all tensors must live in GPU memory"):
             call()
+
+
+def test_calls_in_cpp_that_cannot_be_loaded_are_reported(monkeypatch):
+    lib = mx.load()
+    monkeypatch.setitem(sys.modules, "paper_2506_08027_amd._fastcall", None)   # what an import of it then raises
+    monkeypatch.delattr(sys.modules["paper_2506_08027_amd"], "_fastcall", raising=False)
+    with pytest.warns(RuntimeWarning, match="cannot be loaded"):
+        assert binding._bind_fastcall(lib) is None
