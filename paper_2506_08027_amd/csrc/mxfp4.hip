@@ -80,7 +80,11 @@ __device__ __forceinline__ void fp4_store_scales(uint8_t *s, int64_t r, int64_t 
     }
 }
 
-template <bool BF16, bool ROW, bool COL, bool TILED>
+// FEW: at most 64 rows, i.e. half of the wavefronts would have none. Two wavefronts hold the same 32 rows instead and share the work:
+// one makes the row copy and one the column copy, or each makes half of the only one. In us, tile staged as FP32 | one wavefront | two
+// ([32 x 4096], [64 x 4096]): BF16, both copies 4.4 | 4.8 | 4.2, 4.7 | 5.0 | 4.4; FP32, both 4.7 | 5.3 | 4.8, 5.0 | 5.5 | 5.0; FP32, row
+// copy 4.1 | 4.5 | 3.9, 4.4 | 4.6 | 4.1. Reading twice costs more where the tiles are many: FP32 [64 x 262144], row copy 15.4 | 18.1.
+template <bool BF16, bool ROW, bool COL, bool TILED, bool FEW>
 __global__ __launch_bounds__(kQuantThreads) void quantize_fp4_kernel(const uint8_t *__restrict__ src, int64_t rows, int64_t cols,
                                                                      int64_t ld_bytes, uint8_t *__restrict__ q_row,
                                                                      uint8_t *__restrict__ s_row, uint8_t *__restrict__ q_colT,
@@ -98,7 +102,8 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_fp4_kernel(const uint8
     auto col_line = [](int c) __attribute__((always_inline)) { return c * LINE + (c >> 3) * COL_GAP; };
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int cc = lane % CC, rs = lane / CC;
-    const int lrow0 = wave * 32 + rs * ROWS, lcol0 = cc * VEC;  // first row and column of this lane inside the tile
+    const int band = FEW ? wave & 1 : wave, share = wave >> 1;   // rows of this wavefront, in units of 32; FEW: which half of the work
+    const int lrow0 = band * 32 + rs * ROWS, lcol0 = cc * VEC;  // first row and column of this lane inside the tile
     const int64_t nb_row = cols / kBlock, nb_col = rows / kBlock;
     for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const uint32_t tile_y = tile / tiles_x, tile_x = tile - tile_y * tiles_x;
@@ -113,9 +118,11 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_fp4_kernel(const uint8
             if (active)
                 x[i] = stream_load(reinterpret_cast<const uint4 *>(src + (row0 + i) * ld_bytes + col0 * ESIZE));
         }
-        if constexpr (ROW) {
+        if (ROW && !(FEW && COL && share != 0)) {
 #pragma unroll
             for (int i = 0; i < ROWS; ++i) {
+                if (FEW && !COL && i / (ROWS / 2) != share)
+                    continue;
                 uint32_t am = lane_amax<BF16>(x[i]);
                 am = umax(am, dpp_xor1(am));
                 am = umax(am, dpp_xor2(am));
@@ -139,12 +146,14 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_fp4_kernel(const uint8
                     lds_rs[(lrow0 + i) * 4 + lcol0 / kBlock] = (uint8_t)sb;
             }
         }
-        if constexpr (COL) {
+        if (COL && !(FEW && ROW && share == 0)) {
             // Maxima of the column block, two columns a word (BF16), of the magnitudes shifted up by the sign: masked as in the row
             // direction, the compiler keeps all of them from there on, in twice the registers.
-            uint32_t cm[4];
+            uint32_t cm[4] = {0, 0, 0, 0};
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
+                if (FEW && !ROW && w / 2 != share)
+                    continue;
                 uint32_t m = 0;
 #pragma unroll
                 for (int i = 0; i < ROWS; ++i) {
@@ -161,6 +170,8 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_fp4_kernel(const uint8
             }
 #pragma unroll
             for (int j = 0; j < VEC; ++j) {
+                if (FEW && !ROW && j / (VEC / 2) != share)
+                    continue;
                 const uint32_t am = !BF16 ? cm[j & 3] >> 1 : (j & 1) ? (cm[j >> 1] & 0xFFFF0000u) >> 1 : (cm[j >> 1] & 0xFFFFu) << 15;
                 const uint32_t sb = fp4_scale_byte(am);
                 const float sc = scale_operand(sb);
@@ -188,7 +199,7 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_fp4_kernel(const uint8
                 else
                     *reinterpret_cast<uint2 *>(dst) = make_uint2(q[0], q[ROWS / 8 - 1]);
                 if (rs == 0)
-                    lds_cs[(lcol0 + j) * 4 + wave] = (uint8_t)sb;
+                    lds_cs[(lcol0 + j) * 4 + band] = (uint8_t)sb;
             }
         }
         __syncthreads();
@@ -228,7 +239,7 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_fp4_kernel(const uint8
     }
 }
 
-template <bool BF16, bool TILED>
+template <bool BF16, bool TILED, bool FEW>
 static hipError_t launch_quantize_fp4_t(const void *src, int64_t rows, int64_t cols, int64_t ld, int axis, uint8_t *q_row,
                                         uint8_t *s_row, uint8_t *q_colT, uint8_t *s_colT, hipStream_t stream)
 {
@@ -251,21 +262,30 @@ static hipError_t launch_quantize_fp4_t(const void *src, int64_t rows, int64_t c
     const dim3 grid((unsigned)groups), block(kQuantThreads);
     const uint8_t *s = static_cast<const uint8_t *>(src);
     const int64_t ldb = ld * (BF16 ? 2 : 4);
-    auto kern = axis == 1 ? quantize_fp4_kernel<BF16, true, false, TILED> : axis == 2 ? quantize_fp4_kernel<BF16, false, true, TILED>
-                                                                           : quantize_fp4_kernel<BF16, true, true, TILED>;
+    auto kern = axis == 1 ? quantize_fp4_kernel<BF16, true, false, TILED, FEW> : axis == 2 ? quantize_fp4_kernel<BF16, false, true, TILED, FEW>
+                                                                                : quantize_fp4_kernel<BF16, true, true, TILED, FEW>;
     hipLaunchKernelGGL(kern, grid, block, 0, stream, s, rows, cols, ldb, q_row, s_row, q_colT, s_colT, (uint32_t)tiles_x,
                        (uint32_t)(tiles_x * tiles_y));
     return hipGetLastError();
 }
 
+template <bool FEW>
+static hipError_t launch_quantize_fp4_rows(const void *src, bool bf16, int64_t rows, int64_t cols, int64_t ld, int axis, uint8_t *q_row,
+                                           uint8_t *s_row, uint8_t *q_colT, uint8_t *s_colT, bool tiled_scales, hipStream_t stream)
+{
+    if (bf16)
+        return tiled_scales ? launch_quantize_fp4_t<true, true, FEW>(src, rows, cols, ld, axis, q_row, s_row, q_colT, s_colT, stream)
+                            : launch_quantize_fp4_t<true, false, FEW>(src, rows, cols, ld, axis, q_row, s_row, q_colT, s_colT, stream);
+    return tiled_scales ? launch_quantize_fp4_t<false, true, FEW>(src, rows, cols, ld, axis, q_row, s_row, q_colT, s_colT, stream)
+                        : launch_quantize_fp4_t<false, false, FEW>(src, rows, cols, ld, axis, q_row, s_row, q_colT, s_colT, stream);
+}
+
 hipError_t launch_quantize_fp4(const void *src, bool bf16, int64_t rows, int64_t cols, int64_t ld, int axis, uint8_t *q_row,
                                uint8_t *s_row, uint8_t *q_colT, uint8_t *s_colT, bool tiled_scales, hipStream_t stream)
 {
-    if (bf16)
-        return tiled_scales ? launch_quantize_fp4_t<true, true>(src, rows, cols, ld, axis, q_row, s_row, q_colT, s_colT, stream)
-                            : launch_quantize_fp4_t<true, false>(src, rows, cols, ld, axis, q_row, s_row, q_colT, s_colT, stream);
-    return tiled_scales ? launch_quantize_fp4_t<false, true>(src, rows, cols, ld, axis, q_row, s_row, q_colT, s_colT, stream)
-                        : launch_quantize_fp4_t<false, false>(src, rows, cols, ld, axis, q_row, s_row, q_colT, s_colT, stream);
+    constexpr int64_t kFewCols = 512 * kTile;  // two tiles for each of 256 units ([64 x 65536] gains 3 to 13 %, FP32 column copy -5 %)
+    return rows <= kTile / 2 && cols <= kFewCols ? launch_quantize_fp4_rows<true>(src, bf16, rows, cols, ld, axis, q_row, s_row, q_colT, s_colT, tiled_scales, stream)
+                                                 : launch_quantize_fp4_rows<false>(src, bf16, rows, cols, ld, axis, q_row, s_row, q_colT, s_colT, tiled_scales, stream);
 }
 
 // ---- decode: value = E2M1(code) * 2^(s - 127) -----------------------------------------------------------------

@@ -12,7 +12,7 @@ from paper_2506_08027_amd import synth_inputs as si
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("shape", [(64, 96), (128, 128), (160, 288), (96, 416), (416, 96)])
+@pytest.mark.parametrize("shape", [(32, 160), (64, 96), (64, 288), (128, 128), (160, 288), (96, 416), (416, 96)])
 @pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
 @pytest.mark.parametrize("tiled", [False, True], ids=["rowmajor", "tiled"])
 @pytest.mark.parametrize("off", [0, 1])
@@ -43,3 +43,19 @@ def test_places(shape, bf16, tiled, off):
         for name, first, n in ((q, 16, out[q].numel()), (s, 8 + off, out[s].numel())):
             edge = hold[name].cpu().numpy()
             assert (edge[:first] == 0xEE).all() and (edge[first + n:] == 0xEE).all(), name
+
+
+@pytest.mark.parametrize("rows", [32, 64, 96])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("layout", [mx.SCALES_ROWMAJOR, mx.SCALES_TILED], ids=["rowmajor", "tiled"])
+def test_one_copy_is_the_same_as_of_both(rows, dtype, layout):
+    x = torch.from_numpy(si.fp4_hard_cases(rows, 2080, seed=rows)).cuda().to(dtype)
+    both = mx.fp4_quantize(x, "both", layout)
+    for axis, names in (("rowwise", ("q_row", "s_row")), ("colwise", ("q_colT", "s_colT"))):
+        one = mx.fp4_quantize(x, axis, layout)
+        for name in names:
+            if layout == mx.SCALES_TILED and name[0] == "s":
+                r, c = (rows, 2080) if name == "s_row" else (2080, rows)
+                assert np.array_equal(sl.untile(one[name].cpu().numpy(), r, c // 32), sl.untile(both[name].cpu().numpy(), r, c // 32))
+            else:
+                assert torch.equal(one[name], both[name])

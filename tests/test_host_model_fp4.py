@@ -61,6 +61,16 @@ def test_fp4_quantize_every_tile_of_small_and_odd_grids(hostmodel, tmp_path, row
     _check_quantize(hostmodel, tmp_path, x, True, 3, True, WAVESIM_CUS=1)
 
 
+@pytest.mark.parametrize("rows", [32, 64, 96])
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+def test_fp4_quantize_few_rows(hostmodel, tmp_path, rows, bf16):
+    """Up to 64 rows two wavefronts share the same rows: one copy each, or half of the only copy."""
+    x = si.fp4_hard_cases(rows, 160, seed=rows)
+    x[rows - 1, 3], x[5, 150] = np.inf, np.nan
+    for axis, tiled, ld in ((1, True, 168), (2, False, 160), (3, True, 160)):
+        _check_quantize(hostmodel, tmp_path, x, bf16, axis, tiled, ld=ld)
+
+
 def test_fp4_quantize_tiny_with_specials(hostmodel, tmp_path):
     x = si.tiny_with_specials(256, seed=0)
     _check_quantize(hostmodel, tmp_path, x, False, 3, False)
