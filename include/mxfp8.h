@@ -225,8 +225,9 @@ mxfp8_status mxfp8_requantize_colwise_ex(const uint8_t *q_row, const uint8_t *s_
  *   gets its own product over its own tokens:
  *   c   [groups x M x N]        dW_e starts M*ldc elements after dW_(e-1); an expert without tokens gets zeros.
  *   Requirements: K % 128 == 0; c aligned to its element size (128-bit stores when c is 16-byte aligned and
- *   ldc * sizeof(element) and M * ldc * sizeof(element) are multiples of 16). One workgroup per expert and tile;
- *   max_workgroups is ignored.
+ *   ldc * sizeof(element) and M * ldc * sizeof(element) are multiples of 16). max_workgroups is
+ *   ignored: 256x256 tiles whose rows of C start and end on 16 bytes are shared out to one resident workgroup per
+ *   compute unit (up to 128 experts), anything else takes one workgroup per expert and tile.
  * All passes: groups <= 4096; a_q, a_s, b_q, b_s 16-byte aligned, group_ends 4-byte aligned.
  */
 mxfp8_status mxfp8_gemm_grouped_ex(mxfp8_pass pass, const uint8_t *a_q, const uint8_t *a_s,
@@ -252,8 +253,9 @@ mxfp8_status mxfp8_gemm_bf16(const void *a_bf16, const void *b_bf16, int64_t M, 
                              void *hip_stream);
 
 /*
- * mxfp8_gemm_ex with BF16 output AND, from the same pass, MXFP8 copies of that output, i.e. the next
- * layer's operands (Section 2: the FP32 result is re-quantized when it is needed in MX format;
+ * mxfp8_gemm_ex with BF16 output AND, from the same call, MXFP8 copies of that output, i.e. the next
+ * layer's operands (in one kernel, or the product's and then the quantizer's, whichever is faster for the
+ * shape; Section 2: the FP32 result is re-quantized when it is needed in MX format;
  * Section 3.2 for the two axes; Section 3.3, Appendix A.1/A.2 for the conversion). c_bf16 [M x N] is the
  * accumulator rounded to BF16 (RNE); the copies selected by `axis` are exactly what
  * mxfp8_quantize_ex(c_bf16, BF16, M, N, ldc, axis, ...) would give:

@@ -1,5 +1,6 @@
-// C ABI of the MXFP8 library: argument validation on the host, then one kernel launch on the
-// caller's stream. Nothing is allocated, nothing is synchronised, no state is kept.
+// C ABI of the MXFP8 library: argument validation on the host, then the call's kernels on the caller's stream (one; two or
+// three where the rest of a product's tiles or the copies of its output get a launch of their own). Nothing is allocated,
+// nothing is synchronised, no state is kept.
 #include "../../include/mxfp8.h"
 
 #include <hip/hip_runtime.h>
