@@ -79,7 +79,7 @@ struct Args {
 uint8_t *ptr(const at::Tensor *t) { return t ? static_cast<uint8_t *>(t->data_ptr()) : nullptr; }
 bool dense_bytes(const at::Tensor &t) { return t.scalar_type() == at::kByte && t.is_contiguous(); }
 bool dense_matrix(const at::Tensor &t, int64_t rows, int64_t cols) { return t.dim() == 2 && t.size(0) == rows && t.size(1) == cols && dense_bytes(t); }
-// scale bytes of `operands` operands [rows x cols]
+// scale bytes of an operand [rows x cols]
 bool scales(const at::Tensor &s, int64_t rows, int64_t cols, int64_t layout)
 {
     if (!dense_bytes(s) || cols % 32)
@@ -125,7 +125,7 @@ template <class F, class... A> PyObject *call(int which, PyObject *stream, A... 
     return PyLong_FromLong(rc);
 }
 
-// The copies of a quantizer: q_row, s_row, q_colT, s_colT; `num` / `den` bytes per element, element bytes checked where `exact`
+// The copies of a quantizer: q_row, s_row, q_colT, s_colT; `num` / `den` bytes per element
 struct Copies {
     const at::Tensor *q_row, *s_row, *q_colT, *s_colT;
 };
