@@ -402,8 +402,9 @@ struct KShares {
 // other round over the workgroups backwards, and where one expert has most of the steps its workgroups sit out some rounds
 // (KShares). One after the other in the experts' order, loads that repeat with the rounds gave all long tiles to the same
 // workgroups. In us, one tile per workgroup | in the experts' order | this way (tiled scales, FP32 out): [2048 x 2048], experts of
-// 49,5,5,5,49,5,5,5 steps 95.6 | 133.7 | 90.8; [4096 x 2048], 64 experts of 31 and 1 by turns 1490 | 2157 | 1260; [2816 x 2048], 64
-// experts, one with half of 512 steps 790 | 866 | 721, and eight each 670 | 615 | 559; [5632 x 2048], eight of eight steps 159 | 137 | 134.
+// 49,5,5,5,49,5,5,5 steps 97.8 | 136.5 | 92.8; [4096 x 2048], 64 experts of 31 and 1 by turns 1521 | 2100 | 1266; [2816 x 2048], 64
+// experts, one with 256 of 508 steps 885 | 1074 | 867, and eight each 679 | 626 | 552; [5632 x 2048], eight of eight steps 154 | 135 | 132.
+// Not so where the steps fall off like 1/i: [2048 x 2048], 16 experts of 128 steps 119 | 144 | 125.
 template <class Cfg, bool OUT_BF16, bool TILED, bool SPREAD, int FUSE_Q = 0, int SCHED = MXFP8_GEMM_SCHED, bool GROUPED = false, bool RAGGED = false,
           bool KGROUPED = false>
 __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
@@ -436,43 +437,71 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
     [[maybe_unused]] KExpert *const by_steps = reinterpret_cast<KExpert *>(lds + Cfg::LDS_BYTES_PERSISTENT);
     [[maybe_unused]] KShares shares = {0, 0};
     if constexpr (KGROUPED) {
-        static_assert(Cfg::THREADS >= kMostKExperts, "a work-item per expert");
+        static_assert(Cfg::THREADS == 2 * kMostKExperts && kMostKExperts == 2 * 64, "two work-items per expert, two experts per lane");
         const int per_expert = ntiles, pieces = N * (OUT_BF16 ? 2 : 4) / 16;
-        KExpert own = {0, 0, tid};  // expert `tid`
-        int all = 0;                // steps of all experts
-        ntiles = 0;
-        for (int e = 0, prev = 0; e < groups.count; ++e) {
-            const int end = min(max(groups.ends[e], prev), K), steps = end / BK - prev / BK;
-            if (e == tid)
-                own = {steps, prev / BK, e};
-            if (steps > 0) {
-                ntiles += per_expert;
-            } else {
-                for (int m = blockIdx.x; m < M; m += gridDim.x)
-                    for (int i = tid; i < pieces; i += Cfg::THREADS)
-                        *reinterpret_cast<uint4 *>(c + ((int64_t)e * M + m) * ldc_bytes + (int64_t)i * 16) = make_uint4(0, 0, 0, 0);
-            }
-            prev = end;
-            all = end / BK;
-        }
-        // the experts in the order of their steps, most of them first
-        int32_t *const all_steps = reinterpret_cast<int32_t *>(lds);
-        if (tid < groups.count)
-            all_steps[tid] = own.steps;
-        __syncthreads();
-        if (tid < groups.count) {
-            int rank = 0;
+        // Lane l of every wavefront has the experts 2 l and 2 l + 1; an end is the largest one up to there, at most K. Reading one
+        // expert after the other took 60 ns each, before a tile's first request. In us, one tile per workgroup | one expert after the
+        // other | this way: [512 x 512], 64 experts of 2 and of 6 steps (tiled scales, BF16 out) 22.5 | 26.3 | 18.3 and 31.8 | 35.0 |
+        // 27.2; [1024 x 1024], 16 experts of 6 steps (row-major scales, FP32 out) 29.7 | 31.6 | 29.0.
+        auto end_of = [&](int e) { return e < groups.count ? min(max(groups.ends[e], 0), K) : 0; };
+        int end0 = end_of(2 * lane), end1 = end_of(2 * lane + 1), top = max(end0, end1);
+        for (int d = 1; d < 64; d *= 2)
+            top = max(top, __shfl(top, max(lane - d, 0), 64));
+        const int left = __shfl(top, max(lane - 1, 0), 64), before = lane > 0 ? left : 0;
+        end0 = max(end0, before);
+        end1 = max(end1, end0);
+        const int first0 = before / BK, first1 = end0 / BK, steps0 = first1 - first0, steps1 = end1 / BK - first1;
+        const int all = __builtin_amdgcn_readfirstlane(__shfl(top, 63, 64)) / BK;  // steps of all experts
+        const uint64_t has0 = __ballot(steps0 > 0), has1 = __ballot(steps1 > 0);
+        const int active = __popcll(has0) + __popcll(has1);
+        ntiles = active * per_expert;
+        // Zeros: where every tile has a workgroup, by those that are left over, else by all of them.
+        const int writers = per_expert * groups.count <= (int)gridDim.x ? (int)gridDim.x - ntiles : (int)gridDim.x;
+        const int writer = (int)blockIdx.x - ((int)gridDim.x - writers);
+        if (active < groups.count && writer >= 0)
             for (int e = 0; e < groups.count; ++e)
-                rank += all_steps[e] > own.steps || (all_steps[e] == own.steps && e < tid);
-            by_steps[rank] = own;
+                if (!(((e & 1) ? has1 : has0) >> (e >> 1) & 1))
+                    for (int m = writer; m < M; m += writers)
+                        for (int i = tid; i < pieces; i += Cfg::THREADS)
+                            *reinterpret_cast<uint4 *>(c + ((int64_t)e * M + m) * ldc_bytes + (int64_t)i * 16) = make_uint4(0, 0, 0, 0);
+        int32_t *const scratch = reinterpret_cast<int32_t *>(lds);
+        const bool one_round = ntiles <= (int)gridDim.x;
+        if (one_round) {  // a workgroup has one tile at most: in the experts' order
+            if (wave == 0) {
+                const uint64_t below = ((uint64_t)1 << lane) - 1;
+                int rank = __popcll(has0 & below) + __popcll(has1 & below);
+                if (steps0 > 0)
+                    by_steps[rank++] = {steps0, first0, 2 * lane};
+                if (steps1 > 0)
+                    by_steps[rank] = {steps1, first1, 2 * lane + 1};
+            }
+        } else {  // in the order of their steps, most of them first
+            uint32_t *const keys = reinterpret_cast<uint32_t *>(lds);  // of all kMostKExperts; no two are the same
+            if (wave == 0) {
+                keys[2 * lane] = (uint32_t)steps0 * kMostKExperts + (kMostKExperts - 1 - 2 * lane);
+                keys[2 * lane + 1] = (uint32_t)steps1 * kMostKExperts + (kMostKExperts - 2 - 2 * lane);
+                scratch[kMostKExperts + 2 * lane] = first0;
+                scratch[kMostKExperts + 2 * lane + 1] = first1;
+            }
+            __syncthreads();
+            const int expert = tid >> 1;
+            const uint32_t key = keys[expert];
+            int rank = 0;
+            for (int e = 4 * (tid & 1); e < groups.count; e += 8) {
+                const uint4 k = *reinterpret_cast<const uint4 *>(keys + e);
+                rank += (k.x > key) + (k.y > key) + (k.z > key) + (k.w > key);
+            }
+            rank += __shfl_xor(rank, 1, 64);
+            if ((tid & 1) == 0 && expert < groups.count)
+                by_steps[rank] = {(int)(key / kMostKExperts), scratch[kMostKExperts + expert], expert};
         }
         __syncthreads();
         // Where one expert has far more steps than the others have on average, the workgroups with its tiles sit out the rounds
         // in which the others catch up, if that makes the longest share shorter (in steps; an estimate).
         constexpr int STORE = OUT_BF16 ? 4 : 8;  // what a tile takes besides its K loop
-        const int active = ntiles / per_expert, most = active > 0 ? __builtin_amdgcn_readfirstlane(by_steps[0].steps) : 0;
+        const int most = one_round ? 0 : __builtin_amdgcn_readfirstlane(by_steps[0].steps);
         const int others = all - most + STORE * (active - 1);
-        const int rounds = active > 1 && per_expert < (int)gridDim.x ? (most + STORE) * (active - 1) / others - 1 : 0;
+        const int rounds = !one_round && per_expert < (int)gridDim.x ? (most + STORE) * (active - 1) / others - 1 : 0;
         if (rounds > 0) {
             int longest[2] = {0, 0};  // without and with
             for (int b = tid; b < (int)gridDim.x; b += Cfg::THREADS)
@@ -486,12 +515,12 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_persistent_kernel(
             for (int with = 0; with < 2; ++with) {
                 for (int mask = 32; mask > 0; mask >>= 1)
                     longest[with] = max(longest[with], __shfl_xor(longest[with], mask, 64));
-                all_steps[2 * wave + with] = longest[with];
+                scratch[2 * wave + with] = longest[with];
             }
             __syncthreads();
             for (int w = 0; w < Cfg::WAVES; ++w)
                 for (int with = 0; with < 2; ++with)
-                    longest[with] = max(longest[with], all_steps[2 * w + with]);
+                    longest[with] = max(longest[with], scratch[2 * w + with]);
             if (__builtin_amdgcn_readfirstlane(longest[1]) < __builtin_amdgcn_readfirstlane(longest[0]))
                 shares = {per_expert, rounds};
             __syncthreads();

@@ -111,9 +111,8 @@ WGRAD_MUTANTS = [
     ("wgrad: B scales of the next tile read at the current tile's offset", "bs_off = b_here ? cur_tile.bs_off : next_tile.bs_off;", "bs_off = cur_tile.bs_off;"),
     ("wgrad: B of every expert from the first step on", "            t.b += first_step * BK;\n", ""),
     ("wgrad: second step of a one-step tile fetched past its expert", "        if (cur_tile.steps == 1) {", "        if (false) {"),
-    ("wgrad: experts without a step not cleared", "(int64_t)i * 16) = make_uint4(0, 0, 0, 0);\n            }\n            prev = end;",
-     "(int64_t)i * 16) = make_uint4(1, 0, 0, 0);\n            }\n            prev = end;"),
-    ("wgrad: experts of the same number of steps share a place", " || (all_steps[e] == own.steps && e < tid);", ";"),
+    ("wgrad: experts without a step not cleared", "(int64_t)i * 16) = make_uint4(0, 0, 0, 0);", "(int64_t)i * 16) = make_uint4(1, 0, 0, 0);"),
+    ("wgrad: experts of the same number of steps share a place", "(uint32_t)steps1 * kMostKExperts + (kMostKExperts - 2 - 2 * lane)", "(uint32_t)steps1 * kMostKExperts + (kMostKExperts - 1 - 2 * lane)"),
     ("wgrad: tiles lost behind rounds that workgroups sit out", "min(max(round - 1, 0), skipped) * busy", "min(round, skipped) * busy"),
     ("wgrad: rounds that go backwards counted from the end of the whole round", "(round & 1 ? width - 1 - place : place)", "(round & 1 ? (int)gridDim.x - 1 - place : place)"),
 ]

@@ -49,6 +49,9 @@ inline uint32_t __float_as_uint(float f)
 #define gridDim (::wavesim::g.grid)
 #define __syncthreads() ::wavesim::block_sync()
 #define __shfl_xor(v, mask, width) ::wavesim::shfl_xor((v), (mask))
+#define __shfl(v, src, width) ::wavesim::shfl((v), (src))
+#define __ballot(b) ::wavesim::ballot(b)
+#define __popcll(v) __builtin_popcountll(v)
 
 #define __builtin_amdgcn_readfirstlane(x) ::wavesim::readfirstlane(x)
 #define __builtin_amdgcn_s_waitcnt(imm) ::wavesim::s_waitcnt(imm)

@@ -246,13 +246,24 @@ template <class T> inline T readfirstlane(T v)
     return r;
 }
 
-inline int shfl_xor(int v, int mask)
+inline int shfl(int v, int src)
 {
     Wave &w = publish(v);
-    const int src = g.cur->lane ^ mask;
-    if (src >= kWave || !w.present[src])
-        fail("__shfl_xor reads lane %d, which is not active", src);
+    if (src < 0 || src >= kWave || !w.present[src])
+        fail("a shuffle reads lane %d, which is not active", src);
     int r = peek<int>(w, src);
+    unpublish();
+    return r;
+}
+inline int shfl_xor(int v, int mask) { return shfl(v, g.cur->lane ^ mask); }
+
+inline uint64_t ballot(bool b)
+{
+    Wave &w = publish((int)b);
+    uint64_t r = 0;
+    for (int i = 0; i < kWave; ++i)
+        if (w.present[i] && peek<int>(w, i))
+            r |= (uint64_t)1 << i;
     unpublish();
     return r;
 }

@@ -183,12 +183,16 @@ ONE_HEAVY = [1, 1, 0, 10, 1, 1, 1, 1] + [0] * 56
 @pytest.mark.parametrize("M,N,bf16,tiled,workgroups,steps,mode",
                          [(264, 272, True, False, 5, UNEVEN, MODES[0]), (264, 768, False, True, 8, UNEVEN, MODES[3]),
                           (256, 512, False, True, 8, UNEVEN, MODES[3]), (512, 256, True, False, 5, ONE_HEAVY, MODES[0]),
+                          (256, 512, False, False, 128, UNEVEN, MODES[0]), (256, 512, True, True, 16, UNEVEN, MODES[3]),
+                          (256, 256, False, True, 5, [1, 0, 0, 0, 2, 0, 0, 0] * 16, MODES[0]),
                           (256, 256, True, True, 7, [0] * 126 + [1, 0, 2], MODES[0])],
-                         ids=["rowmajor", "tiled-by-xcd", "whole-tiles", "busy-workgroups", "more-experts-than-sorted"])
+                         ids=["rowmajor", "tiled-by-xcd", "whole-tiles", "busy-workgroups", "a-workgroup-per-tile", "one-round",
+                              "as-many-experts-as-sorted", "more-experts-than-sorted"])
 def test_grouped_wgrad_resident(hostmodel, tmp_path, M, N, bf16, tiled, workgroups, steps, mode):
     """Resident 256x256 tiles: experts of 0 .. 3 K steps side by side, so that requests one and two steps ahead end in the
     same tile, the next one and the one after it; ragged tiles moved back and whole ones; workgroups with several tiles and with
-    one; an expert with so many steps that its workgroups sit out a round; experts that stay with one tile per workgroup."""
+    one; an expert with so many steps that its workgroups sit out a round; a workgroup for every tile, so that those of empty
+    experts write the zeros; tiles of all experts in one round, where all write them; experts that stay with one tile per workgroup."""
     ends = [int(e) * 128 for e in np.cumsum(steps)]
     K = ends[-1]
     a = oracle.quantize_rowwise(si.gradients(M, K, seed=8, spikes=True))
@@ -198,3 +202,17 @@ def test_grouped_wgrad_resident(hostmodel, tmp_path, M, N, bf16, tiled, workgrou
     _, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_CUS=workgroups, **mode)
     assert calls[0] == (0, list(range(workgroups if len(steps) <= 128 else len(steps))))
     _wgrad_check(out, M, N, N + 16, ops, ends, bf16)
+
+
+@pytest.mark.parametrize("workgroups", [128, 5])
+def test_grouped_wgrad_resident_bad_ends_are_clamped(hostmodel, tmp_path, workgroups):
+    """Ends that are negative, that fall, that lie behind K, and the two of one work-item out of order."""
+    M, N, K = 256, 512, 768
+    ends = [-7, 256, 128, 128, 384, 0, 640, 9999, 512, -1] + [300] * 54
+    a = oracle.quantize_rowwise(si.gradients(M, K, seed=12, spikes=True))
+    b = oracle.quantize_rowwise(np.asarray(si.activations(N, K, seed=13, bf16=False), np.float32))
+    ops = (a[0], a[1], b[0], b[1])
+    line, out = _wgrad_case(tmp_path, M, N, K, ops, ends)
+    _, calls = run_case(hostmodel, tmp_path, [line], WAVESIM_CUS=workgroups)
+    assert calls[0] == (0, list(range(workgroups)))
+    _wgrad_check(out, M, N, N, ops, ends, False)
